@@ -30,8 +30,9 @@
  *     nothing is launched; ccl_last_error() gives a per-thread message.
  *   - Tuning overrides, read when a plan is made: CCL_GEMM_TILE=RxC (kernel
  *     tile 256x256, 256x128, 128x256 or 128x128), CCL_GEMM_WAVES=4|8 (waves
- *     per workgroup; 8, the default, exists for every bf16 tile and for fp8
- *     256x256 tiles) and CCL_GEMM_GROUP_M=n (rows of the tile raster group).
+ *     per workgroup; 8, the default, exists for every bf16 tile, for fp8
+ *     256x256 tiles and, where K / Gr and K / Gc are multiples of 128, for
+ *     the other fp8 tiles) and CCL_GEMM_GROUP_M=n (rows of the tile raster group).
  *     Unset, the plan chooses.
  *
  * CCL layout of an operand X (R x Cc) under a Gr x Gc grid (the same grid

@@ -137,11 +137,14 @@ void choose_gemm_config(Plan* p) {
   int gm = panels_touched(g, 8) < panels_touched(g, 4) ? 8 : 4;
   if (const char* e = std::getenv("CCL_GEMM_GROUP_M")) gm = std::max(1, std::atoi(e));
   g.group_m = (int)std::min<int64_t>(gm, g.tiles_m);
-  // Waves per workgroup: 8 (two per SIMD) for every bf16 tile and for fp8
-  // 256x256 tiles, 4 for the other fp8 tiles. On the Qwen3 shapes the 8-wave
-  // forms of the 256x128 and 128x128 tiles measured 0-10 % faster than 4.
+  // Waves per workgroup: 8 (two per SIMD) for every bf16 tile, for fp8
+  // 256x256 tiles and for the other fp8 tiles where both K blocks are
+  // multiples of 128 (gemm_fp8s_kernel's stage), 4 for fp8 tiles below
+  // 256x256 otherwise. On the Qwen3 shapes the 8-wave forms of the bf16
+  // 256x128 and 128x128 tiles measured 0-10 % faster than 4.
   // CCL_GEMM_WAVES=4 selects the 4-wave form.
-  const bool eight_ok = (btm == 256 && btn == 256) || p->ab_type == DT_BF16;
+  const bool eight_ok = (btm == 256 && btn == 256) || p->ab_type == DT_BF16 ||
+                        ((p->K / p->Gc) % 128 == 0 && (p->K / p->Gr) % 128 == 0);
   g.waves = eight_ok ? 8 : 4;
   if (const char* e = std::getenv("CCL_GEMM_WAVES"))
     g.waves = (std::atoi(e) == 8 && eight_ok) ? 8 : 4;

@@ -13,6 +13,8 @@
 //    fragment reads pipelined across steps;
 //  * gemm_fp8x_kernel: the same plans with two stages and the fragment reads
 //    after each step's barrier (CCL_GEMM_FP8_PIPE=0);
+//  * gemm_fp8s_kernel: fp8 tiles below 256x256 with 8 waves and K blocks that
+//    are multiples of 128 (128-K stages);
 //  * gemm_fp8_kernel: the other fp8 plans (v_mfma_f32_32x32x64_f8f6f4).
 //
 // bf16: workgroup = 2 x WGN waves, output tile BM x BN, K step 32 (kBK).
@@ -376,7 +378,7 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
   constexpr int HALF = BM / 2;              // rows per half
   constexpr int RPI = 64 / CPR;             // rows per wave-wide 16-byte access
   constexpr int RPW = BM / NW;              // rows copied out per wave
-  static_assert(WM == HALF, "a wave's rows lie in one half");
+  static_assert(HALF % WM == 0, "a wave's rows lie in one half");
   static_assert(RPW % RPI == 0, "whole accesses per wave");
   // No wave reads the stage buffers any more and no load into them is in
   // flight (the direct-to-LDS loads of the last steps included).
@@ -384,10 +386,10 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  char* half = wm ? hi : lo;
+  char* half = wm * WM < HALF ? lo : hi;
 #pragma unroll
   for (int mt = 0; mt < TM; ++mt) {
-    const int r = mt * 16 + (lane & 15);
+    const int r = (wm * WM) % HALF + mt * 16 + (lane & 15);
 #pragma unroll
     for (int nt = 0; nt < TN; ++nt) {
       const int col = wn * WN + nt * 16 + 4 * (lane >> 4);
@@ -422,11 +424,12 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
 // that workgroup ((w >> 3) / kChunks) * 8 + (w & 7) of the unsplit GEMM
 // computes, so it runs on the XCD that wrote the partials. Each thread sums
 // its float4 over the splits in ascending order and writes C through store4.
-// MD is the MFMA tile of the GEMM kernel that wrote the partials.
-template <int BM, int BN, int WGN, int MD>
+// MD is the MFMA tile and WGM x WGN the wave grid of the GEMM kernel that
+// wrote the partials.
+template <int BM, int BN, int WGN, int MD, int WGM = 2>
 __global__ void __launch_bounds__(256) splitk_reduce_kernel(GemmParams p) {
   using L = AccLayout<MD>;
-  constexpr int WM = BM / 2, WN = BN / WGN;
+  constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / MD, TN = WN / MD;
   constexpr int kChunks = BM * BN / (4 * 256);
   const int64_t slot = blockIdx.x >> 3;
@@ -2248,6 +2251,274 @@ __global__ void __launch_bounds__(512, 2) gemm_fp8p_kernel(GemmParams p) {
 #endif
 }
 
+// ---------------------------------------------------------------------------
+// fp8 tiles below 256x256 with 128-K stages (gemm_fp8s_kernel): the MFMA
+// (16x16x128), K order, fragment layout and swizzles of gemm_fp8x_kernel, so
+// A rows in LDS are whole 128-byte lines, in a ring of 3 (256x128, 128x256)
+// or 4 (128x128) stages and with gemm_kernel's step: the MFMAs of the first
+// half of the A fragments, behind them the reads of the other half and the
+// loads NS - 1 stages ahead; barrier; the MFMAs of the second half, behind
+// them the next stage's first fragments.
+//
+// Bound by feeding the matrix cores from L2 and LDS (12-24 tiles on an XCD's
+// 32 CUs; a copy whose operands all sit in L2 runs 7-11 % faster). Against
+// gemm_fp8_kernel (4 waves, 64-byte A rows; C identical bit for bit), us per
+// launch on one box: 4096x1536x2048 20.7 -> 15.7, 4096x768x2048 12.7 -> 10.3,
+// 768x2048x4096 18.7 -> 14.8 (split-K 2: 17.6 -> 16.5), 1024x5120x4096 31.1
+// -> 23.2. The same kernel with 4 waves: 17.7 / 11.7 / 17.0 / 27.3.
+// ---------------------------------------------------------------------------
+
+template <int BM, int BN, int WGM, int WGN>
+struct Tile8s {
+  static constexpr int NW = WGM * WGN;                 // waves per workgroup
+  static constexpr int THREADS = 64 * NW;
+  static constexpr int WM = BM / WGM, WN = BN / WGN;   // wave tile
+  static constexpr int TM = WM / 16, TN = WN / 16;     // MFMA tiles per wave
+  static constexpr int A_BYTES = BM * kBK8x;           // one stage
+  static constexpr int B_BYTES = kBK8x * BN;
+  static constexpr int NA = A_BYTES / (1024 * NW);     // 8 A rows of 128 B per load
+  static constexpr int CPR_B = BN / 16;
+  static constexpr int RPI_B = 64 / CPR_B;
+  static constexpr int NB = B_BYTES / (1024 * NW);
+  static constexpr int NL = NA + NB;
+  static constexpr int NS = (160 * 1024) / (A_BYTES + B_BYTES) >= 4 ? 4 : 3;
+  static_assert(BM * BN < 256 * 256, "256x256 tiles use the pipelined kernel");
+  static_assert(NA >= 1 && NB >= 1 && TM % 2 == 0 && TN >= 1, "tile too small for the wave grid");
+  static_assert(NS * (A_BYTES + B_BYTES) <= 160 * 1024, "LDS stages exceed 160 KiB");
+  static_assert((NS - 2) * NL <= 63, "the stage wait count exceeds vmcnt's range");
+  static_assert(BN == 128 || BN == 256, "B swizzle is defined for 128- and 256-byte rows");
+};
+
+template <int BM, int BN, int WGM, int WGN>
+__global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 4) gemm_fp8s_kernel(GemmParams p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  using T = Tile8s<BM, BN, WGM, WGN>;
+  constexpr int NS = T::NS;
+  __shared__ __attribute__((aligned(1024))) char smA[NS][T::A_BYTES];
+  __shared__ __attribute__((aligned(1024))) char smB[NS][T::B_BYTES];
+
+  int32_t pr, pc, ti, tj, split;
+  if (!tile_of_block(p, &pr, &pc, &ti, &tj, &split)) return;
+  const int32_t k0 = __builtin_amdgcn_readfirstlane(split * p.ksteps_per_split);
+  const int32_t ksteps = __builtin_amdgcn_readfirstlane(min(p.ksteps, k0 + p.ksteps_per_split) - k0);
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+
+  // ---- global -> LDS: byte offsets from the tile corner of a stage, minus
+  // the instruction offset 1024 (i % 4) of load i in its run of up to four
+  // that share M0 (row >= 8 i and ld >= 128, so they stay non-negative) ----
+  uint32_t a_voff[T::NA];
+#pragma unroll
+  for (int i = 0; i < T::NA; ++i) {
+    const int row = 8 * (wave * T::NA + i) + (lane >> 3);
+    const int chunk = (lane & 7) ^ swz_a8x(row);
+    a_voff[i] = (uint32_t)(row * p.a.ld + chunk * 16) - 1024u * (i & 3);
+  }
+  uint32_t b_voff[T::NB];
+#pragma unroll
+  for (int i = 0; i < T::NB; ++i) {
+    const int row = T::RPI_B * (wave * T::NB + i) + lane / T::CPR_B;
+    const int chunk = (lane % T::CPR_B) ^ swz_b8x<BN>(row);
+    b_voff[i] = (uint32_t)(row * p.b.ld + chunk * 16) - 1024u * (i & 3);
+  }
+
+  // ---- LDS fragment read offsets (bytes) ----
+  int32_t a_rd[2];
+  {
+    const int row = wm * T::WM + (lane & 15);
+    const int g = lane >> 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) a_rd[h] = row * kBK8x + (((4 * h + g) ^ swz_a8x(row)) * 16);
+  }
+  int32_t b_rd[T::TN][4];
+  {
+    const int g = lane >> 4, s = lane & 15;
+#pragma unroll
+    for (int nt = 0; nt < T::TN; ++nt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int krow = 64 * (r >> 1) + 16 * g + 8 * (r & 1) + (s >> 1);
+        const int col = wn * T::WN + nt * 16 + 8 * (s & 1);
+        b_rd[nt][r] = krow * BN + (((col >> 4) ^ swz_b8x<BN>(krow)) * 16) + (col & 15);
+      }
+    }
+  }
+
+  // One descriptor per operand for the whole tile over all K blocks (the
+  // launch checks that both extents fit in 31 bits); a stage is selected by
+  // the loads' scalar offset.
+  const int32_t K = p.ksteps * kBK8x;
+  const int32_t a_extent = (K / p.a.kslice - 1) * p.a.slice + (BM - 1) * p.a.ld + p.a.kslice;
+  const int32_t b_extent = (int32_t)((K / p.b.kslice - 1) * p.b.slice +
+                                     (int64_t)(p.b.kslice - 1) * p.b.ld + BN);
+  const char* A = reinterpret_cast<const char*>(p.A);
+  const char* B = reinterpret_cast<const char*>(p.B);
+  const i32x4 a_desc = buffer_rsrc(A + pr * p.a.part + (int64_t)(ti * BM) * p.a.ld, a_extent);
+  const i32x4 b_desc = buffer_rsrc(B + pc * p.b.part + tj * BN, b_extent);
+  int64_t a_slice_off, b_slice_off;
+  int32_t a_kl, b_kl;
+  k_start(p.a, k0 * kBK8x, &a_slice_off, &a_kl);
+  k_start(p.b, k0 * kBK8x, &b_slice_off, &b_kl);
+  const int32_t a_steps = p.a.kslice / kBK8x, b_steps = p.b.kslice / kBK8x;
+  int32_t a_left = a_steps - a_kl / kBK8x, b_left = b_steps - b_kl / kBK8x;
+  const uint32_t a_adv = kBK8x, a_adv_wrap = (uint32_t)(kBK8x + p.a.slice - p.a.kslice);
+  const uint32_t b_adv = (uint32_t)(kBK8x * p.b.ld);
+  const uint32_t b_adv_wrap = (uint32_t)(b_adv + p.b.slice - (int64_t)p.b.kslice * p.b.ld);
+  uint32_t a_so = (uint32_t)(a_slice_off + a_kl);
+  uint32_t b_so = (uint32_t)(b_slice_off + (int64_t)b_kl * p.b.ld);
+  struct StageSrc {
+    i32x4 ra, rb;
+    uint32_t sa, sb;
+  };
+  // The next stage: the descriptors (empty past the last step, so no memory
+  // is touched) and the stage's byte offsets.
+  auto next_src = [&](bool live) __attribute__((always_inline)) {
+    StageSrc d;
+    d.ra = a_desc;
+    d.rb = b_desc;
+    if (!live) d.ra[2] = d.rb[2] = 0;
+    d.sa = a_so;
+    d.sb = b_so;
+    const bool a_wrap = --a_left == 0;
+    a_so += a_wrap ? a_adv_wrap : a_adv;
+    a_left = a_wrap ? a_steps : a_left;
+    const bool b_wrap = --b_left == 0;
+    b_so += b_wrap ? b_adv_wrap : b_adv;
+    b_left = b_wrap ? b_steps : b_left;
+    return d;
+  };
+  auto load_run = [&](const i32x4& r, uint32_t voff, uint32_t so, char* dst, int i)
+      __attribute__((always_inline)) {
+    if ((i & 3) == 0) lds_dma16_first(r, voff, so, dst + i * 1024);
+    else if ((i & 3) == 1) lds_dma16_next<1024>(r, voff, so);
+    else if ((i & 3) == 2) lds_dma16_next<2048>(r, voff, so);
+    else lds_dma16_next<3072>(r, voff, so);
+  };
+  auto load_one = [&](const StageSrc& d, char* sA, char* sB, int i) __attribute__((always_inline)) {
+    if (i < T::NA) load_run(d.ra, a_voff[i], d.sa, sA + wave * T::NA * 1024, i);
+    else load_run(d.rb, b_voff[i - T::NA], d.sb, sB + wave * T::NB * 1024, i - T::NA);
+  };
+
+  constexpr int kHalfM = T::TM / 2;
+  i32x8 fa[T::TM], fb0[T::TN], fb1[T::TN];
+  // A read i of a half step: fragment i / 2, half i % 2.
+  auto read_a = [&](const char* sA, int mt, int h) __attribute__((always_inline)) {
+    const i32x4v v = *(const lds_i32x4*)(sA + a_rd[h] + mt * 16 * kBK8x);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) fa[mt][4 * h + q] = v[q];
+  };
+  auto read_b = [&](const char* sB, i32x8 (&fb)[T::TN], int i) __attribute__((always_inline)) {
+    const int nt = i >> 2, r = i & 3;
+    const i32x2 v = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)(sB + b_rd[nt][r]));
+    fb[nt][2 * r] = v[0];
+    fb[nt][2 * r + 1] = v[1];
+  };
+
+  f32x4 acc[T::TM][T::TN];
+#pragma unroll
+  for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
+  auto mfma_one = [&](const i32x8 (&fb)[T::TN], int mt, int nt) __attribute__((always_inline)) {
+    acc[mt][nt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fb[nt], fa[mt], acc[mt][nt], 0, 0,
+                                                                  0, 0, 0, 0);
+  };
+  auto stage_barrier = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm((NS - 2) * T::NL, 0));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+
+  // One step on stage (sA, sB): on entry A fragments 0 .. kHalfM-1 and fb
+  // hold its data. Memory operations are spread evenly behind the MFMAs.
+  auto step = [&](const char* sA, const i32x8 (&fb)[T::TN], i32x8 (&fbn)[T::TN], char* lA, char* lB,
+                  const char* nA, const char* nB, const StageSrc& d) __attribute__((always_inline)) {
+    constexpr int kMfma = kHalfM * T::TN;
+    constexpr int kOps1 = 2 * kHalfM + T::NL;
+    constexpr int kOps2 = 2 * kHalfM + 4 * T::TN;
+#pragma unroll
+    for (int i = 0; i < kMfma; ++i) {
+      mfma_one(fb, i / T::TN, i % T::TN);
+#pragma unroll
+      for (int q = i * kOps1 / kMfma; q < (i + 1) * kOps1 / kMfma; ++q) {
+        if (q < 2 * kHalfM) read_a(sA, kHalfM + q / 2, q & 1);
+        else load_one(d, lA, lB, q - 2 * kHalfM);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    stage_barrier();
+#pragma unroll
+    for (int i = 0; i < kMfma; ++i) {
+      mfma_one(fb, kHalfM + i / T::TN, i % T::TN);
+#pragma unroll
+      for (int q = i * kOps2 / kMfma; q < (i + 1) * kOps2 / kMfma; ++q) {
+        if (q < 2 * kHalfM) read_a(nA, q / 2, q & 1);
+        else read_b(nB, fbn, q - 2 * kHalfM);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+#pragma unroll
+  for (int j = 0; j < NS - 1; ++j) {
+    const StageSrc d = next_src(j < ksteps);
+#pragma unroll
+    for (int i = 0; i < T::NL; ++i) load_one(d, smA[j], smB[j], i);
+  }
+  stage_barrier();
+#pragma unroll
+  for (int q = 0; q < 2 * kHalfM; ++q) read_a(smA[0], q / 2, q & 1);
+#pragma unroll
+  for (int q = 0; q < 4 * T::TN; ++q) read_b(smB[0], fb0, q);
+  // Step s (phase ph = s modulo kRound) works on stage s % NS, loads stage
+  // (s + NS - 1) % NS and reads stage (s + 1) % NS; the B fragment sets
+  // alternate.
+  auto phase_step = [&](auto PH, bool live) __attribute__((always_inline)) {
+    constexpr int ph = decltype(PH)::value;
+    const StageSrc d = next_src(live);
+    if constexpr (ph % 2 == 0)
+      step(smA[ph % NS], fb0, fb1, smA[(ph + NS - 1) % NS], smB[(ph + NS - 1) % NS],
+           smA[(ph + 1) % NS], smB[(ph + 1) % NS], d);
+    else
+      step(smA[ph % NS], fb1, fb0, smA[(ph + NS - 1) % NS], smB[(ph + NS - 1) % NS],
+           smA[(ph + 1) % NS], smB[(ph + 1) % NS], d);
+  };
+  // Whole rounds of steps whose loads all exist, branch-free; then the rest,
+  // each behind a (uniform) bound check.
+  constexpr int kRound = NS % 2 ? 2 * NS : NS;
+  int32_t s = 0;
+#define CCL_FP8S_LIVE(k) if constexpr (k < kRound) phase_step(std::integral_constant<int, k>{}, true)
+  for (; s + kRound + NS - 1 <= ksteps; s += kRound) {
+    CCL_FP8S_LIVE(0); CCL_FP8S_LIVE(1); CCL_FP8S_LIVE(2);
+    CCL_FP8S_LIVE(3); CCL_FP8S_LIVE(4); CCL_FP8S_LIVE(5);
+  }
+#undef CCL_FP8S_LIVE
+#define CCL_FP8S_REST(k) \
+  if constexpr (k < kRound) { if (s + k < ksteps) phase_step(std::integral_constant<int, k>{}, s + k + NS - 1 < ksteps); }
+  for (; s < ksteps; s += kRound) {
+    CCL_FP8S_REST(0); CCL_FP8S_REST(1); CCL_FP8S_REST(2);
+    CCL_FP8S_REST(3); CCL_FP8S_REST(4); CCL_FP8S_REST(5);
+  }
+#undef CCL_FP8S_REST
+
+  static_assert((BM / 2) * BN * 2 <= NS * T::A_BYTES && (BM / 2) * BN * 2 <= NS * T::B_BYTES,
+                "each half of the bf16 C tile fits in one operand's stage buffers");
+  int ln = lane;
+  asm volatile("" : "+v"(ln));
+  if (p.epi == 0 && !p.c_f32 && !p.ws)
+    store_tile_staged<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, true>(
+        p, acc, &smA[0][0], &smB[0][0], pr, pc, ti, tj, wm, wn, wave, ln);
+  else
+    store_tile<BM, BN, 16, T::TM, T::TN, T::WM, T::WN>(p, acc, pr, pc, ti, tj, split, wm, wn, ln);
+#endif
+}
+
 // Records, per workgroup of the GEMM grid, the XCD it ran on and its tile.
 __global__ void __launch_bounds__(64) dispatch_probe_kernel(TileMap map, int32_t tiles_m,
                                                             int32_t tiles_n, int32_t* out) {
@@ -2302,23 +2573,25 @@ hipError_t scratch_workspace(float** ws) {
 }
 
 // Second launch of a split-K GEMM: sum the partials of every tile into C.
-static hipError_t launch_splitk_reduce(const Plan& p, GemmParams gp, hipStream_t stream) {
+// md, waves and wgm are the MFMA tile, the waves and the rows of the wave grid
+// of the kernel that wrote them, which set their fragment order.
+static hipError_t launch_splitk_reduce(const Plan& p, GemmParams gp, int md, int waves,
+                                       hipStream_t stream, int wgm = 2) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   gp.map = tile_map(p, 1);
   const dim3 grid((unsigned)splitk_reduce_workgroups(p));
   const GemmConfig& g = p.gemm;
-  // The partials are in the fragment order of the kernel that wrote them:
-  // 16x16 MFMA tiles for bf16, 32x32 for fp8.
-  const int md = p.ab_type == DT_FP8_E4M3 ? 32 : 16;
 #define CCL_REDUCE(BM_, BN_, WGN_, MD_) \
   hipLaunchKernelGGL((splitk_reduce_kernel<BM_, BN_, WGN_, MD_>), grid, dim3(256), 0, stream, gp)
 #define CCL_REDUCE_MD(BM_, BN_, WGN_) \
   do { if (md == 16) CCL_REDUCE(BM_, BN_, WGN_, 16); else CCL_REDUCE(BM_, BN_, WGN_, 32); } while (0)
-  if (g.tile_m == 256 && g.tile_n == 256 && g.waves == 8) CCL_REDUCE_MD(256, 256, 4);
-  else if (g.tile_m == 256 && g.tile_n == 128 && g.waves == 8) CCL_REDUCE_MD(256, 128, 4);
-  else if (g.tile_m == 128 && g.tile_n == 256 && g.waves == 8) CCL_REDUCE_MD(128, 256, 4);
-  else if (g.tile_m == 128 && g.tile_n == 128 && g.waves == 8) CCL_REDUCE_MD(128, 128, 4);
+  if (g.tile_m == 256 && g.tile_n == 256 && waves == 8) CCL_REDUCE_MD(256, 256, 4);
+  else if (g.tile_m == 256 && g.tile_n == 128 && waves == 8 && wgm == 4)
+    hipLaunchKernelGGL((splitk_reduce_kernel<256, 128, 2, 16, 4>), grid, dim3(256), 0, stream, gp);
+  else if (g.tile_m == 256 && g.tile_n == 128 && waves == 8) CCL_REDUCE(256, 128, 4, 16);
+  else if (g.tile_m == 128 && g.tile_n == 256 && waves == 8) CCL_REDUCE(128, 256, 4, 16);
+  else if (g.tile_m == 128 && g.tile_n == 128 && waves == 8) CCL_REDUCE(128, 128, 4, 16);
   else if (g.tile_m == 256 && g.tile_n == 256) CCL_REDUCE_MD(256, 256, 2);
   else if (g.tile_m == 256 && g.tile_n == 128) CCL_REDUCE_MD(256, 128, 2);
   else if (g.tile_m == 128 && g.tile_n == 256) CCL_REDUCE_MD(128, 256, 2);
@@ -2390,11 +2663,40 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
                        stream, gp);
     return hipGetLastError();
   }
+  // fp8 below 256x256 with 8 waves (the plan's choice where both K blocks are
+  // multiples of 128): 128-K stages, with split-K only where the K ranges of
+  // 64-K steps are whole stages, and extents within the descriptors' 31 bits.
+  const int waves8 = g.tile_m == 256 && g.tile_n == 256 ? waves : 4;
+  if (fp8 && waves == 8 && !(g.tile_m == 256 && g.tile_n == 256) && a.kslice % kBK8x == 0 &&
+      b.kslice % kBK8x == 0) {
+    const int64_t lim = ((int64_t)1 << 31) - 4096;
+    const bool fits = (p.K / a.kslice - 1) * a.slice + 256 * (int64_t)a.ld < lim &&
+                      (p.K / b.kslice - 1) * b.slice + (int64_t)b.kslice * b.ld + 256 < lim;
+    const int32_t ks128 = (int32_t)(p.K / kBK8x);
+    const int32_t per128 = (ks128 + splits - 1) / splits;
+    if (fits && (splits == 1 || 2 * per128 == gp.ksteps_per_split)) {
+      gp.ksteps = ks128;
+      gp.ksteps_per_split = per128;
+#define CCL_LAUNCH8S(BM_, BN_, WGM_, WGN_)                                                  \
+  hipLaunchKernelGGL((gemm_fp8s_kernel<BM_, BN_, WGM_, WGN_>), grid,                        \
+                     dim3(Tile8s<BM_, BN_, WGM_, WGN_>::THREADS), 0, stream, gp)
+      // wave tiles of 64x64 for 256x128 (a 4 x 2 grid reads 176 KiB of LDS per
+      // stage, 2 x 4 208 KiB: 1.5-3.5 % faster), 64x64 and 64x32 otherwise
+      const bool tall = g.tile_m == 256;
+      if (tall && g.tile_n == 128) CCL_LAUNCH8S(256, 128, 4, 2);
+      else if (g.tile_m == 128 && g.tile_n == 256) CCL_LAUNCH8S(128, 256, 2, 4);
+      else if (g.tile_m == 128 && g.tile_n == 128) CCL_LAUNCH8S(128, 128, 2, 4);
+      else return hipErrorInvalidValue;
+#undef CCL_LAUNCH8S
+      return splits > 1 ? launch_splitk_reduce(p, gp, 16, waves, stream, tall ? 4 : 2)
+                        : hipGetLastError();
+    }
+  }
   if (fp8) {
 #define CCL_LAUNCH8(BM_, BN_, WGN_)                                                    \
   hipLaunchKernelGGL((gemm_fp8_kernel<BM_, BN_, WGN_>), grid, dim3(Tile8<BM_, BN_, WGN_>::THREADS), \
                      0, stream, gp)
-    if (g.tile_m == 256 && g.tile_n == 256 && waves == 8)
+    if (g.tile_m == 256 && g.tile_n == 256 && waves8 == 8)
       CCL_LAUNCH8(256, 256, 4);
     else if (g.tile_m == 256 && g.tile_n == 256)
       CCL_LAUNCH8(256, 256, 2);
@@ -2407,7 +2709,7 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
     else
       return hipErrorInvalidValue;
 #undef CCL_LAUNCH8
-    return splits > 1 ? launch_splitk_reduce(p, gp, stream) : hipGetLastError();
+    return splits > 1 ? launch_splitk_reduce(p, gp, 32, waves8, stream) : hipGetLastError();
   }
   // 64-K stages (plan's choice for the bf16 tiles below 256x256): both K
   // blocks a multiple of 64, the 4-step rounds' extents (255 rows of A or
@@ -2436,7 +2738,7 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
       else if (g.tile_m == 128 && g.tile_n == 128) CCL_LAUNCH64(128, 128);
       else return hipErrorInvalidValue;
 #undef CCL_LAUNCH64
-      return splits > 1 ? launch_splitk_reduce(p, gp, stream) : hipGetLastError();
+      return splits > 1 ? launch_splitk_reduce(p, gp, 16, waves, stream) : hipGetLastError();
     }
   }
   // The 64-K-pair kernel's A descriptor spans the tile's 256 rows over all
@@ -2469,7 +2771,7 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
   else
     return hipErrorInvalidValue;
 #undef CCL_LAUNCH
-  return splits > 1 ? launch_splitk_reduce(p, gp, stream) : hipGetLastError();
+  return splits > 1 ? launch_splitk_reduce(p, gp, 16, waves, stream) : hipGetLastError();
 }
 
 hipError_t launch_dispatch_probe(const Plan& p, int32_t* out, hipStream_t stream) {
