@@ -356,19 +356,21 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, const Acc (&acc)
 }
 
 // Epilogue of the kernels with 16x16 MFMA tiles (bf16, fp8 16x16x128) for a
-// plain bf16 C (alpha 1, beta 0, no split-K), staged through LDS so that C leaves the CU in whole 128-byte
-// lines. The direct form (store_tile) writes 8 bytes per lane, i.e. 32-byte
+// bf16 C that is not read (beta 0, no split-K), staged through LDS so that C
+// leaves the CU in whole 128-byte lines. The direct form (store_tile) writes 8 bytes per lane, i.e. 32-byte
 // pieces of 16 rows per instruction, and a CU then issues its C tile at
 // about 17 GB/s. Here each wave first writes its bf16 values into the
 // (then idle) stage buffers: rows 0 .. BM/2 - 1 of the tile into `lo`,
 // rows BM/2 .. BM - 1 into `hi`, row pitch BN * 2 bytes, with the 16-byte
 // chunk index XORed with (row mod 16) so that the 16 rows of one write fall
 // in distinct banks. Then every wave copies BM / NW whole rows to C, 16
-// bytes per lane. NT marks the stores to C non-temporal (C is not read back
+// bytes per lane. SCALED: alpha != 1 (dequantised fp8 products; staging them
+// too took 4096x1536x2048 fp8 from 18.7 to 15.6 us, 8192x28672x8192 fp8 from
+// 1385 to 1349). NT marks the stores to C non-temporal (C is not read back
 // by the kernel); the 64-K-stage kernel uses it, where its Qwen3-shaped
 // launches (gate/up, dH) ran 1.5-3 % faster with it, measured alternating,
 // and so does the pipelined fp8 kernel.
-template <int BM, int BN, int NW, int TM, int TN, int WM, int WN, bool NT = false>
+template <int BM, int BN, int NW, int TM, int TN, int WM, int WN, bool NT, bool SCALED>
 __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32x4 (&acc)[TM][TN],
                                                   char* lo, char* hi, int32_t pr, int32_t pc,
                                                   int32_t ti, int32_t tj, int wm, int wn, int wave,
@@ -393,9 +395,11 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
 #pragma unroll
     for (int nt = 0; nt < TN; ++nt) {
       const int col = wn * WN + nt * 16 + 4 * (lane >> 4);
+      f32x4 o = acc[mt][nt];
+      if constexpr (SCALED) o *= p.alpha;
       uint2 v;
-      v.x = bf16_rne(acc[mt][nt][0]) | (bf16_rne(acc[mt][nt][1]) << 16);
-      v.y = bf16_rne(acc[mt][nt][2]) | (bf16_rne(acc[mt][nt][3]) << 16);
+      v.x = bf16_rne(o[0]) | (bf16_rne(o[1]) << 16);
+      v.y = bf16_rne(o[2]) | (bf16_rne(o[3]) << 16);
       *reinterpret_cast<uint2*>(half + r * ROWB + (((col >> 3) ^ (r & 15)) << 4) + ((col >> 2) & 1) * 8) = v;
     }
   }
@@ -416,6 +420,131 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
       __builtin_nontemporal_store(__builtin_bit_cast(i32x4, v), reinterpret_cast<i32x4*>(dst));
     else
       *dst = v;
+  }
+}
+
+// The same for an fp32 C and for a C that is read (beta != 0): the fp32
+// accumulators are staged, and each wave combines whole rows with C as it
+// copies them out (the formulas of store4). Each half of the tile goes
+// through its buffer in P passes of RP rows. The old C values of a pass are
+// loaded before its accumulators are staged, so their latency overlaps the
+// LDS writes and the barrier. Bound by the write-out: all CUs finish a tile
+// together. Against 16-row pieces straight from the registers, us per launch
+// on one box: 8192x28672x8192, fp32 C += 2842 -> 2764 (a plain bf16 C: 2570);
+// 8192x8192x3584, fp32 C 359 -> 353, C += 412 -> 396; 4096x1536x2048, bf16
+// C += 31.3 -> 27.6, fp32 C 30.0 -> 28.4. Plain stores instead of
+// non-temporal ones: 0-3 % slower on a C that is not read, else the same.
+template <int BM, int BN, int NW, int TM, int TN, int WM, int WN, int BUF, bool F32>
+__device__ __forceinline__ void store_tile_staged_f32(const GemmParams& p, const f32x4 (&acc)[TM][TN],
+                                                      char* lo, char* hi, int32_t pr, int32_t pc,
+                                                      int32_t ti, int32_t tj, int wm, int wn,
+                                                      int wave, int lane) {
+  constexpr int HALF = BM / 2;
+  constexpr int ROWB = BN * 4;                        // bytes per row in LDS
+  constexpr int CPR = BN / 4;                         // 16-byte chunks (4 columns) per row
+  constexpr int RPI = 64 / CPR;                       // rows per wave-wide access
+  constexpr int kPassBytes = BUF < 4 * NW * RPI * ROWB ? BUF : 4 * NW * RPI * ROWB;
+  // Passes: each half's rows of a pass fit in BUF, and a lane holds at most
+  // 8 old C values of 4 columns at once (32 registers beside the accumulators).
+  constexpr int P = (HALF * ROWB + kPassBytes - 1) / kPassBytes;
+  constexpr int RP = HALF / P;                        // rows of each half per pass
+  constexpr int RPW = 2 * RP / NW;                    // rows copied out per wave and pass
+  constexpr int NI = RPW / RPI;
+  static_assert(HALF % WM == 0 && RP % 16 == 0 && RP * P == HALF, "whole MFMA tiles per pass");
+  static_assert(RP % WM == 0 || WM % RP == 0, "a wave's rows nest in the passes");
+  static_assert(RP * ROWB <= BUF && RPW % RPI == 0 && RP % RPW == 0, "whole accesses per wave");
+  __builtin_amdgcn_s_waitcnt(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  const int64_t c_tile = pr * p.c.part + pc * p.c.slice + (int64_t)(ti * BM) * p.c.ld + tj * BN;
+  const int c = lane % CPR;
+  const int row0 = wave * RPW + lane / CPR;           // first staged row of this lane in a pass
+  char* half = wm * WM < HALF ? lo : hi;
+#pragma unroll
+  for (int ps = 0; ps < P; ++ps) {
+    // rows 0 .. RP-1 of a pass are the first half's, RP .. 2 RP-1 the second's
+    const int64_t at = c_tile + (int64_t)((row0 < RP ? row0 : row0 - RP + HALF) + ps * RP) * p.c.ld + 4 * c;
+    f32x4 old[NI];
+    if (p.epi == 2) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int64_t idx = at + (int64_t)(i * RPI) * p.c.ld;
+        if constexpr (F32) {
+          old[i] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.C) + idx);
+        } else {
+          const uint2 b = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.C) + idx);
+          old[i] = f32x4{__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xffff0000u),
+                         __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xffff0000u)};
+        }
+      }
+    }
+#pragma unroll
+    for (int mt = 0; mt < TM; ++mt) {
+      const int r0 = (wm * WM) % HALF + mt * 16 - ps * RP;   // wave-uniform
+      if (r0 < 0 || r0 >= RP) continue;
+      const int r = r0 + (lane & 15);
+#pragma unroll
+      for (int nt = 0; nt < TN; ++nt) {
+        const int ch = (wn * WN + nt * 16) / 4 + (lane >> 4);
+        *reinterpret_cast<f32x4*>(half + r * ROWB + ((ch ^ (r & 15)) << 4)) = acc[mt][nt];
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int row = row0 + i * RPI;
+      const int r = row < RP ? row : row - RP;
+      f32x4 o = *reinterpret_cast<const f32x4*>((row < RP ? lo : hi) + r * ROWB + ((c ^ (r & 15)) << 4));
+      if (p.epi == 2) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = __builtin_fmaf(p.alpha, o[j], p.beta * old[i][j]);
+      } else if (p.epi == 1) {
+        o *= p.alpha;
+      }
+      const int64_t idx = at + (int64_t)(i * RPI) * p.c.ld;
+      if constexpr (F32) {
+        __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + idx));
+      } else {
+        uint2 v;
+        v.x = bf16_rne(o[0]) | (bf16_rne(o[1]) << 16);
+        v.y = bf16_rne(o[2]) | (bf16_rne(o[3]) << 16);
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.C) + idx) = v;
+      }
+    }
+    if (ps + 1 < P) {
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    }
+  }
+}
+
+// The epilogue of the kernels with 16x16 MFMA tiles. lo and hi: the stage
+// arrays of A and B, idle after the K loop, with at least BUF bytes each.
+template <int BM, int BN, int NW, int TM, int TN, int WM, int WN, int BUF, bool NT>
+__device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&acc)[TM][TN], char* lo,
+                                           char* hi, int32_t pr, int32_t pc, int32_t ti, int32_t tj,
+                                           int32_t split, int wm, int wn, int wave, int lane) {
+  static_assert((BM / 2) * BN * 2 <= BUF, "each half of the bf16 C tile fits in one operand's buffers");
+  const bool direct = NW == 4 && (p.c_f32 || p.epi == 2);   // 4 waves: 256 accumulators, no registers left
+  if (!p.ws && !p.c_f32 && p.epi == 0)
+    store_tile_staged<BM, BN, NW, TM, TN, WM, WN, NT, false>(p, acc, lo, hi, pr, pc, ti, tj, wm, wn, wave, lane);
+  else if (p.ws || direct)
+    store_tile<BM, BN, 16, TM, TN, WM, WN>(p, acc, pr, pc, ti, tj, split, wm, wn, lane);
+  else if (!p.c_f32 && p.epi == 1)
+    store_tile_staged<BM, BN, NW, TM, TN, WM, WN, NT, true>(p, acc, lo, hi, pr, pc, ti, tj, wm, wn, wave, lane);
+  else if constexpr (NW == 8) {
+    if (p.c_f32)
+      store_tile_staged_f32<BM, BN, NW, TM, TN, WM, WN, BUF, true>(p, acc, lo, hi, pr, pc, ti, tj, wm, wn,
+                                                                   wave, lane);
+    else
+      store_tile_staged_f32<BM, BN, NW, TM, TN, WM, WN, BUF, false>(p, acc, lo, hi, pr, pc, ti, tj, wm, wn,
+                                                                    wave, lane);
   }
 }
 
@@ -768,13 +897,9 @@ __global__ void __launch_bounds__(128 * WGN, WGN / 2) gemm_kernel(GemmParams p) 
     tl_rt[2] = __builtin_amdgcn_s_memrealtime();
     tl_clk[1] = __builtin_amdgcn_s_memtime();
   }
-  static_assert((BM / 2) * BN * 2 <= NS * T::A_BYTES && (BM / 2) * BN * 2 <= NS * T::B_BYTES,
-                "each half of the bf16 C tile fits in one operand's stage buffers");
-  if (p.epi == 0 && !p.c_f32 && !p.ws)
-    store_tile_staged<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN>(p, acc, &smA[0][0], &smB[0][0], pr,
-                                                                 pc, ti, tj, wm, wn, wave, lane);
-  else
-    store_tile<BM, BN, 16, T::TM, T::TN, T::WM, T::WN>(p, acc, pr, pc, ti, tj, split, wm, wn, lane);
+  constexpr int kBuf = NS * T::A_BYTES < NS * T::B_BYTES ? NS * T::A_BYTES : NS * T::B_BYTES;
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, false>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+                                                                    ti, tj, split, wm, wn, wave, lane);
   if (tl_on) record_timeline(p.timeline + ((int64_t)blockIdx.x * T::NW + wave) * kTimelineWords,
                              tl_rt, tl_clk, lane);
 #endif
@@ -1087,13 +1212,9 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
     tl_rt[2] = __builtin_amdgcn_s_memrealtime();
     tl_clk[1] = __builtin_amdgcn_s_memtime();
   }
-  static_assert((BM / 2) * BN * 2 <= NS * T::A_BYTES && (BM / 2) * BN * 2 <= NS * T::B_BYTES,
-                "each half of the bf16 C tile fits in one operand's stage buffers");
-  if (p.epi == 0 && !p.c_f32 && !p.ws)
-    store_tile_staged<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, true>(
-        p, acc, &smA[0][0], &smB[0][0], pr, pc, ti, tj, wm, wn, wave, lane);
-  else
-    store_tile<BM, BN, 16, T::TM, T::TN, T::WM, T::WN>(p, acc, pr, pc, ti, tj, split, wm, wn, lane);
+  constexpr int kBuf = NS * T::A_BYTES < NS * T::B_BYTES ? NS * T::A_BYTES : NS * T::B_BYTES;
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, true>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+                                                                    ti, tj, split, wm, wn, wave, lane);
   if (tl_on) record_timeline(p.timeline + ((int64_t)blockIdx.x * T::NW + wave) * kTimelineWords,
                              tl_rt, tl_clk, lane);
 #endif
@@ -1429,13 +1550,9 @@ __global__ void __launch_bounds__(512, 2) gemm_a2_kernel(GemmParams p) {
     tl_rt[2] = __builtin_amdgcn_s_memrealtime();
     tl_clk[1] = __builtin_amdgcn_s_memtime();
   }
-  static_assert((BM / 2) * BN * 2 <= T::NP * T::A2_BYTES && (BM / 2) * BN * 2 <= T::NSB * T::B_BYTES,
-                "each half of the bf16 C tile fits in one operand's buffers");
-  if (p.epi == 0 && !p.c_f32 && !p.ws)
-    store_tile_staged<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN>(p, acc, &smA[0][0], &smB[0][0], pr,
-                                                                 pc, ti, tj, wm, wn, wave, lane);
-  else
-    store_tile<BM, BN, 16, T::TM, T::TN, T::WM, T::WN>(p, acc, pr, pc, ti, tj, split, wm, wn, lane);
+  constexpr int kBuf = T::NP * T::A2_BYTES < T::NSB * T::B_BYTES ? T::NP * T::A2_BYTES : T::NSB * T::B_BYTES;
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, false>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+                                                                    ti, tj, split, wm, wn, wave, lane);
   if (tl_on) record_timeline(p.timeline + ((int64_t)blockIdx.x * T::NW + wave) * kTimelineWords,
                              tl_rt, tl_clk, lane);
 #endif
@@ -1930,13 +2047,9 @@ __global__ void __launch_bounds__(128 * WGN, WGN / 2) gemm_fp8x_kernel(GemmParam
     step(0, false);
   }
 
-  static_assert((BM / 2) * BN * 2 <= 2 * T::A_BYTES && (BM / 2) * BN * 2 <= 2 * T::B_BYTES,
-                "each half of the bf16 C tile fits in one operand's stage buffers");
-  if (p.epi == 0 && !p.c_f32 && !p.ws)
-    store_tile_staged<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN>(p, acc, &smA[0][0], &smB[0][0], pr,
-                                                                 pc, ti, tj, wm, wn, wave, lane);
-  else
-    store_tile<BM, BN, 16, T::TM, T::TN, T::WM, T::WN>(p, acc, pr, pc, ti, tj, split, wm, wn, lane);
+  constexpr int kBuf = 2 * T::A_BYTES < 2 * T::B_BYTES ? 2 * T::A_BYTES : 2 * T::B_BYTES;
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, false>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+                                                                    ti, tj, split, wm, wn, wave, lane);
 #endif
 }
 
@@ -2234,8 +2347,6 @@ __global__ void __launch_bounds__(512, 2) gemm_fp8p_kernel(GemmParams p) {
   }
 #undef CCL_FP8P_PHASE
 
-  static_assert((BM / 2) * BN * 2 <= T::NSA * T::A_BYTES && (BM / 2) * BN * 2 <= T::NSB * T::B_BYTES,
-                "each half of the bf16 C tile fits in one operand's stage buffers");
   // The lane index, made opaque here so that the epilogue's addresses are
   // computed after the K loop instead of being hoisted before it (where
   // they would stay live through the loop and spill).
@@ -2243,11 +2354,9 @@ __global__ void __launch_bounds__(512, 2) gemm_fp8p_kernel(GemmParams p) {
   asm volatile("" : "+v"(ln));
   // Non-temporal C stores: at the power limit the fp8 GEMMs ran 1-4 % faster
   // with them, at a 1 % higher clock (same box, alternating).
-  if (p.epi == 0 && !p.c_f32 && !p.ws)
-    store_tile_staged<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, true>(
-        p, acc, &smA[0][0], &smB[0][0], pr, pc, ti, tj, wm, wn, wave, ln);
-  else
-    store_tile<BM, BN, 16, T::TM, T::TN, T::WM, T::WN>(p, acc, pr, pc, ti, tj, split, wm, wn, ln);
+  constexpr int kBuf = T::NSA * T::A_BYTES < T::NSB * T::B_BYTES ? T::NSA * T::A_BYTES : T::NSB * T::B_BYTES;
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, true>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+                                                                    ti, tj, split, wm, wn, wave, ln);
 #endif
 }
 
@@ -2507,15 +2616,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 4) gemm_fp8s_kerne
   }
 #undef CCL_FP8S_REST
 
-  static_assert((BM / 2) * BN * 2 <= NS * T::A_BYTES && (BM / 2) * BN * 2 <= NS * T::B_BYTES,
-                "each half of the bf16 C tile fits in one operand's stage buffers");
   int ln = lane;
   asm volatile("" : "+v"(ln));
-  if (p.epi == 0 && !p.c_f32 && !p.ws)
-    store_tile_staged<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, true>(
-        p, acc, &smA[0][0], &smB[0][0], pr, pc, ti, tj, wm, wn, wave, ln);
-  else
-    store_tile<BM, BN, 16, T::TM, T::TN, T::WM, T::WN>(p, acc, pr, pc, ti, tj, split, wm, wn, ln);
+  constexpr int kBuf = NS * T::A_BYTES < NS * T::B_BYTES ? NS * T::A_BYTES : NS * T::B_BYTES;
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, true>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+                                                                    ti, tj, split, wm, wn, wave, ln);
 #endif
 }
 
