@@ -13,6 +13,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -21,6 +22,9 @@ namespace ccl {
 namespace {
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // one 16-byte chunk
+// The same at any byte address: gfx950 global memory accesses need no
+// alignment (one dwordx4 instruction either way).
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
 
 constexpr int64_t kInfinityCacheBytes = 256ll << 20;          // MI355X MALL
 // Workgroups of copy_stream_kernel's resident grid: 8 of 256 threads per CU
@@ -58,9 +62,23 @@ struct PackArgs {
   int64_t hr;              // block rows
   int64_t row_bytes;       // bytes of one block row (wc * e)
   int32_t grid_c;
-  uint32_t units_per_block;  // hr * row_bytes / sizeof(U)
-  DivMagic units_per_row;    // row_bytes / sizeof(U)
+  uint32_t units_per_block;  // hr * units_per_row
+  DivMagic units_per_row;    // ceil(row_bytes / unit)
 };
+
+// Byte offsets of unit q of a block on both sides. Units are US bytes of one
+// block row. EXACT: a row is a whole number of them. Otherwise its last unit
+// ends at the row's end and overlaps the one before (the same bytes twice),
+// so no access leaves the row.
+template <int64_t US, bool EXACT>
+__device__ __forceinline__ void unit_offsets(const PackArgs& a, uint32_t q, int64_t* rm, int64_t* ccl) {
+  const uint32_t row = fdiv(q, a.units_per_row);
+  const uint32_t i = q - row * a.units_per_row.d;
+  int64_t col = (int64_t)i * US;
+  if constexpr (!EXACT) col = std::min<int64_t>(col, a.row_bytes - US);
+  *rm = (int64_t)row * a.ld_bytes + col;
+  *ccl = EXACT ? (int64_t)q * US : (int64_t)row * a.row_bytes + col;
+}
 
 // Load / store one unit; NT = non-temporal (streaming) access.
 template <bool NT, typename T>
@@ -74,108 +92,85 @@ __device__ __forceinline__ void st(T* p, T v) {
   else *p = v;
 }
 
-// U = unit moved per access: one 16-byte vector, or one element (1, 2 or 4
-// bytes) when rows are not 16-byte multiples. UNPACK = false: row-major ->
-// CCL; true: CCL -> row-major. NTL / NTS: streaming (non-temporal) loads /
-// stores, used for tensors larger than the 256 MiB Infinity Cache
-// (measured: +10 % on a 470 MB copy, -15 % on a 134 MB one that the cache
-// holds). Below that size, plain stores let the packed operand land in the
-// Infinity Cache: streaming stores made the 134 MB activation pack 12 %
-// slower between the FFN GEMMs.
-template <typename U, bool UNPACK, bool NTL, bool NTS>
+// Tensors above the Infinity Cache size, with streaming (non-temporal) loads
+// and stores (measured: +10 % on a 470 MB copy, -15 % on a 134 MB one that
+// the cache holds). U = unit moved per access, at any byte address: 16 bytes,
+// or one element where rows are shorter than that. UNPACK = false: row-major
+// -> CCL; true: CCL -> row-major.
+template <typename U, bool UNPACK, bool EXACT>
 __global__ void __launch_bounds__(256) copy_kernel(PackArgs a) {
   const int32_t b = blockIdx.y;                      // strip / chiplet
   const int64_t pr = b / a.grid_c, pc = b % a.grid_c;
   const int64_t rm_base = pr * a.hr * a.ld_bytes + pc * a.row_bytes;
-  const char* src_rm = a.rm + rm_base;
-  char* dst_rm = a.rm_out + rm_base;
-  const int64_t strip_base = (int64_t)b * a.strip;
+  const char* src = UNPACK ? a.ccl + (int64_t)b * a.strip : a.rm + rm_base;
+  char* dst = UNPACK ? a.rm_out + rm_base : a.ccl_out + (int64_t)b * a.strip;
   constexpr int UNROLL = 4;
-  constexpr int64_t US = sizeof(U);
   const uint32_t stride = gridDim.x * 256u;
   for (uint32_t base = blockIdx.x * 256u * UNROLL; base < a.units_per_block; base += stride * UNROLL) {
     U v[UNROLL];
-    int64_t rm_off[UNROLL];
+    int64_t to[UNROLL];
     bool ok[UNROLL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       const uint32_t q = base + threadIdx.x + u * 256u;
       ok[u] = q < a.units_per_block;
-      const uint32_t row = fdiv(q, a.units_per_row);
-      const uint32_t col = q - row * a.units_per_row.d;
-      rm_off[u] = (int64_t)row * a.ld_bytes + (int64_t)col * US;
-      if (ok[u]) {
-        if (UNPACK)
-          v[u] = ld<NTL>(reinterpret_cast<const U*>(a.ccl + strip_base + (int64_t)q * US));
-        else
-          v[u] = ld<NTL>(reinterpret_cast<const U*>(src_rm + rm_off[u]));
-      }
+      int64_t rm, ccl;
+      unit_offsets<sizeof(U), EXACT>(a, q, &rm, &ccl);
+      to[u] = UNPACK ? rm : ccl;
+      if (ok[u]) v[u] = ld<true>(reinterpret_cast<const U*>(src + (UNPACK ? ccl : rm)));
     }
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      const uint32_t q = base + threadIdx.x + u * 256u;
-      if (ok[u]) {
-        if (UNPACK)
-          st<NTS>(reinterpret_cast<U*>(dst_rm + rm_off[u]), v[u]);
-        else
-          st<NTS>(reinterpret_cast<U*>(a.ccl_out + strip_base + (int64_t)q * US), v[u]);
-      }
-    }
+    for (int u = 0; u < UNROLL; ++u)
+      if (ok[u]) st<true>(reinterpret_cast<U*>(dst + to[u]), v[u]);
   }
 }
 
-// 16-byte units of tensors below the Infinity Cache size: a resident grid
+// Tensors below the Infinity Cache size: a resident grid
 // (about 8 workgroups per CU) walks each strip with a stride of the whole
 // grid, and issues the loads of its next round before the stores of the
 // current one, so every workgroup keeps a round of loads in flight instead
 // of one load-then-store pass per workgroup. Loads stream (the source is
 // not read again by the path); stores are plain, so the packed operand can
-// stay in the Infinity Cache for the GEMM that reads it next. Measured on
-// the 134 MB pack of X from HBM: 5.39-5.41 TB/s against 5.05-5.14 for
-// copy_kernel; inside the FFN step 46 us against 54 us.
-template <bool UNPACK>
+// stay in the Infinity Cache for the GEMM that reads it next (streaming
+// stores made the 134 MB activation pack 12 % slower between the FFN GEMMs).
+// Measured on the 134 MB pack of X from HBM: 5.39-5.41 TB/s against
+// 5.05-5.14 for copy_kernel; inside the FFN step 46 us against 54 us. U as
+// in copy_kernel.
+template <typename U, bool UNPACK, bool EXACT>
 __global__ void __launch_bounds__(256) copy_stream_kernel(PackArgs a) {
   const int32_t b = blockIdx.y;                      // strip / chiplet
   const int64_t pr = b / a.grid_c, pc = b % a.grid_c;
   const int64_t rm_base = pr * a.hr * a.ld_bytes + pc * a.row_bytes;
-  const char* src_rm = a.rm + rm_base;
-  char* dst_rm = a.rm_out + rm_base;
-  const int64_t strip_base = (int64_t)b * a.strip;
+  const char* src = UNPACK ? a.ccl + (int64_t)b * a.strip : a.rm + rm_base;
+  char* dst = UNPACK ? a.rm_out + rm_base : a.ccl_out + (int64_t)b * a.strip;
   constexpr int UNROLL = 4;
   constexpr uint32_t kRound = 256u * UNROLL;         // units per workgroup round
   const uint32_t stride = gridDim.x * kRound;
-  auto rm_off = [&](uint32_t q) {
-    const uint32_t row = fdiv(q, a.units_per_row);
-    const uint32_t col = q - row * a.units_per_row.d;
-    return (int64_t)row * a.ld_bytes + (int64_t)col * 16;
-  };
-  auto load = [&](uint32_t base, u32x4* v) {
+  auto load = [&](uint32_t base, U* v) {
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       const uint32_t q = base + threadIdx.x + u * 256u;
       if (q < a.units_per_block) {
-        if (UNPACK)
-          v[u] = ld<true>(reinterpret_cast<const u32x4*>(a.ccl + strip_base + (int64_t)q * 16));
-        else
-          v[u] = ld<true>(reinterpret_cast<const u32x4*>(src_rm + rm_off(q)));
+        int64_t rm, ccl;
+        unit_offsets<sizeof(U), EXACT>(a, q, &rm, &ccl);
+        v[u] = ld<true>(reinterpret_cast<const U*>(src + (UNPACK ? ccl : rm)));
       }
     }
   };
-  auto store = [&](uint32_t base, const u32x4* v) {
+  auto store = [&](uint32_t base, const U* v) {
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       const uint32_t q = base + threadIdx.x + u * 256u;
       if (q < a.units_per_block) {
-        if (UNPACK)
-          *reinterpret_cast<u32x4*>(dst_rm + rm_off(q)) = v[u];
-        else
-          *reinterpret_cast<u32x4*>(a.ccl_out + strip_base + (int64_t)q * 16) = v[u];
+        int64_t rm, ccl;
+        unit_offsets<sizeof(U), EXACT>(a, q, &rm, &ccl);
+        *reinterpret_cast<U*>(dst + (UNPACK ? rm : ccl)) = v[u];
       }
     }
   };
   uint32_t base = blockIdx.x * kRound;
   if (base >= a.units_per_block) return;
-  u32x4 cur[UNROLL], nxt[UNROLL];
+  U cur[UNROLL], nxt[UNROLL];
   load(base, cur);
   for (; base < a.units_per_block; base += stride) {
     const uint32_t next = base + stride;
@@ -186,13 +181,8 @@ __global__ void __launch_bounds__(256) copy_stream_kernel(PackArgs a) {
   }
 }
 
-// Stored-transpose pack through LDS, for blocks whose sides are multiples of
-// 64 but not of the register kernel's block edge below (fp8 blocks with a
-// side of 64 mod 128): src holds X^T (cols x rows, leading dimension ld
-// elements), X is rows x cols of element type E. A 64 x 64 tile is read
-// along X's rows (contiguous in src) in 16-byte chunks, transposed through
-// LDS and written in 16-byte chunks along X's columns (contiguous in the
-// CCL strip). Tiles never straddle blocks (hr, wc multiples of 64).
+// Stored-transpose packs: src holds X^T (cols x rows, leading dimension ld
+// elements), X is rows x cols of element type E.
 struct TransArgs {
   const char* src;
   char* dst;
@@ -200,43 +190,9 @@ struct TransArgs {
   int64_t strip;           // bytes
   int64_t hr, wc;          // elements
   int32_t grid_c;
+  int32_t rows, cols;
+  DivMagic div_hr, div_wc;
 };
-
-template <typename E>
-__global__ void __launch_bounds__(256) pack_trans_kernel(TransArgs a) {
-  constexpr int EPC = 16 / sizeof(E);                  // elements per 16-byte chunk
-  constexpr int CPR = 64 / EPC;                        // chunks per 64-element row
-  constexpr int ITER = 64 * CPR / 256;                 // chunks per thread
-  __shared__ E tile[64][64 + 16 / sizeof(E)];
-  const int64_t r0 = (int64_t)blockIdx.y * 64;        // X rows = src columns
-  const int64_t c0 = (int64_t)blockIdx.x * 64;        // X cols = src rows
-  const int t = threadIdx.x;
-  const E* src = reinterpret_cast<const E*>(a.src);
-#pragma unroll
-  for (int i = 0; i < ITER; ++i) {
-    const int idx = t + i * 256;
-    const int sr = idx / CPR, ch = idx % CPR;
-    uint4 v = *reinterpret_cast<const uint4*>(src + (c0 + sr) * a.ld + r0 + ch * EPC);
-    const E* e = reinterpret_cast<const E*>(&v);
-#pragma unroll
-    for (int j = 0; j < EPC; ++j) tile[sr][ch * EPC + j] = e[j];
-  }
-  __syncthreads();
-  const int64_t pr = r0 / a.hr, pc = c0 / a.wc;
-  const int64_t b = pr * a.grid_c + pc;
-  E* strip = reinterpret_cast<E*>(a.dst + b * a.strip);
-  const int64_t rl0 = r0 - pr * a.hr, cl0 = c0 - pc * a.wc;
-#pragma unroll
-  for (int i = 0; i < ITER; ++i) {
-    const int idx = t + i * 256;
-    const int xr = idx / CPR, ch = idx % CPR;
-    uint4 v;
-    E* e = reinterpret_cast<E*>(&v);
-#pragma unroll
-    for (int j = 0; j < EPC; ++j) e[j] = tile[ch * EPC + j][xr];
-    *reinterpret_cast<uint4*>(strip + (rl0 + xr) * a.wc + cl0 + ch * EPC) = v;
-  }
-}
 
 // Stored-transpose pack without LDS. With EPC elements per 16-byte chunk,
 // each thread moves an EPC x EPC block: it reads EPC chunks, one from each
@@ -246,11 +202,17 @@ __global__ void __launch_bounds__(256) pack_trans_kernel(TransArgs a) {
 // R0 + EPC a .. + EPC - 1 and X columns C0 + EPC b .. + EPC - 1, so a wave
 // covers a WB x WB block (WB = 8 EPC) and each of its loads and stores
 // touches 8 rows x 128 contiguous bytes. The 4 waves of a workgroup take 4
-// consecutive blocks along X's columns. Blocks never straddle CCL blocks
-// (hr and wc are multiples of WB). NTL: streaming loads (sources beyond the
-// Infinity Cache). The stores always stream: on a 134 MB transpose that
-// measured +12 % from HBM and no loss with the source cache-resident.
-template <typename E, bool NTL>
+// consecutive blocks along X's columns. Loads stream: the stored tensor is
+// read once (134 MB from HBM: 5.05 against 4.92 TB/s). Streaming stores
+// measured +12 % on a 134 MB transpose from HBM and no loss with the source
+// cache-resident.
+// RAGGED = false: hr and wc are multiples of WB, so a wave's block never
+// straddles CCL blocks, and src and dst are 16-byte aligned. RAGGED = true:
+// hr and wc are multiples of EPC only, so each thread's own EPC x EPC block
+// lies within one CCL block, which it finds for itself; any alignment. Against
+// one element per thread: 1152x3328 bf16 in 416-column blocks 19.4 -> 5.0 us
+// (odd leading dimension 20.7 -> 6.4), 4096x2112 fp8 37.0 -> 7.4.
+template <typename E, bool RAGGED>
 __global__ void __launch_bounds__(256) pack_trans_reg_kernel(TransArgs a, int32_t wb_cols) {
   constexpr int EPC = 16 / (int)sizeof(E);
   constexpr int WB = 8 * EPC;
@@ -269,12 +231,16 @@ __global__ void __launch_bounds__(256) pack_trans_reg_kernel(TransArgs a, int32_
   if (wcb >= wb_cols) return;
   const int la = lane & 7, lb = lane >> 3;
   const int64_t R0 = (int64_t)by * WB, C0 = (int64_t)wcb * WB;
+  typedef std::conditional_t<RAGGED, u32x4_any, u32x4> chunk;
+  if constexpr (RAGGED)
+    if (R0 + EPC * la >= a.rows || C0 + EPC * lb >= a.cols) return;
   const E* src = reinterpret_cast<const E*>(a.src) + (C0 + EPC * lb) * a.ld + R0 + EPC * la;
   ev in[EPC];
 #pragma unroll
   for (int j = 0; j < EPC; ++j)
-    in[j] = __builtin_bit_cast(ev, ld<NTL>(reinterpret_cast<const u32x4*>(src + j * a.ld)));
-  const int32_t pr = (int32_t)(R0 / a.hr), pc = (int32_t)(C0 / a.wc);
+    in[j] = __builtin_bit_cast(ev, (u32x4)ld<true>(reinterpret_cast<const chunk*>(src + j * a.ld)));
+  const uint32_t r = (uint32_t)R0 + (RAGGED ? EPC * la : 0), c = (uint32_t)C0 + (RAGGED ? EPC * lb : 0);
+  const uint32_t pr = fdiv(r, a.div_hr), pc = fdiv(c, a.div_wc);
   E* strip = reinterpret_cast<E*>(a.dst + ((int64_t)pr * a.grid_c + pc) * a.strip);
   E* dst = strip + (R0 - pr * a.hr + EPC * la) * a.wc + (C0 - pc * a.wc) + EPC * lb;
 #pragma unroll
@@ -282,22 +248,44 @@ __global__ void __launch_bounds__(256) pack_trans_reg_kernel(TransArgs a, int32_
     ev o;
 #pragma unroll
     for (int j = 0; j < EPC; ++j) o[j] = in[j][i];
-    st<true>(reinterpret_cast<u32x4*>(dst + i * a.wc), __builtin_bit_cast(u32x4, o));
+    st<true>(reinterpret_cast<chunk*>(dst + i * a.wc), (chunk)__builtin_bit_cast(u32x4, o));
   }
 }
 
-// Any shape: one element per thread, src holds X^T.
+// Any shape: a 64 x 64 tile through LDS, element by element, so that both
+// the reads (along X's rows, contiguous in src) and the writes (along X's
+// columns, contiguous in a block) of a wave cover whole lines: 8192x8200 bf16
+// in 1025-column blocks 355 -> 116 us against one element per thread.
 template <typename E>
-__global__ void __launch_bounds__(256) pack_trans_scalar_kernel(TransArgs a, int64_t rows,
-                                                                int64_t cols) {
-  const int64_t n = rows * cols;
-  const E* src = reinterpret_cast<const E*>(a.src);
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const int64_t r = i / cols, c = i % cols;          // write order: along X rows
-    const int64_t pr = r / a.hr, pc = c / a.wc;
-    const int64_t b = pr * a.grid_c + pc;
-    E* strip = reinterpret_cast<E*>(a.dst + b * a.strip);
-    strip[(r - pr * a.hr) * a.wc + (c - pc * a.wc)] = src[c * a.ld + r];
+__global__ void __launch_bounds__(256) pack_trans_any_kernel(TransArgs a, uint32_t row_tiles,
+                                                             uint32_t tiles) {
+  typedef E any_e __attribute__((aligned(1)));
+  __shared__ E tile[64][64 + 4 / sizeof(E)];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const uint32_t tc = t / row_tiles, tr = t - tc * row_tiles;
+    const int64_t r0 = (int64_t)tr * 64, c0 = (int64_t)tc * 64;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int c = i * 4 + wave;
+      if (r0 + lane < a.rows && c0 + c < a.cols)
+        tile[c][lane] = *reinterpret_cast<const any_e*>(a.src + ((c0 + c) * a.ld + r0 + lane) * (int64_t)sizeof(E));
+    }
+    __syncthreads();
+    const int64_t col = c0 + lane;
+    if (col < a.cols) {
+      const uint32_t pc = fdiv((uint32_t)col, a.div_wc);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int64_t row = r0 + i * 4 + wave;
+        if (row >= a.rows) continue;
+        const uint32_t pr = fdiv((uint32_t)row, a.div_hr);
+        char* strip = a.dst + ((int64_t)pr * a.grid_c + pc) * a.strip;
+        *reinterpret_cast<any_e*>(strip + ((row - pr * a.hr) * a.wc + col - pc * a.wc) * (int64_t)sizeof(E)) =
+            tile[lane][i * 4 + wave];
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -309,34 +297,56 @@ int grid_x_for(uint32_t units, int unroll) {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-template <typename U>
-void copy_launch(dim3 grid, const PackArgs& a, bool unpack, hipStream_t stream) {
-  if (unpack)
-    hipLaunchKernelGGL((copy_kernel<U, true, false, false>), grid, dim3(256), 0, stream, a);
+typedef uint8_t u8_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+
+template <typename U, bool UNPACK>
+void copy_launch_as(dim3 grid, const PackArgs& a, bool big, bool exact, hipStream_t stream) {
+  if (big && exact)
+    hipLaunchKernelGGL((copy_kernel<U, UNPACK, true>), grid, dim3(256), 0, stream, a);
+  else if (big)
+    hipLaunchKernelGGL((copy_kernel<U, UNPACK, false>), grid, dim3(256), 0, stream, a);
+  else if (exact)
+    hipLaunchKernelGGL((copy_stream_kernel<U, UNPACK, true>), grid, dim3(256), 0, stream, a);
   else
-    hipLaunchKernelGGL((copy_kernel<U, false, false, false>), grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((copy_stream_kernel<U, UNPACK, false>), grid, dim3(256), 0, stream, a);
 }
 
-// path 2: register blocks, 1: LDS tiles, 0: one element per thread.
+// Units of type U: fills in the unit counts and picks the kernel by size.
+template <typename U>
+void copy_launch(const Layout& L, PackArgs a, bool unpack, hipStream_t stream) {
+  const int64_t per_row = (a.row_bytes + (int64_t)sizeof(U) - 1) / (int64_t)sizeof(U);
+  const bool exact = per_row * (int64_t)sizeof(U) == a.row_bytes;
+  a.units_per_block = (uint32_t)(L.block_rows * per_row);
+  a.units_per_row = make_div((uint32_t)per_row);
+  const unsigned strips = (unsigned)(L.grid_r * L.grid_c);
+  dim3 grid(grid_x_for(a.units_per_block, 4), strips);
+  // above the cache size both sides stream (measured: +10 % on 470 MB);
+  // below it a resident grid: kResidentWgs workgroups in all, at most one
+  // round each per strip
+  const bool big = L.rows * L.cols * L.elem_bytes > kInfinityCacheBytes;
+  if (!big) grid.x = std::min(std::max(1u, kResidentWgs / strips), grid.x);
+  if (unpack) copy_launch_as<U, true>(grid, a, big, exact, stream);
+  else copy_launch_as<U, false>(grid, a, big, exact, stream);
+}
+
+// aligned: src, ld, dst and strips are multiples of 16 bytes.
 template <typename E>
-void trans_launch(const Layout& L, const TransArgs& a, int path, bool ntl, hipStream_t stream) {
-  if (path == 2) {
-    constexpr int WB = 8 * 16 / (int)sizeof(E);
-    const int32_t wb_cols = (int32_t)(L.cols / WB);
-    dim3 grid((unsigned)((wb_cols + 3) / 4), (unsigned)(L.rows / WB));
-    if (ntl)
-      hipLaunchKernelGGL((pack_trans_reg_kernel<E, true>), grid, dim3(256), 0, stream, a, wb_cols);
-    else
-      hipLaunchKernelGGL((pack_trans_reg_kernel<E, false>), grid, dim3(256), 0, stream, a, wb_cols);
-  } else if (path == 1) {
-    dim3 grid((unsigned)(L.cols / 64), (unsigned)(L.rows / 64));
-    hipLaunchKernelGGL((pack_trans_kernel<E>), grid, dim3(256), 0, stream, a);
+void trans_launch(const Layout& L, const TransArgs& a, bool aligned, hipStream_t stream) {
+  constexpr int EPC = 16 / (int)sizeof(E);
+  constexpr int WB = 8 * EPC;         // block edge of a wave of the register kernel
+  const int32_t wb_cols = (int32_t)((L.cols + WB - 1) / WB);
+  const int64_t wb_rows = (L.rows + WB - 1) / WB;
+  dim3 grid((unsigned)((wb_cols + 3) / 4), (unsigned)wb_rows);
+  if (aligned && L.block_rows % WB == 0 && L.block_cols % WB == 0 && wb_rows <= 65535) {
+    hipLaunchKernelGGL((pack_trans_reg_kernel<E, false>), grid, dim3(256), 0, stream, a, wb_cols);
+  } else if (L.block_rows % EPC == 0 && L.block_cols % EPC == 0 && wb_rows <= 65535) {
+    hipLaunchKernelGGL((pack_trans_reg_kernel<E, true>), grid, dim3(256), 0, stream, a, wb_cols);
   } else {
-    int64_t n = L.rows * L.cols;
-    int64_t wgs = (n + 255) / 256;
-    if (wgs > 8192) wgs = 8192;
-    hipLaunchKernelGGL((pack_trans_scalar_kernel<E>), dim3((unsigned)wgs), dim3(256), 0, stream, a,
-                       L.rows, L.cols);
+    const int64_t row_tiles = (L.rows + 63) / 64, tiles = row_tiles * ((L.cols + 63) / 64);
+    hipLaunchKernelGGL((pack_trans_any_kernel<E>), dim3((unsigned)std::min<int64_t>(tiles, 1 << 20)),
+                       dim3(256), 0, stream, a, (uint32_t)row_tiles, (uint32_t)tiles);
   }
 }
 
@@ -346,10 +356,6 @@ hipError_t launch_copy(const Plan& p, int op, const void* rowmajor, int64_t ld, 
                        bool unpack, hipStream_t stream) {
   const Layout& L = p.lay[op];
   const int64_t e = L.elem_bytes;
-  const int64_t row_bytes = L.block_cols * e;
-  const bool vec = (row_bytes % 16 == 0) && ((ld * e) % 16 == 0) && aligned16(rowmajor) &&
-                   aligned16(ccl_buf) && (L.strip_stride_bytes % 16 == 0);
-  const int64_t unit = vec ? 16 : e;
   PackArgs a;
   a.rm = static_cast<const char*>(rowmajor);
   a.rm_out = const_cast<char*>(static_cast<const char*>(rowmajor));
@@ -358,36 +364,20 @@ hipError_t launch_copy(const Plan& p, int op, const void* rowmajor, int64_t ld, 
   a.ld_bytes = ld * e;
   a.strip = L.strip_stride_bytes;
   a.hr = L.block_rows;
-  a.row_bytes = row_bytes;
+  a.row_bytes = L.block_cols * e;
   a.grid_c = (int32_t)L.grid_c;
-  a.units_per_block = (uint32_t)(L.block_rows * row_bytes / unit);
-  a.units_per_row = make_div((uint32_t)(row_bytes / unit));
-  const unsigned strips = (unsigned)(L.grid_r * L.grid_c);
-  dim3 grid(grid_x_for(a.units_per_block, 4), strips);
-  if (vec) {
-    const bool big = L.rows * L.cols * e > kInfinityCacheBytes;
-    if (big) {
-      // above the cache size both sides stream (measured: +10 % on 470 MB)
-      if (unpack)
-        hipLaunchKernelGGL((copy_kernel<u32x4, true, true, true>), grid, dim3(256), 0, stream, a);
-      else
-        hipLaunchKernelGGL((copy_kernel<u32x4, false, true, true>), grid, dim3(256), 0, stream, a);
-    } else {
-      // resident grid: kResidentWgs workgroups in all, at most one round each per strip
-      const unsigned per_strip = std::max(1u, kResidentWgs / strips);
-      const dim3 g((unsigned)std::min<int64_t>(per_strip, grid.x), strips);
-      if (unpack)
-        hipLaunchKernelGGL((copy_stream_kernel<true>), g, dim3(256), 0, stream, a);
-      else
-        hipLaunchKernelGGL((copy_stream_kernel<false>), g, dim3(256), 0, stream, a);
-    }
-  } else if (e == 1) {
-    copy_launch<uint8_t>(grid, a, unpack, stream);
-  } else if (e == 2) {
-    copy_launch<uint16_t>(grid, a, unpack, stream);
-  } else {
-    copy_launch<uint32_t>(grid, a, unpack, stream);
-  }
+  // 16-byte units wherever a block row holds one, whatever the alignment.
+  // Against one element per access: 8192x8192 bf16 with an odd leading
+  // dimension 104 -> 50 us, in rows of 1025 elements 108 -> 60 us (unpack 109
+  // -> 63), 4096x2048 12.8 -> 7.6 us.
+  if (a.row_bytes >= 16)
+    copy_launch<u32x4_any>(L, a, unpack, stream);
+  else if (e == 1)
+    copy_launch<u8_any>(L, a, unpack, stream);
+  else if (e == 2)
+    copy_launch<u16_any>(L, a, unpack, stream);
+  else
+    copy_launch<u32_any>(L, a, unpack, stream);
   return hipGetLastError();
 }
 
@@ -403,23 +393,18 @@ hipError_t launch_pack_trans(const Plan& p, int op, const void* src, int64_t ld,
   a.hr = L.block_rows;
   a.wc = L.block_cols;
   a.grid_c = (int32_t)L.grid_c;
-  const bool vec = (ld * e) % 16 == 0 && aligned16(src) && aligned16(dst) &&
-                   L.strip_stride_bytes % 16 == 0;
-  const int64_t wb = 8 * 16 / e;      // block edge of the register-transpose kernel
-  int path = 0;
-  if (vec && L.block_rows % wb == 0 && L.block_cols % wb == 0 && L.rows / wb <= 65535)
-    path = 2;
-  else if (vec && L.block_rows % 64 == 0 && L.block_cols % 64 == 0 && L.rows / 64 <= 65535)
-    path = 1;
-  // Loads stream at every size: the stored tensor is read once (measured on
-  // the 134 MB X^T from HBM: 5.05 against 4.92 TB/s).
-  const bool ntl = true;
+  a.rows = (int32_t)L.rows;
+  a.cols = (int32_t)L.cols;
+  a.div_hr = make_div((uint32_t)L.block_rows);
+  a.div_wc = make_div((uint32_t)L.block_cols);
+  const bool aligned = (ld * e) % 16 == 0 && aligned16(src) && aligned16(dst) &&
+                       L.strip_stride_bytes % 16 == 0;
   if (e == 1)
-    trans_launch<uint8_t>(L, a, path, ntl, stream);
+    trans_launch<uint8_t>(L, a, aligned, stream);
   else if (e == 2)
-    trans_launch<uint16_t>(L, a, path, ntl, stream);
+    trans_launch<uint16_t>(L, a, aligned, stream);
   else
-    trans_launch<uint32_t>(L, a, path, ntl, stream);
+    trans_launch<uint32_t>(L, a, aligned, stream);
   return hipGetLastError();
 }
 
