@@ -203,16 +203,20 @@ struct TransArgs {
 // covers a WB x WB block (WB = 8 EPC) and each of its loads and stores
 // touches 8 rows x 128 contiguous bytes. The 4 waves of a workgroup take 4
 // consecutive blocks along X's columns. Loads stream: the stored tensor is
-// read once (134 MB from HBM: 5.05 against 4.92 TB/s). Streaming stores
-// measured +12 % on a 134 MB transpose from HBM and no loss with the source
-// cache-resident.
+// read once (134 MB from HBM: 5.05 against 4.92 TB/s). NTS: streaming stores,
+// for operands above the Infinity Cache size (470 MB W_up^T: 162 against
+// 177 us with plain ones). Below it they are plain, so the GEMM that follows
+// finds the operand in the cache: alone, the 134 MB transpose is 12 % faster
+// with streaming stores, but the whole weight-gradient pass is not (2943
+// against 2938 us), and at 6 MB the GEMM behind the pack took 41 us instead
+// of 29 (pass 55.3 against 42.9 us; 768x2048x4096: 43.6 against 37.4).
 // RAGGED = false: hr and wc are multiples of WB, so a wave's block never
 // straddles CCL blocks, and src and dst are 16-byte aligned. RAGGED = true:
 // hr and wc are multiples of EPC only, so each thread's own EPC x EPC block
 // lies within one CCL block, which it finds for itself; any alignment. Against
 // one element per thread: 1152x3328 bf16 in 416-column blocks 19.4 -> 5.0 us
 // (odd leading dimension 20.7 -> 6.4), 4096x2112 fp8 37.0 -> 7.4.
-template <typename E, bool RAGGED>
+template <typename E, bool RAGGED, bool NTS>
 __global__ void __launch_bounds__(256) pack_trans_reg_kernel(TransArgs a, int32_t wb_cols) {
   constexpr int EPC = 16 / (int)sizeof(E);
   constexpr int WB = 8 * EPC;
@@ -248,7 +252,7 @@ __global__ void __launch_bounds__(256) pack_trans_reg_kernel(TransArgs a, int32_
     ev o;
 #pragma unroll
     for (int j = 0; j < EPC; ++j) o[j] = in[j][i];
-    st<true>(reinterpret_cast<chunk*>(dst + i * a.wc), (chunk)__builtin_bit_cast(u32x4, o));
+    st<NTS>(reinterpret_cast<chunk*>(dst + i * a.wc), (chunk)__builtin_bit_cast(u32x4, o));
   }
 }
 
@@ -338,11 +342,14 @@ void trans_launch(const Layout& L, const TransArgs& a, bool aligned, hipStream_t
   constexpr int WB = 8 * EPC;         // block edge of a wave of the register kernel
   const int32_t wb_cols = (int32_t)((L.cols + WB - 1) / WB);
   const int64_t wb_rows = (L.rows + WB - 1) / WB;
+  const bool big = L.rows * L.cols * L.elem_bytes > kInfinityCacheBytes;
   dim3 grid((unsigned)((wb_cols + 3) / 4), (unsigned)wb_rows);
   if (aligned && L.block_rows % WB == 0 && L.block_cols % WB == 0 && wb_rows <= 65535) {
-    hipLaunchKernelGGL((pack_trans_reg_kernel<E, false>), grid, dim3(256), 0, stream, a, wb_cols);
+    if (big) hipLaunchKernelGGL((pack_trans_reg_kernel<E, false, true>), grid, dim3(256), 0, stream, a, wb_cols);
+    else hipLaunchKernelGGL((pack_trans_reg_kernel<E, false, false>), grid, dim3(256), 0, stream, a, wb_cols);
   } else if (L.block_rows % EPC == 0 && L.block_cols % EPC == 0 && wb_rows <= 65535) {
-    hipLaunchKernelGGL((pack_trans_reg_kernel<E, true>), grid, dim3(256), 0, stream, a, wb_cols);
+    if (big) hipLaunchKernelGGL((pack_trans_reg_kernel<E, true, true>), grid, dim3(256), 0, stream, a, wb_cols);
+    else hipLaunchKernelGGL((pack_trans_reg_kernel<E, true, false>), grid, dim3(256), 0, stream, a, wb_cols);
   } else {
     const int64_t row_tiles = (L.rows + 63) / 64, tiles = row_tiles * ((L.cols + 63) / 64);
     hipLaunchKernelGGL((pack_trans_any_kernel<E>), dim3((unsigned)std::min<int64_t>(tiles, 1 << 20)),
