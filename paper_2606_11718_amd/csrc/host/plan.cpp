@@ -153,11 +153,10 @@ void choose_gemm_config(Plan* p) {
   // B/clk when most CUs load, against 57-64 B/clk for whole lines
   // (direct-to-LDS loads of L2-resident data). The tiles below 256x256 need
   // 48-64 B/clk per CU at the matrix cores' rate, so they take 64-K stages
-  // (whole-line A rows), where both K blocks allow it. 256x256 keeps 32:
-  // two 64-K stages would leave one step of load lookahead.
+  // (whole-line A rows). 256x256 keeps 32: two 64-K stages would leave one
+  // step of load lookahead.
   // CCL_GEMM_STAGE_K=32 selects the 32-K stages everywhere.
-  g.stage_k = (p->ab_type == DT_BF16 && g.waves == 8 && !(btm == 256 && btn == 256) &&
-               (p->K / p->Gc) % 64 == 0 && (p->K / p->Gr) % 64 == 0) ? 64 : 32;
+  g.stage_k = (p->ab_type == DT_BF16 && g.waves == 8 && !(btm == 256 && btn == 256)) ? 64 : 32;
   if (const char* e = std::getenv("CCL_GEMM_STAGE_K"))
     if (std::atoi(e) == 32) g.stage_k = 32;
   // 256x256 keeps 32-K steps for B and the MFMA schedule but stages A in

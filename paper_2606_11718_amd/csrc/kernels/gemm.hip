@@ -923,6 +923,12 @@ __global__ void __launch_bounds__(128 * WGN, WGN / 2) gemm_kernel(GemmParams p) 
 // (checked against the measured ds_read_b128 grouping: lanes with equal
 // parity of lane bits 2..4 are served together). B rows are as in the 32-K
 // kernel, twice as many per stage.
+// RAGGED: K blocks and K ranges that are odd multiples of 32. A stage is two
+// 32-K steps that may lie in different K blocks: the loads of its second 32 K
+// (half of the lanes for A, whole load instructions for B) get the jump to
+// the next block added to their offsets, and a last half stage is filled
+// with zeros. The MFMAs and their order are the 32-K kernel's (C is identical
+// bit for bit).
 // ---------------------------------------------------------------------------
 
 constexpr int kBK64 = 64;        // K extent of one stage of gemm_k64_kernel
@@ -953,7 +959,7 @@ struct Tile64 {
   static_assert(BN == 128 || BN == 256, "B swizzle is defined for 16- and 32-chunk rows");
 };
 
-template <int BM, int BN>
+template <int BM, int BN, bool RAGGED>
 __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using T = Tile64<BM, BN>;
@@ -969,9 +975,12 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   }
   int32_t pr, pc, ti, tj, split;
   if (!tile_of_block(p, &pr, &pc, &ti, &tj, &split)) return;
-  // K range of this workgroup: steps [k0, k0 + ksteps) (all of K without split-K)
+  // K range of this workgroup: from k0 steps (of kUnit K) on, all of K
+  // without split-K; units: its length in steps, ksteps: in stages of 64 K.
+  constexpr int kUnit = RAGGED ? kBK : kBK64;
   const int32_t k0 = __builtin_amdgcn_readfirstlane(split * p.ksteps_per_split);
-  const int32_t ksteps = __builtin_amdgcn_readfirstlane(min(p.ksteps, k0 + p.ksteps_per_split) - k0);
+  const int32_t units = __builtin_amdgcn_readfirstlane(min(p.ksteps, k0 + p.ksteps_per_split) - k0);
+  const int32_t ksteps = RAGGED ? (units + 1) / 2 : units;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -981,12 +990,13 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   // ---- global -> LDS: per-lane byte offsets from the K step's tile corner ----
   // A load i of this wave fills LDS rows 8*(wave*NA+i) .. +7 (128 B each);
   // the lane at LDS chunk q of its row fetches global chunk q ^ swz_a64(row).
-  uint32_t a_voff[T::NA];
+  uint32_t a_voff[T::NA], a_hi[T::NA];
 #pragma unroll
   for (int i = 0; i < T::NA; ++i) {
     const int row = 8 * (wave * T::NA + i) + (lane >> 3);
     const int chunk = (lane & 7) ^ swz_a64(row);
     a_voff[i] = (uint32_t)(row * p.a.ld + chunk * 8) * 2u;
+    a_hi[i] = chunk >= 4 ? 0xffffffffu : 0u;      // lanes of the stage's second 32 K
   }
   uint32_t b_voff[T::NB];
 #pragma unroll
@@ -1029,18 +1039,42 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   const uint16_t* b_base = p.B + pc * p.b.part + tj * BN;
   int64_t a_slice_off, b_slice_off;
   int32_t a_kl, b_kl;
-  k_start(p.a, k0 * kBK64, &a_slice_off, &a_kl);
-  k_start(p.b, k0 * kBK64, &b_slice_off, &b_kl);
+  k_start(p.a, k0 * kUnit, &a_slice_off, &a_kl);
+  k_start(p.b, k0 * kUnit, &b_slice_off, &b_kl);
   const char* a_next = reinterpret_cast<const char*>(a_base + a_slice_off + a_kl);
   const char* b_next = reinterpret_cast<const char*>(b_base + b_slice_off + (int64_t)b_kl * p.b.ld);
-  const int32_t a_steps = p.a.kslice / kBK64, b_steps = p.b.kslice / kBK64;
-  int32_t a_left = a_steps - a_kl / kBK64, b_left = b_steps - b_kl / kBK64;
+  const int32_t a_steps = p.a.kslice / kUnit, b_steps = p.b.kslice / kUnit;
+  int32_t a_left = a_steps - a_kl / kUnit, b_left = b_steps - b_kl / kUnit;
   const int64_t a_adv = kBK64 * 2, b_adv = (int64_t)kBK64 * p.b.ld * 2;
   const int64_t a_jump = (p.a.slice - p.a.kslice) * 2;
   const int64_t b_jump = (p.b.slice - (int64_t)p.b.kslice * p.b.ld) * 2;
 
+  // RAGGED: da / db are added to the byte offsets of the stage's second 32 K
+  // (the jump to the next K block where the first 32 K end one; past the
+  // range's end da leaves every descriptor and rb_hi is empty, so those loads
+  // return zeros).
   struct StageSrc {
-    i32x4 ra, rb;
+    i32x4 ra, rb, rb_hi;
+    uint32_t da, db;
+  };
+  auto next_ragged = [&](int32_t s) {
+    StageSrc d;
+    const bool live0 = 2 * s < units, live1 = 2 * s + 1 < units;
+    const bool a_mid = a_left == 1, b_mid = b_left == 1;      // the first 32 K end a block
+    d.da = live1 ? (uint32_t)(a_mid ? a_jump : 0) : 0x7ffffff0u;
+    d.db = (uint32_t)(b_mid ? b_jump : 0);
+    d.ra = buffer_rsrc(a_next, live0 ? a_extent + (int32_t)(a_mid ? a_jump : 0) : 0);
+    d.rb = buffer_rsrc(b_next, live0 ? b_extent + (int32_t)d.db : 0);
+    d.rb_hi = d.rb;
+    if (!live1) d.rb_hi[2] = 0;
+    a_left = a_mid ? a_steps : a_left - 1;
+    b_left = b_mid ? b_steps : b_left - 1;
+    const bool a_end = a_left == 1, b_end = b_left == 1;
+    a_next += a_adv + (a_mid ? a_jump : 0) + (a_end ? a_jump : 0);
+    b_next += b_adv + (b_mid ? b_jump : 0) + (b_end ? b_jump : 0);
+    a_left = a_end ? a_steps : a_left - 1;
+    b_left = b_end ? b_steps : b_left - 1;
+    return d;
   };
   auto next_src = [&](bool live) {
     StageSrc d;
@@ -1071,7 +1105,15 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
     return d;
   };
   auto load_one = [&](const StageSrc& d, int j, char* sA, char* sB, int i) {
-    if (i < T::NA) {
+    if constexpr (RAGGED) {
+      if (i < T::NA) {
+        lds_dma16(d.ra, a_voff[i] + (a_hi[i] & d.da), sA + (wave * T::NA + i) * 1024);
+      } else {
+        const int l = wave * T::NB + (i - T::NA);               // rows RPI_B l .. + RPI_B - 1
+        const bool hi = l * T::RPI_B >= 32;
+        lds_dma16_so(hi ? d.rb_hi : d.rb, b_voff[i - T::NA], hi ? d.db : 0u, sB + l * 1024);
+      }
+    } else if (i < T::NA) {
       char* dst = sA + (wave * T::NA + i) * 1024;
       if (j < 0) lds_dma16(d.ra, a_voff[i], dst);
       else lds_dma16_so(d.ra, a_voff[i], so_a[j], dst);
@@ -1081,8 +1123,9 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
       else lds_dma16_so(d.rb, b_voff[i - T::NA], so_b[j], dst);
     }
   };
-  auto load_stage = [&](char* sA, char* sB, bool live) {
-    const StageSrc d = next_src(live);
+  auto stage_src = [&](int32_t s) { return RAGGED ? next_ragged(s) : next_src(s < ksteps); };
+  auto load_stage = [&](char* sA, char* sB, int32_t s) {
+    const StageSrc d = stage_src(s);
 #pragma unroll
     for (int i = 0; i < T::NL; ++i) load_one(d, -1, sA, sB, i);
   };
@@ -1156,7 +1199,7 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
 
   // Prologue: the first NS-1 stages in flight, then stage 0's sub-step 0.
 #pragma unroll
-  for (int j = 0; j < NS - 1; ++j) load_stage(smA[j], smB[j], j < ksteps);
+  for (int j = 0; j < NS - 1; ++j) load_stage(smA[j], smB[j], j);
   stage_barrier();
   if (tl_on) tl_rt[1] = __builtin_amdgcn_s_memrealtime();
 #pragma unroll
@@ -1170,11 +1213,11 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
          smA[(ph + 1) % NS], smB[(ph + 1) % NS], d, j);
   };
   auto single_step = [&](int ph, int32_t s) {
-    const StageSrc d = next_src(s + NS - 1 < ksteps);
+    const StageSrc d = stage_src(s + NS - 1);
     phase_step(ph, d, -1);
   };
   int32_t s = 0;
-  if (p.round_fast) {
+  if (!RAGGED && p.round_fast) {
     // Rounds of 4 steps whose loads (steps s+NS-1 .. s+NS+2) form a
     // 4-aligned group, all live, sharing one pair of descriptors. The first
     // kFirst steps run alone so that the first round's loads start
@@ -2816,28 +2859,45 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
 #undef CCL_LAUNCH8
     return splits > 1 ? launch_splitk_reduce(p, gp, 32, waves8, stream) : hipGetLastError();
   }
-  // 64-K stages (plan's choice for the bf16 tiles below 256x256): both K
-  // blocks a multiple of 64, the 4-step rounds' extents (255 rows of A or
-  // B) within 32-bit offsets, and with split-K only where the K ranges are
-  // the 32-K ranges (each range an even number of 32-K steps), so the
-  // workspace and the reduce are unchanged.
+  // 64-K stages (plan's choice for the bf16 tiles below 256x256), with the
+  // extents of the 4-step rounds (255 rows of A or B) or of a stage across
+  // two K blocks within 32-bit offsets. Where both K blocks are multiples of
+  // 64 and split-K cuts K at whole stages, the rounds form runs; otherwise the
+  // ragged one, whose K ranges are the 32-K ranges, so that the workspace and
+  // the reduce do not depend on the kernel.
   {
     const int64_t lim = ((int64_t)1 << 31) - 4096;
     const int32_t ks64 = (int32_t)(p.K / kBK64);
     const int32_t per64 = (ks64 + splits - 1) / splits;
-    const bool k64 = g.stage_k == 64 && !fp8 && waves == 8 &&
-                     !(g.tile_m == 256 && g.tile_n == 256) && a.kslice % kBK64 == 0 &&
-                     b.kslice % kBK64 == 0 && 255 * (int64_t)a.ld * 2 + 512 < lim &&
-                     255 * (int64_t)b.ld * 2 + 512 < lim && 2 * per64 == gp.ksteps_per_split;
-    if (k64) {
-      const auto aligned64 = [&](const OperandAddr& o) {
-        return (int64_t)o.kslice == p.K || (o.kslice / kBK64) % 4 == 0;
-      };
-      gp.ksteps = ks64;
-      gp.ksteps_per_split = per64;
-      gp.round_fast = aligned64(a) && aligned64(b) && (splits == 1 || per64 % 4 == 0) ? 1 : 0;
-#define CCL_LAUNCH64(BM_, BN_)                                                                \
-  hipLaunchKernelGGL((gemm_k64_kernel<BM_, BN_>), grid, dim3(Tile64<BM_, BN_>::THREADS), 0, stream, gp)
+    const bool whole = a.kslice % kBK64 == 0 && b.kslice % kBK64 == 0 && 2 * per64 == gp.ksteps_per_split;
+    const int64_t a_jump = (a.slice - a.kslice) * 2, b_jump = (b.slice - (int64_t)b.kslice * b.ld) * 2;
+    const bool fits = whole ? 255 * (int64_t)a.ld * 2 + 512 < lim && 255 * (int64_t)b.ld * 2 + 512 < lim
+                            : 255 * (int64_t)a.ld * 2 + 512 + a_jump < lim &&
+                                  63 * (int64_t)b.ld * 2 + 512 + b_jump < lim;
+    // More than 32 ragged 128x128 tiles per XCD stay with the 32-K stages, whose
+    // 64 KiB let two workgroups share a CU (1920x5120x1792, 75 tiles: 44.7
+    // against 51.5 us); up to 32 there is one per CU and the 64-K stages win
+    // (1152x2048x3328, 18 tiles: 27.4 -> 26.5 us; 1024x3072x9984, 24 tiles:
+    // 104.6 -> 88.3).
+    const bool paired = !whole && g.tile_m == 128 && g.tile_n == 128 && gp.map.tiles_per_xcd > 32;
+    if (g.stage_k == 64 && waves == 8 && !(g.tile_m == 256 && g.tile_n == 256) && fits && !paired) {
+      if (whole) {
+        const auto aligned64 = [&](const OperandAddr& o) {
+          return (int64_t)o.kslice == p.K || (o.kslice / kBK64) % 4 == 0;
+        };
+        gp.ksteps = ks64;
+        gp.ksteps_per_split = per64;
+        gp.round_fast = aligned64(a) && aligned64(b) && (splits == 1 || per64 % 4 == 0) ? 1 : 0;
+      }
+#define CCL_LAUNCH64(BM_, BN_)                                                                  \
+  do {                                                                                          \
+    if (whole)                                                                                  \
+      hipLaunchKernelGGL((gemm_k64_kernel<BM_, BN_, false>), grid, dim3(Tile64<BM_, BN_>::THREADS), \
+                         0, stream, gp);                                                        \
+    else                                                                                        \
+      hipLaunchKernelGGL((gemm_k64_kernel<BM_, BN_, true>), grid, dim3(Tile64<BM_, BN_>::THREADS), \
+                         0, stream, gp);                                                        \
+  } while (0)
       if (g.tile_m == 256 && g.tile_n == 128) CCL_LAUNCH64(256, 128);
       else if (g.tile_m == 128 && g.tile_n == 256) CCL_LAUNCH64(128, 256);
       else if (g.tile_m == 128 && g.tile_n == 128) CCL_LAUNCH64(128, 128);
