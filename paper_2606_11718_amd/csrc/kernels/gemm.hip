@@ -148,6 +148,13 @@ __device__ __forceinline__ void lds_dma16_so(i32x4 rsrc, uint32_t voff, uint32_t
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :: "s"(m0v), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
 }
+// lds_dma16_so with the non-temporal policy, for operand lines that no other
+// workgroup of the XCD reads.
+__device__ __forceinline__ void lds_dma16_nt(i32x4 rsrc, uint32_t voff, uint32_t soff, const char* lds) {
+  const uint32_t m0v = (uint32_t)(uintptr_t)(const lds_char*)lds;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+               :: "s"(m0v), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
+}
 // A run of loads that share one M0: the first sets M0 to the LDS
 // destination of the run, the next ones (lds_dma16_next<OFF>) reuse it.
 // Their instruction offset moves both the memory address and the LDS
@@ -959,7 +966,7 @@ struct Tile64 {
   static_assert(BN == 128 || BN == 256, "B swizzle is defined for 16- and 32-chunk rows");
 };
 
-template <int BM, int BN, bool RAGGED>
+template <int BM, int BN, bool RAGGED, bool BNT>
 __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using T = Tile64<BM, BN>;
@@ -1111,7 +1118,10 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
       } else {
         const int l = wave * T::NB + (i - T::NA);               // rows RPI_B l .. + RPI_B - 1
         const bool hi = l * T::RPI_B >= 32;
-        lds_dma16_so(hi ? d.rb_hi : d.rb, b_voff[i - T::NA], hi ? d.db : 0u, sB + l * 1024);
+        if constexpr (BNT)
+          lds_dma16_nt(hi ? d.rb_hi : d.rb, b_voff[i - T::NA], hi ? d.db : 0u, sB + l * 1024);
+        else
+          lds_dma16_so(hi ? d.rb_hi : d.rb, b_voff[i - T::NA], hi ? d.db : 0u, sB + l * 1024);
       }
     } else if (i < T::NA) {
       char* dst = sA + (wave * T::NA + i) * 1024;
@@ -1119,7 +1129,8 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
       else lds_dma16_so(d.ra, a_voff[i], so_a[j], dst);
     } else {
       char* dst = sB + (wave * T::NB + (i - T::NA)) * 1024;
-      if (j < 0) lds_dma16(d.rb, b_voff[i - T::NA], dst);
+      if constexpr (BNT) lds_dma16_nt(d.rb, b_voff[i - T::NA], j < 0 ? 0u : so_b[j], dst);
+      else if (j < 0) lds_dma16(d.rb, b_voff[i - T::NA], dst);
       else lds_dma16_so(d.rb, b_voff[i - T::NA], so_b[j], dst);
     }
   };
@@ -2889,20 +2900,28 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
         gp.ksteps_per_split = per64;
         gp.round_fast = aligned64(a) && aligned64(b) && (splits == 1 || per64 % 4 == 0) ? 1 : 0;
       }
-#define CCL_LAUNCH64(BM_, BN_)                                                                  \
-  do {                                                                                          \
-    if (whole)                                                                                  \
-      hipLaunchKernelGGL((gemm_k64_kernel<BM_, BN_, false>), grid, dim3(Tile64<BM_, BN_>::THREADS), \
-                         0, stream, gp);                                                        \
-    else                                                                                        \
-      hipLaunchKernelGGL((gemm_k64_kernel<BM_, BN_, true>), grid, dim3(Tile64<BM_, BN_>::THREADS), \
-                         0, stream, gp);                                                        \
+      // With one tile row per partition each line of B is read by one
+      // workgroup of the XCD only, so B streams past the L2 (non-temporal):
+      // 128x28672x8192 98.4 -> 96.0 us, 128x8192x28672 in 4 ranges 101.9 ->
+      // 93.3, 128x14336x4096 43.8 -> 42.1. Where tile rows share B it is
+      // 20-50 % slower.
+      const bool b_once = g.tiles_m == 1 && remap;
+#define CCL_LAUNCH64_AS(BM_, BN_, RAGGED_, BNT_)                                                   \
+  hipLaunchKernelGGL((gemm_k64_kernel<BM_, BN_, RAGGED_, BNT_>), grid,                             \
+                     dim3(Tile64<BM_, BN_>::THREADS), 0, stream, gp)
+#define CCL_LAUNCH64(BM_, BN_)                                       \
+  do {                                                               \
+    if (whole && b_once) CCL_LAUNCH64_AS(BM_, BN_, false, true);     \
+    else if (whole) CCL_LAUNCH64_AS(BM_, BN_, false, false);         \
+    else if (b_once) CCL_LAUNCH64_AS(BM_, BN_, true, true);          \
+    else CCL_LAUNCH64_AS(BM_, BN_, true, false);                     \
   } while (0)
       if (g.tile_m == 256 && g.tile_n == 128) CCL_LAUNCH64(256, 128);
       else if (g.tile_m == 128 && g.tile_n == 256) CCL_LAUNCH64(128, 256);
       else if (g.tile_m == 128 && g.tile_n == 128) CCL_LAUNCH64(128, 128);
       else return hipErrorInvalidValue;
 #undef CCL_LAUNCH64
+#undef CCL_LAUNCH64_AS
       return splits > 1 ? launch_splitk_reduce(p, gp, 16, waves, stream) : hipGetLastError();
     }
   }
