@@ -13,6 +13,7 @@ namespace ccl {
 constexpr int kModelTile = 128;   // output tile of the traffic model (Sec. IV-A)
 constexpr int kNumXcd = 8;        // MI355X: 8 XCDs, workgroups dispatched round-robin
 constexpr int kMaxChiplets = 64;
+constexpr int64_t kInfinityCacheBytes = 256ll << 20;  // MI355X MALL
 constexpr int kGemmBK = 32;       // K extent of one GEMM main-loop step (bf16)
 constexpr int kGemmBK8 = 64;      // the same for fp8 operands
 constexpr int kMaxSplits = 16;    // split-K ranges per tile
@@ -49,6 +50,7 @@ struct GemmConfig {
   int stage_k = 32;                 // bf16: K extent of one LDS stage (32 or 64)
   bool a_pairs = false;             // bf16 256x256: A staged in 64-K pairs (whole lines)
   bool fp8_pipe = false;            // fp8 256x256: fragment reads pipelined across steps
+  bool stream_b = false;            // bf16 64-K stages: B read past the L2 (non-temporal)
   bool supported = false;           // whether ccl_gemm can run this plan
   std::string why_unsupported;
 };

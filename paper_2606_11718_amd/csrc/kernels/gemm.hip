@@ -2900,12 +2900,7 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
         gp.ksteps_per_split = per64;
         gp.round_fast = aligned64(a) && aligned64(b) && (splits == 1 || per64 % 4 == 0) ? 1 : 0;
       }
-      // With one tile row per partition each line of B is read by one
-      // workgroup of the XCD only, so B streams past the L2 (non-temporal):
-      // 128x28672x8192 98.4 -> 96.0 us, 128x8192x28672 in 4 ranges 101.9 ->
-      // 93.3, 128x14336x4096 43.8 -> 42.1. Where tile rows share B it is
-      // 20-50 % slower.
-      const bool b_once = g.tiles_m == 1 && remap;
+      const bool b_once = g.stream_b && remap;
 #define CCL_LAUNCH64_AS(BM_, BN_, RAGGED_, BNT_)                                                   \
   hipLaunchKernelGGL((gemm_k64_kernel<BM_, BN_, RAGGED_, BNT_>), grid,                             \
                      dim3(Tile64<BM_, BN_>::THREADS), 0, stream, gp)

@@ -26,7 +26,6 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // one 16-byte chu
 // alignment (one dwordx4 instruction either way).
 typedef u32x4 u32x4_any __attribute__((aligned(1)));
 
-constexpr int64_t kInfinityCacheBytes = 256ll << 20;          // MI355X MALL
 // Workgroups of copy_stream_kernel's resident grid: 8 of 256 threads per CU
 // on 256 CUs (2048 measured best of 1024, 2048, 3072 and 4096).
 constexpr unsigned kResidentWgs = 2048;
