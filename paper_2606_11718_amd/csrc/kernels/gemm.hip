@@ -174,6 +174,26 @@ __device__ __forceinline__ void lds_dma16_next(i32x4 rsrc, uint32_t voff, uint32
   asm volatile("buffer_load_dwordx4 %0, %1, %2 offen offset:%3 lds"
                :: "v"(voff), "s"(rsrc), "s"(soff), "n"(OFF));
 }
+// Load i of a run; NT as in lds_dma16_nt. lds: where the load itself lands.
+template <bool NT>
+__device__ __forceinline__ void lds_dma16_run(i32x4 rsrc, uint32_t voff, uint32_t soff, const char* lds,
+                                              int i) {
+  if (i == 0) {
+    if constexpr (NT) lds_dma16_nt(rsrc, voff, soff, lds);
+    else lds_dma16_first(rsrc, voff, soff, lds);
+  } else if constexpr (NT) {
+    if (i == 1)
+      asm volatile("buffer_load_dwordx4 %0, %1, %2 offen offset:1024 nt lds" :: "v"(voff), "s"(rsrc), "s"(soff));
+    else if (i == 2)
+      asm volatile("buffer_load_dwordx4 %0, %1, %2 offen offset:2048 nt lds" :: "v"(voff), "s"(rsrc), "s"(soff));
+    else
+      asm volatile("buffer_load_dwordx4 %0, %1, %2 offen offset:3072 nt lds" :: "v"(voff), "s"(rsrc), "s"(soff));
+  } else {
+    if (i == 1) lds_dma16_next<1024>(rsrc, voff, soff);
+    else if (i == 2) lds_dma16_next<2048>(rsrc, voff, soff);
+    else lds_dma16_next<3072>(rsrc, voff, soff);
+  }
+}
 #pragma clang diagnostic pop
 
 // s_waitcnt immediate: vmcnt(vm) and lgkmcnt(lgkm), expcnt not waited on.
@@ -931,10 +951,10 @@ __global__ void __launch_bounds__(128 * WGN, WGN / 2) gemm_kernel(GemmParams p) 
 // parity of lane bits 2..4 are served together). B rows are as in the 32-K
 // kernel, twice as many per stage.
 // RAGGED: K blocks and K ranges that are odd multiples of 32. A stage is two
-// 32-K steps that may lie in different K blocks: the loads of its second 32 K
-// (half of the lanes for A, whole load instructions for B) get the jump to
-// the next block added to their offsets, and a last half stage is filled
-// with zeros. The MFMAs and their order are the 32-K kernel's (C is identical
+// 32-K steps that may lie in different K blocks: A's lanes of the second 32 K
+// get the jump to the next block added to their offsets, B's second 32 K are
+// loaded by waves of their own (4-7), and a last half stage is filled with
+// zeros. The MFMAs and their order are the 32-K kernel's (C is identical
 // bit for bit).
 // ---------------------------------------------------------------------------
 
@@ -994,7 +1014,10 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / T::WGN, wn = wave % T::WGN;
 
-  // ---- global -> LDS: per-lane byte offsets from the K step's tile corner ----
+  // ---- global -> LDS: per-lane byte offsets from the stage's tile corner,
+  // minus the instruction offset 1024 (i % 4) of load i in its run of up to
+  // four that share M0 (they stay non-negative: an operand row is at least as
+  // long as its LDS row) ----
   // A load i of this wave fills LDS rows 8*(wave*NA+i) .. +7 (128 B each);
   // the lane at LDS chunk q of its row fetches global chunk q ^ swz_a64(row).
   uint32_t a_voff[T::NA], a_hi[T::NA];
@@ -1002,18 +1025,19 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   for (int i = 0; i < T::NA; ++i) {
     const int row = 8 * (wave * T::NA + i) + (lane >> 3);
     const int chunk = (lane & 7) ^ swz_a64(row);
-    a_voff[i] = (uint32_t)(row * p.a.ld + chunk * 8) * 2u;
+    a_voff[i] = (uint32_t)(row * p.a.ld + chunk * 8) * 2u - 1024u * (i & 3);
     a_hi[i] = chunk >= 4 ? 0xffffffffu : 0u;      // lanes of the stage's second 32 K
   }
+  // Waves 0-3 load B's first 32 K rows of a stage, waves 4-7 the second.
+  const int b_half = wave >> 2;
   uint32_t b_voff[T::NB];
 #pragma unroll
   for (int i = 0; i < T::NB; ++i) {
-    const int row = T::RPI_B * (wave * T::NB + i) + lane / T::CPR_B;
-    const int chunk = (lane % T::CPR_B) ^ swz_b(row);
-    b_voff[i] = (uint32_t)(row * p.b.ld + chunk * 8) * 2u;
+    const int at = (wave * T::NB + i) * 64 + lane;       // chunk of the stage
+    const int row = at / T::CPR_B;
+    const int chunk = (at % T::CPR_B) ^ swz_b(row);
+    b_voff[i] = (uint32_t)((row - (RAGGED ? 32 * b_half : 0)) * p.b.ld + chunk * 8) * 2u - 1024u * (i & 3);
   }
-  const int32_t a_extent = (BM - 1) * p.a.ld * 2 + kBK64 * 2;
-  const int32_t b_extent = (kBK64 - 1) * p.b.ld * 2 + BN * 2;
 
   // ---- LDS fragment read offsets (bytes), sub-step kk ----
   // A fragment of MFMA tile mt: lane l reads row wm*WM + 16 mt + l % 16,
@@ -1041,104 +1065,72 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   }
   constexpr int kB_KK = 32 * BN * 2;            // bytes between the two sub-steps' B rows
 
-  // ---- operand corners; K-slice block advances every kslice columns/rows ----
-  const uint16_t* a_base = p.A + pr * p.a.part + (int64_t)(ti * BM) * p.a.ld;
-  const uint16_t* b_base = p.B + pc * p.b.part + tj * BN;
+  // ---- one descriptor per operand for the tile over all K blocks (the launch
+  // checks that both extents fit in 31 bits); a stage is the loads' scalar
+  // offset. Against descriptors rebuilt for every stage, which the ragged form
+  // spent 300-800 clocks of a 1000-clock stage on: 1152x2048x3328 28.1 -> 26.5
+  // us, 1024x3072x9984 79.3 -> 74.0; whole K blocks (rebuilt every fourth
+  // stage) measured the same ----
+  const int32_t K = p.ksteps * kUnit;
+  const int32_t a_extent = (int32_t)(((K / p.a.kslice - 1) * p.a.slice + (int64_t)(BM - 1) * p.a.ld + p.a.kslice) * 2);
+  const int32_t b_extent = (int32_t)(((K / p.b.kslice - 1) * p.b.slice + (int64_t)(p.b.kslice - 1) * p.b.ld + BN) * 2);
+  i32x4 a_desc = buffer_rsrc(p.A + pr * p.a.part + (int64_t)(ti * BM) * p.a.ld, a_extent);
+  i32x4 b_desc = buffer_rsrc(p.B + pc * p.b.part + tj * BN, b_extent);
+  // Position in units of kUnit K. RAGGED: B's is this wave's half of the stage.
+  const int32_t kb = RAGGED ? k0 + b_half : k0;
   int64_t a_slice_off, b_slice_off;
   int32_t a_kl, b_kl;
   k_start(p.a, k0 * kUnit, &a_slice_off, &a_kl);
-  k_start(p.b, k0 * kUnit, &b_slice_off, &b_kl);
-  const char* a_next = reinterpret_cast<const char*>(a_base + a_slice_off + a_kl);
-  const char* b_next = reinterpret_cast<const char*>(b_base + b_slice_off + (int64_t)b_kl * p.b.ld);
+  k_start(p.b, kb * kUnit, &b_slice_off, &b_kl);
+  uint32_t a_so = (uint32_t)((a_slice_off + a_kl) * 2);
+  uint32_t b_so = (uint32_t)((b_slice_off + (int64_t)b_kl * p.b.ld) * 2);
   const int32_t a_steps = p.a.kslice / kUnit, b_steps = p.b.kslice / kUnit;
   int32_t a_left = a_steps - a_kl / kUnit, b_left = b_steps - b_kl / kUnit;
-  const int64_t a_adv = kBK64 * 2, b_adv = (int64_t)kBK64 * p.b.ld * 2;
-  const int64_t a_jump = (p.a.slice - p.a.kslice) * 2;
-  const int64_t b_jump = (p.b.slice - (int64_t)p.b.kslice * p.b.ld) * 2;
+  constexpr int kStep = kBK64 / kUnit;          // units per stage
+  const uint32_t a_adv = kBK64 * 2, b_adv = (uint32_t)(kBK64 * p.b.ld * 2);
+  const uint32_t a_jump = (uint32_t)((p.a.slice - p.a.kslice) * 2);
+  const uint32_t b_jump = (uint32_t)((p.b.slice - (int64_t)p.b.kslice * p.b.ld) * 2);
 
-  // RAGGED: da / db are added to the byte offsets of the stage's second 32 K
-  // (the jump to the next K block where the first 32 K end one; past the
-  // range's end da leaves every descriptor and rb_hi is empty, so those loads
-  // return zeros).
+  // Scalar offsets of a stage; da (RAGGED) is added to A's lanes of the
+  // second 32 K: the jump where the first 32 K end a K block, or an offset
+  // past every extent at the end of the range (those loads return zeros).
   struct StageSrc {
-    i32x4 ra, rb, rb_hi;
-    uint32_t da, db;
+    uint32_t sa, sb, da;
   };
-  auto next_ragged = [&](int32_t s) {
+  // The next stage, number s. Past the range the descriptors stay empty.
+  auto next_src = [&](int32_t s, bool live) __attribute__((always_inline)) {
     StageSrc d;
-    const bool live0 = 2 * s < units, live1 = 2 * s + 1 < units;
-    const bool a_mid = a_left == 1, b_mid = b_left == 1;      // the first 32 K end a block
-    d.da = live1 ? (uint32_t)(a_mid ? a_jump : 0) : 0x7ffffff0u;
-    d.db = (uint32_t)(b_mid ? b_jump : 0);
-    d.ra = buffer_rsrc(a_next, live0 ? a_extent + (int32_t)(a_mid ? a_jump : 0) : 0);
-    d.rb = buffer_rsrc(b_next, live0 ? b_extent + (int32_t)d.db : 0);
-    d.rb_hi = d.rb;
-    if (!live1) d.rb_hi[2] = 0;
-    a_left = a_mid ? a_steps : a_left - 1;
-    b_left = b_mid ? b_steps : b_left - 1;
-    const bool a_end = a_left == 1, b_end = b_left == 1;
-    a_next += a_adv + (a_mid ? a_jump : 0) + (a_end ? a_jump : 0);
-    b_next += b_adv + (b_mid ? b_jump : 0) + (b_end ? b_jump : 0);
-    a_left = a_end ? a_steps : a_left - 1;
-    b_left = b_end ? b_steps : b_left - 1;
-    return d;
-  };
-  auto next_src = [&](bool live) {
-    StageSrc d;
-    d.ra = buffer_rsrc(a_next, live ? a_extent : 0);
-    d.rb = buffer_rsrc(b_next, live ? b_extent : 0);
-    const bool a_wrap = --a_left == 0;
-    a_next += a_adv + (a_wrap ? a_jump : 0);
-    a_left = a_wrap ? a_steps : a_left;
-    const bool b_wrap = --b_left == 0;
-    b_next += b_adv + (b_wrap ? b_jump : 0);
-    b_left = b_wrap ? b_steps : b_left;
-    return d;
-  };
-  const int32_t a_extent4 = (BM - 1) * p.a.ld * 2 + 4 * kBK64 * 2;
-  const int32_t b_extent4 = (4 * kBK64 - 1) * p.b.ld * 2 + BN * 2;
-  const uint32_t so_a[4] = {0u, (uint32_t)a_adv, (uint32_t)(2 * a_adv), (uint32_t)(3 * a_adv)};
-  const uint32_t so_b[4] = {0u, (uint32_t)b_adv, (uint32_t)(2 * b_adv), (uint32_t)(3 * b_adv)};
-  auto round_src = [&]() {
-    StageSrc d;
-    d.ra = buffer_rsrc(a_next, a_extent4);
-    d.rb = buffer_rsrc(b_next, b_extent4);
-    const bool a_wrap = a_left == 4;
-    a_next += 4 * a_adv + (a_wrap ? a_jump : 0);
-    a_left = a_wrap ? a_steps : a_left - 4;
-    const bool b_wrap = b_left == 4;
-    b_next += 4 * b_adv + (b_wrap ? b_jump : 0);
-    b_left = b_wrap ? b_steps : b_left - 4;
-    return d;
-  };
-  auto load_one = [&](const StageSrc& d, int j, char* sA, char* sB, int i) {
+    d.sa = a_so;
+    d.sb = b_so;
+    d.da = 0;
     if constexpr (RAGGED) {
-      if (i < T::NA) {
-        lds_dma16(d.ra, a_voff[i] + (a_hi[i] & d.da), sA + (wave * T::NA + i) * 1024);
-      } else {
-        const int l = wave * T::NB + (i - T::NA);               // rows RPI_B l .. + RPI_B - 1
-        const bool hi = l * T::RPI_B >= 32;
-        if constexpr (BNT)
-          lds_dma16_nt(hi ? d.rb_hi : d.rb, b_voff[i - T::NA], hi ? d.db : 0u, sB + l * 1024);
-        else
-          lds_dma16_so(hi ? d.rb_hi : d.rb, b_voff[i - T::NA], hi ? d.db : 0u, sB + l * 1024);
+      if (!live) {
+        if (2 * s >= units) a_desc[2] = 0;
+        if (2 * s + b_half >= units) b_desc[2] = 0;
       }
-    } else if (i < T::NA) {
-      char* dst = sA + (wave * T::NA + i) * 1024;
-      if (j < 0) lds_dma16(d.ra, a_voff[i], dst);
-      else lds_dma16_so(d.ra, a_voff[i], so_a[j], dst);
-    } else {
-      char* dst = sB + (wave * T::NB + (i - T::NA)) * 1024;
-      if constexpr (BNT) lds_dma16_nt(d.rb, b_voff[i - T::NA], j < 0 ? 0u : so_b[j], dst);
-      else if (j < 0) lds_dma16(d.rb, b_voff[i - T::NA], dst);
-      else lds_dma16_so(d.rb, b_voff[i - T::NA], so_b[j], dst);
+      const bool a_mid = a_left == 1;             // the first 32 K end a block
+      d.da = a_mid ? a_jump : 0u;
+      if (!live && 2 * s + 1 >= units) d.da = 0x7ffffff0u;
+    } else if (!live) {
+      if (s >= ksteps) a_desc[2] = b_desc[2] = 0;
     }
+    a_left -= kStep;
+    b_left -= kStep;
+    const bool a_wrap = a_left <= 0, b_wrap = b_left <= 0;
+    a_so += a_adv + (a_wrap ? a_jump : 0u);
+    a_left += a_wrap ? a_steps : 0;
+    b_so += b_adv + (b_wrap ? b_jump : 0u);
+    b_left += b_wrap ? b_steps : 0;
+    return d;
   };
-  auto stage_src = [&](int32_t s) { return RAGGED ? next_ragged(s) : next_src(s < ksteps); };
-  auto load_stage = [&](char* sA, char* sB, int32_t s) {
-    const StageSrc d = stage_src(s);
-#pragma unroll
-    for (int i = 0; i < T::NL; ++i) load_one(d, -1, sA, sB, i);
+  auto load_one = [&](const StageSrc& d, char* sA, char* sB, int i) __attribute__((always_inline)) {
+    if (i < T::NA) {
+      const uint32_t v = RAGGED ? a_voff[i] + (a_hi[i] & d.da) : a_voff[i];
+      lds_dma16_run<false>(a_desc, v, d.sa, sA + (wave * T::NA + i) * 1024, i & 3);
+    } else {
+      const int k = i - T::NA;
+      lds_dma16_run<BNT>(b_desc, b_voff[k], d.sb, sB + (wave * T::NB + k) * 1024, k & 3);
+    }
   };
 
   AFrags<T::TM> fa0, fa1;
@@ -1173,7 +1165,7 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
 
   // One step on stage (sA, sB); on entry fa0/fb0 hold its sub-step 0.
   auto step = [&](const char* sA, const char* sB, char* lA, char* lB, const char* nA,
-                  const char* nB, const StageSrc& d, int j) {
+                  const char* nB, const StageSrc& d) __attribute__((always_inline)) {
     constexpr int kMfma = T::TM * T::TN;
     constexpr int kReads = T::TM + 2 * T::TN;
     constexpr int kOps1 = kReads + T::NL;
@@ -1182,14 +1174,14 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
       mfma_one(fa0, fb0, i / T::TN, i % T::TN);
       if (i < T::TM) read_a(sA, fa1, 1, i);
       else if (i < kReads) read_b(sB, fb1, 1, i - T::TM);
-      else if (i < kOps1) load_one(d, j, lA, lB, i - kReads);
+      else if (i < kOps1) load_one(d, lA, lB, i - kReads);
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int i = kMfma; i < kOps1; ++i) {
       if (i < T::TM) read_a(sA, fa1, 1, i);
       else if (i < kReads) read_b(sB, fb1, 1, i - T::TM);
-      else load_one(d, j, lA, lB, i - kReads);
+      else load_one(d, lA, lB, i - kReads);
     }
     __builtin_amdgcn_sched_barrier(0);
     stage_barrier();
@@ -1210,56 +1202,37 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
 
   // Prologue: the first NS-1 stages in flight, then stage 0's sub-step 0.
 #pragma unroll
-  for (int j = 0; j < NS - 1; ++j) load_stage(smA[j], smB[j], j);
+  for (int j = 0; j < NS - 1; ++j) {
+    const StageSrc d = next_src(j, false);
+#pragma unroll
+    for (int i = 0; i < T::NL; ++i) load_one(d, smA[j], smB[j], i);
+  }
   stage_barrier();
   if (tl_on) tl_rt[1] = __builtin_amdgcn_s_memrealtime();
 #pragma unroll
   for (int mt = 0; mt < T::TM; ++mt) read_a(smA[0], fa0, 0, mt);
 #pragma unroll
   for (int i = 0; i < 2 * T::TN; ++i) read_b(smB[0], fb0, 0, i);
-  // Step s works on stage s % NS, loads stage (s + NS - 1) % NS and reads
-  // stage (s + 1) % NS; ph is s modulo a multiple of NS.
-  auto phase_step = [&](int ph, const StageSrc& d, int j) {
-    step(smA[ph % NS], smB[ph % NS], smA[(ph + NS - 1) % NS], smB[(ph + NS - 1) % NS],
-         smA[(ph + 1) % NS], smB[(ph + 1) % NS], d, j);
+  // Step s (phase ph = s % NS) works on stage s % NS, loads stage
+  // (s + NS - 1) % NS and reads stage (s + 1) % NS. live: the stage it loads
+  // is a whole one of the range.
+  auto phase_step = [&](int ph, int32_t s, bool live) __attribute__((always_inline)) {
+    const StageSrc d = next_src(s + NS - 1, live);
+    step(smA[ph], smB[ph], smA[(ph + NS - 1) % NS], smB[(ph + NS - 1) % NS], smA[(ph + 1) % NS],
+         smB[(ph + 1) % NS], d);
   };
-  auto single_step = [&](int ph, int32_t s) {
-    const StageSrc d = stage_src(s + NS - 1);
-    phase_step(ph, d, -1);
-  };
+  // Rounds of NS steps whose loads are all whole stages, branch-free; then
+  // the rest, each behind a (uniform) bound check.
+  const int32_t whole = RAGGED ? units / 2 : ksteps;
   int32_t s = 0;
-  if (!RAGGED && p.round_fast) {
-    // Rounds of 4 steps whose loads (steps s+NS-1 .. s+NS+2) form a
-    // 4-aligned group, all live, sharing one pair of descriptors. The first
-    // kFirst steps run alone so that the first round's loads start
-    // 4-aligned; a loop iteration runs kLoop steps (a multiple of NS and of
-    // 4, so every phase is known at compile time); the remaining steps
-    // (fewer than kLoop + NS - 1) run alone.
-    constexpr int kFirst = (4 - (NS - 1) % 4) % 4;
-    constexpr int kLoop = NS % 4 == 0 ? NS : 4 * NS;
+  for (; s + 2 * NS - 1 <= whole; s += NS) {
 #pragma unroll
-    for (int t = 0; t < kFirst; ++t)
-      if (t < ksteps) single_step(t, t);
-    for (s = kFirst; s + kLoop + NS - 1 <= ksteps; s += kLoop) {
+    for (int j = 0; j < NS; ++j) phase_step(j, s + j, true);
+  }
+  for (; s < ksteps; s += NS) {
 #pragma unroll
-      for (int r = 0; r < kLoop / 4; ++r) {
-        const StageSrc d = round_src();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) phase_step(kFirst + 4 * r + j, d, j);
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < kLoop + NS - 2; ++t)
-      if (s + t < ksteps) single_step(kFirst + t, s + t);
-  } else {
-    const int32_t full = ksteps - ksteps % NS;
-    for (; s < full; s += NS) {
-#pragma unroll
-      for (int j = 0; j < NS; ++j) single_step(j, s + j);
-    }
-#pragma unroll
-    for (int j = 0; j < NS - 1; ++j)
-      if (s + j < ksteps) single_step(j, s + j);
+    for (int j = 0; j < NS; ++j)
+      if (s + j < ksteps) phase_step(j, s + j, false);
   }
 
   if (tl_on) {
@@ -2871,20 +2844,19 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
     return splits > 1 ? launch_splitk_reduce(p, gp, 32, waves8, stream) : hipGetLastError();
   }
   // 64-K stages (plan's choice for the bf16 tiles below 256x256), with the
-  // extents of the 4-step rounds (255 rows of A or B) or of a stage across
-  // two K blocks within 32-bit offsets. Where both K blocks are multiples of
-  // 64 and split-K cuts K at whole stages, the rounds form runs; otherwise the
-  // ragged one, whose K ranges are the 32-K ranges, so that the workspace and
-  // the reduce do not depend on the kernel.
+  // operands' extents within the descriptors' 31 bits. Where both K blocks are
+  // multiples of 64 and split-K cuts K at whole stages, a stage lies in one K
+  // block; otherwise the ragged form, whose K ranges are the 32-K ranges, so
+  // that the workspace and the reduce do not depend on the kernel, and whose K
+  // blocks hold at least a stage.
   {
     const int64_t lim = ((int64_t)1 << 31) - 4096;
     const int32_t ks64 = (int32_t)(p.K / kBK64);
     const int32_t per64 = (ks64 + splits - 1) / splits;
     const bool whole = a.kslice % kBK64 == 0 && b.kslice % kBK64 == 0 && 2 * per64 == gp.ksteps_per_split;
-    const int64_t a_jump = (a.slice - a.kslice) * 2, b_jump = (b.slice - (int64_t)b.kslice * b.ld) * 2;
-    const bool fits = whole ? 255 * (int64_t)a.ld * 2 + 512 < lim && 255 * (int64_t)b.ld * 2 + 512 < lim
-                            : 255 * (int64_t)a.ld * 2 + 512 + a_jump < lim &&
-                                  63 * (int64_t)b.ld * 2 + 512 + b_jump < lim;
+    const bool fits = ((p.K / a.kslice - 1) * a.slice + 256 * (int64_t)a.ld) * 2 < lim &&
+                      ((p.K / b.kslice - 1) * b.slice + (int64_t)b.kslice * b.ld + 256) * 2 < lim &&
+                      (whole || (a.kslice >= kBK64 && b.kslice >= kBK64));
     // More than 32 ragged 128x128 tiles per XCD stay with the 32-K stages, whose
     // 64 KiB let two workgroups share a CU (1920x5120x1792, 75 tiles: 44.7
     // against 51.5 us); up to 32 there is one per CU and the 64-K stages win
@@ -2893,12 +2865,8 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
     const bool paired = !whole && g.tile_m == 128 && g.tile_n == 128 && gp.map.tiles_per_xcd > 32;
     if (g.stage_k == 64 && waves == 8 && !(g.tile_m == 256 && g.tile_n == 256) && fits && !paired) {
       if (whole) {
-        const auto aligned64 = [&](const OperandAddr& o) {
-          return (int64_t)o.kslice == p.K || (o.kslice / kBK64) % 4 == 0;
-        };
         gp.ksteps = ks64;
         gp.ksteps_per_split = per64;
-        gp.round_fast = aligned64(a) && aligned64(b) && (splits == 1 || per64 % 4 == 0) ? 1 : 0;
       }
       const bool b_once = g.stream_b && remap;
 #define CCL_LAUNCH64_AS(BM_, BN_, RAGGED_, BNT_)                                                   \

@@ -1,0 +1,27 @@
+"""The bf16 64-K-stage kernels' direct-to-LDS loads, in the gfx950 assembly
+built here from source (no GPU needed): loads of one operand share an M0 write,
+and load i of such a run must carry the instruction offset 1024 i, with no
+other M0 write inside the run and the run's loads in order; and nothing spills."""
+import re
+
+import pytest
+
+from tests.test_host_isa import _body, _lds_offset, asm  # noqa: F401
+
+
+@pytest.mark.parametrize("bm,bn,lengths", [(256, 128, {2, 4}), (128, 256, {2, 4}), (128, 128, {2})])
+@pytest.mark.parametrize("ragged", [0, 1])
+@pytest.mark.parametrize("nt", [0, 1])
+def test_k64_runs(asm, bm, bn, lengths, ragged, nt):  # noqa: F811
+    name = (f"_ZN3ccl12_GLOBAL__N_115gemm_k64_kernelILi{bm}ELi{bn}ELb{ragged}ELb{nt}EEEv"
+            "NS0_10GemmParamsE")
+    body = _body(asm, name)
+    runs = []
+    for ln in body:
+        if re.match(r"s_\w+\s+m0\b", ln):
+            runs.append([])
+        elif "buffer_load" in ln and re.search(r"\blds\b", ln):
+            runs[-1].append(_lds_offset(ln))
+    assert {len(r) for r in runs} == lengths
+    assert all(r == [1024 * i for i in range(len(r))] for r in runs)
+    assert not any("scratch_" in ln for ln in body)
