@@ -157,8 +157,9 @@ void choose_gemm_config(Plan* p) {
   // step of load lookahead.
   // CCL_GEMM_STAGE_K=32 selects the 32-K stages everywhere.
   g.stage_k = (p->ab_type == DT_BF16 && g.waves == 8 && !(btm == 256 && btn == 256)) ? 64 : 32;
-  if (const char* e = std::getenv("CCL_GEMM_STAGE_K"))
-    if (std::atoi(e) == 32) g.stage_k = 32;
+  const char* stage_env = std::getenv("CCL_GEMM_STAGE_K");
+  const bool stage32 = stage_env && std::atoi(stage_env) == 32;
+  if (stage32) g.stage_k = 32;
   // B streams past the L2 where each of its lines is read by one workgroup of
   // the XCD only (one tile row per partition), and it is above the Infinity
   // Cache size (non-temporal lines do not stay there either): 128x28672x8192
@@ -189,6 +190,25 @@ void choose_gemm_config(Plan* p) {
   g.fp8_pipe = p->ab_type == DT_FP8_E4M3 && g.waves == 8 && btm == 256 && btn == 256;
   if (const char* e = std::getenv("CCL_GEMM_FP8_PIPE"))
     if (std::atoi(e) == 0) g.fp8_pipe = false;
+  // 128x192 tiles for unsplit bf16 launches where their waves of 32 per XCD
+  // cost less than the tile above (same estimate). They fill partitions whose
+  // 128- or 256-wide tiles leave CUs idle: 4096x1536x2048 (2048x384 per XCD, 24
+  // tiles of 256x128, now 32) 33.9 -> 30.9 us, 256x16896x1280 (33 tiles of
+  // 128x128, now 22) 25.7 -> 18.0. The kernel has 64-K stages, K blocks of at
+  // least one, and 31-bit extents. CCL_GEMM_WIDE=0|1 forbids / takes them
+  // wherever they exist.
+  {
+    const int64_t lim = ((int64_t)1 << 31) - 4096;
+    const Layout &la = p->lay[OP_A], &lb = p->lay[OP_B];
+    const bool exists = p->ab_type == DT_BF16 && pr % 128 == 0 && pc % 192 == 0 && g.waves == 8 &&
+                        (g.stage_k == 64 || (btm == 256 && btn == 256 && !stage32)) && !forced &&
+                        p->K / p->Gc >= 64 && p->K / p->Gr >= 64 &&
+                        la.strip_stride_bytes * p->Gc + 512 * p->K < lim && lb.total_bytes + 512 < lim;
+    const int64_t tiles = (pr / 128) * (pc / 192);
+    const int64_t waves = ((tiles + g.xcd_per_chiplet - 1) / g.xcd_per_chiplet + 31) / 32;
+    g.wide = exists && (double)waves * 128 * 192 / 0.75 < best;
+    if (const char* e = std::getenv("CCL_GEMM_WIDE")) g.wide = exists && std::atoi(e) != 0;
+  }
   if (g.workgroups > 0x7fffffff) {
     g.why_unsupported = "launch too large";
     return;
@@ -412,6 +432,15 @@ TileMap tile_map(const Plan& p, int splits) {
   const int64_t per_xcd = (g.tiles_m * g.tiles_n * splits + g.xcd_per_chiplet - 1) / g.xcd_per_chiplet;
   return TileMap{g.xcd_per_chiplet, p.Gc, (int32_t)g.tiles_m, (int32_t)g.tiles_n,
                  (int32_t)per_xcd, g.group_m, splits};
+}
+
+TileMap wide_tile_map(const Plan& p) {
+  const GemmConfig& g = p.gemm;
+  const int64_t tm = p.part_rows() / 128, tn = p.part_cols() / 192;
+  // 8 tile rows per group: 32 resident tiles then cover 1024 x 768 of C
+  return TileMap{g.xcd_per_chiplet, p.Gc, (int32_t)tm, (int32_t)tn,
+                 (int32_t)((tm * tn + g.xcd_per_chiplet - 1) / g.xcd_per_chiplet),
+                 (int32_t)std::min<int64_t>(8, tm), 1};
 }
 
 int64_t gemm_ksteps(const Plan& p) {

@@ -107,6 +107,14 @@ __device__ __forceinline__ int swz_a16(int row) { return ((row >> 2) & 1) << 1; 
 // 2 * ((row & 3) | (row & 8) >> 1) sends these 16 (row, chunk) pairs to 16
 // distinct 16-byte bank slots.
 __device__ __forceinline__ int swz_b(int row) { return ((row & 3) << 1) | (((row >> 3) & 1) << 3); }
+// Rows of 24 chunks (BN = 192) already put odd rows 8 slots after even ones;
+// XOR-ing the chunk with 2 * ((row & 2) >> 1 | (row & 8) >> 2) stays within
+// groups of 8 chunks and sends the same 16 pairs to distinct slots.
+template <int BN>
+__device__ __forceinline__ int swz_bn(int row) {
+  if constexpr (BN % 128 == 0) return swz_b(row);
+  else return (row & 2) | (((row >> 3) & 1) << 2);
+}
 
 __device__ __forceinline__ uint32_t bf16_rne(float f) {
   uint32_t u = __float_as_uint(f);
@@ -382,6 +390,19 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, const Acc (&acc)
   }
 }
 
+// The i-th wave-wide access of consecutive 16-byte chunks over rows of CPR
+// chunks: the row and chunk of a lane.
+template <int CPR>
+struct RowAccess {
+  static constexpr bool kWhole = 64 % CPR == 0;       // an access is whole rows
+  __device__ static __forceinline__ int row(int i, int lane) {
+    return kWhole ? i * (64 / CPR) + lane / CPR : (i * 64 + lane) / CPR;
+  }
+  __device__ static __forceinline__ int col(int i, int lane) {
+    return kWhole ? lane % CPR : (i * 64 + lane) % CPR;
+  }
+};
+
 // Epilogue of the kernels with 16x16 MFMA tiles (bf16, fp8 16x16x128) for a
 // bf16 C that is not read (beta 0, no split-K), staged through LDS so that C
 // leaves the CU in whole 128-byte lines. The direct form (store_tile) writes 8 bytes per lane, i.e. 32-byte
@@ -405,10 +426,12 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
   constexpr int ROWB = BN * 2;              // bytes per C row in LDS and in C
   constexpr int CPR = BN / 8;               // 16-byte chunks per row
   constexpr int HALF = BM / 2;              // rows per half
-  constexpr int RPI = 64 / CPR;             // rows per wave-wide 16-byte access
   constexpr int RPW = BM / NW;              // rows copied out per wave
+  using X = RowAccess<CPR>;
   static_assert(HALF % WM == 0, "a wave's rows lie in one half");
-  static_assert(RPW % RPI == 0, "whole accesses per wave");
+  static_assert(RPW * CPR % 64 == 0, "whole accesses per wave");
+  // Chunk swizzle of row r: rows of 24 chunks already alternate by 8 slots.
+  auto swz = [](int r) { return CPR % 16 == 0 ? r & 15 : (r >> 1) & 7; };
   // No wave reads the stage buffers any more and no load into them is in
   // flight (the direct-to-LDS loads of the last steps included).
   __builtin_amdgcn_s_waitcnt(0);
@@ -427,7 +450,7 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
       uint2 v;
       v.x = bf16_rne(o[0]) | (bf16_rne(o[1]) << 16);
       v.y = bf16_rne(o[2]) | (bf16_rne(o[3]) << 16);
-      *reinterpret_cast<uint2*>(half + r * ROWB + (((col >> 3) ^ (r & 15)) << 4) + ((col >> 2) & 1) * 8) = v;
+      *reinterpret_cast<uint2*>(half + r * ROWB + (((col >> 3) ^ swz(r)) << 4) + ((col >> 2) & 1) * 8) = v;
     }
   }
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
@@ -436,12 +459,11 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
   asm volatile("" ::: "memory");
   uint16_t* C = static_cast<uint16_t*>(p.C) + pr * p.c.part + pc * p.c.slice +
                 (int64_t)(ti * BM) * p.c.ld + tj * BN;
-  const int c = lane % CPR;
 #pragma unroll
-  for (int i = 0; i < RPW / RPI; ++i) {
-    const int row = wave * RPW + i * RPI + lane / CPR;
+  for (int i = 0; i < RPW * CPR / 64; ++i) {
+    const int row = wave * RPW + X::row(i, lane), c = X::col(i, lane);
     const int r = row % HALF;
-    const uint4 v = *reinterpret_cast<const uint4*>((row < HALF ? lo : hi) + r * ROWB + ((c ^ (r & 15)) << 4));
+    const uint4 v = *reinterpret_cast<const uint4*>((row < HALF ? lo : hi) + r * ROWB + ((c ^ swz(r)) << 4));
     uint4* dst = reinterpret_cast<uint4*>(C + (int64_t)row * p.c.ld + c * 8);
     if constexpr (NT)
       __builtin_nontemporal_store(__builtin_bit_cast(i32x4, v), reinterpret_cast<i32x4*>(dst));
@@ -469,34 +491,34 @@ __device__ __forceinline__ void store_tile_staged_f32(const GemmParams& p, const
   constexpr int HALF = BM / 2;
   constexpr int ROWB = BN * 4;                        // bytes per row in LDS
   constexpr int CPR = BN / 4;                         // 16-byte chunks (4 columns) per row
-  constexpr int RPI = 64 / CPR;                       // rows per wave-wide access
-  constexpr int kPassBytes = BUF < 4 * NW * RPI * ROWB ? BUF : 4 * NW * RPI * ROWB;
+  using X = RowAccess<CPR>;
+  constexpr int kPassBytes = BUF < 4 * NW * 1024 ? BUF : 4 * NW * 1024;
   // Passes: each half's rows of a pass fit in BUF, and a lane holds at most
   // 8 old C values of 4 columns at once (32 registers beside the accumulators).
-  constexpr int P = (HALF * ROWB + kPassBytes - 1) / kPassBytes;
+  constexpr int kMinP = (HALF * ROWB + kPassBytes - 1) / kPassBytes;
+  constexpr int P = kMinP <= 1 ? 1 : kMinP <= 2 ? 2 : kMinP <= 4 ? 4 : 8;
   constexpr int RP = HALF / P;                        // rows of each half per pass
   constexpr int RPW = 2 * RP / NW;                    // rows copied out per wave and pass
-  constexpr int NI = RPW / RPI;
+  constexpr int NI = RPW * CPR / 64;
   static_assert(HALF % WM == 0 && RP % 16 == 0 && RP * P == HALF, "whole MFMA tiles per pass");
   static_assert(RP % WM == 0 || WM % RP == 0, "a wave's rows nest in the passes");
-  static_assert(RP * ROWB <= BUF && RPW % RPI == 0 && RP % RPW == 0, "whole accesses per wave");
+  static_assert(RP * ROWB <= BUF && RPW * CPR % 64 == 0 && RP % RPW == 0, "whole accesses per wave");
   __builtin_amdgcn_s_waitcnt(0);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   const int64_t c_tile = pr * p.c.part + pc * p.c.slice + (int64_t)(ti * BM) * p.c.ld + tj * BN;
-  const int c = lane % CPR;
-  const int row0 = wave * RPW + lane / CPR;           // first staged row of this lane in a pass
+  const int row0 = wave * RPW;                        // first staged row of this wave in a pass
   char* half = wm * WM < HALF ? lo : hi;
 #pragma unroll
   for (int ps = 0; ps < P; ++ps) {
     // rows 0 .. RP-1 of a pass are the first half's, RP .. 2 RP-1 the second's
-    const int64_t at = c_tile + (int64_t)((row0 < RP ? row0 : row0 - RP + HALF) + ps * RP) * p.c.ld + 4 * c;
+    const int64_t at = c_tile + (int64_t)((row0 < RP ? row0 : row0 - RP + HALF) + ps * RP) * p.c.ld;
     f32x4 old[NI];
     if (p.epi == 2) {
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
-        const int64_t idx = at + (int64_t)(i * RPI) * p.c.ld;
+        const int64_t idx = at + (int64_t)X::row(i, lane) * p.c.ld + 4 * X::col(i, lane);
         if constexpr (F32) {
           old[i] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.C) + idx);
         } else {
@@ -523,7 +545,7 @@ __device__ __forceinline__ void store_tile_staged_f32(const GemmParams& p, const
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int row = row0 + i * RPI;
+      const int row = row0 + X::row(i, lane), c = X::col(i, lane);
       const int r = row < RP ? row : row - RP;
       f32x4 o = *reinterpret_cast<const f32x4*>((row < RP ? lo : hi) + r * ROWB + ((c ^ (r & 15)) << 4));
       if (p.epi == 2) {
@@ -532,7 +554,7 @@ __device__ __forceinline__ void store_tile_staged_f32(const GemmParams& p, const
       } else if (p.epi == 1) {
         o *= p.alpha;
       }
-      const int64_t idx = at + (int64_t)(i * RPI) * p.c.ld;
+      const int64_t idx = at + (int64_t)X::row(i, lane) * p.c.ld + 4 * c;
       if constexpr (F32) {
         __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + idx));
       } else {
@@ -977,13 +999,14 @@ struct Tile64 {
   static constexpr int NB = B_BYTES / (1024 * NW);     // B loads per wave per stage
   static constexpr int NL = NA + NB;
   // as many stages as 160 KiB holds, at most 4: 3 for 256x128 and
-  // 128x256, 4 for 128x128
+  // 128x256, 4 for 128x192 and 128x128 (5 measured the same there)
   static constexpr int NS = (160 * 1024) / (A_BYTES + B_BYTES) >= 4 ? 4 : 3;
   static_assert(BM * BN < 256 * 256, "256x256 tiles use the 32-K stages");
   static_assert(NA >= 1 && NB >= 1 && TN >= 1 && TM >= 1, "tile too small for the wave grid");
   static_assert(NS * (A_BYTES + B_BYTES) <= 160 * 1024, "LDS stages exceed 160 KiB");
   static_assert((NS - 2) * NL <= 63, "the stage wait count exceeds vmcnt's range");
-  static_assert(BN == 128 || BN == 256, "B swizzle is defined for 16- and 32-chunk rows");
+  static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "whole loads per wave");
+  static_assert(BN == 128 || BN == 192 || BN == 256, "B swizzle is defined for 16-, 24- and 32-chunk rows");
 };
 
 template <int BM, int BN, bool RAGGED, bool BNT>
@@ -1035,7 +1058,7 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   for (int i = 0; i < T::NB; ++i) {
     const int at = (wave * T::NB + i) * 64 + lane;       // chunk of the stage
     const int row = at / T::CPR_B;
-    const int chunk = (at % T::CPR_B) ^ swz_b(row);
+    const int chunk = (at % T::CPR_B) ^ swz_bn<BN>(row);
     b_voff[i] = (uint32_t)((row - (RAGGED ? 32 * b_half : 0)) * p.b.ld + chunk * 8) * 2u - 1024u * (i & 3);
   }
 
@@ -1059,7 +1082,7 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
       for (int r = 0; r < 2; ++r) {
         const int krow = 8 * g + 4 * r + (s >> 2);
         const int col = wn * T::WN + nt * 16 + 4 * (s & 3);
-        b_rd[nt][r] = krow * (BN * 2) + (((col >> 3) ^ swz_b(krow)) * 16) + ((col >> 2) & 1) * 8;
+        b_rd[nt][r] = krow * (BN * 2) + (((col >> 3) ^ swz_bn<BN>(krow)) * 16) + ((col >> 2) & 1) * 8;
       }
     }
   }
@@ -2750,7 +2773,9 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
   gp.c = c;
   if (splits < 1 || (splits > 1 && (!remap || !ws))) return hipErrorInvalidValue;
   splits = effective_splits(p, splits);      // every K range non-empty
-  gp.map = tile_map(p, splits);
+  // 128x192 tiles (the plan's choice, with operands that fit the kernel below)
+  const bool wide = g.wide && remap && splits == 1 && !timeline;
+  gp.map = wide ? wide_tile_map(p) : tile_map(p, splits);
   const bool fp8 = p.ab_type == DT_FP8_E4M3;
   if (timeline && (fp8 || splits > 1)) return hipErrorInvalidValue;   // bf16 kernel only
   gp.ksteps = (int32_t)(p.K / (fp8 ? kBK8 : kBK));
@@ -2862,13 +2887,14 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
     // against 51.5 us); up to 32 there is one per CU and the 64-K stages win
     // (1152x2048x3328, 18 tiles: 27.4 -> 26.5 us; 1024x3072x9984, 24 tiles:
     // 104.6 -> 88.3).
-    const bool paired = !whole && g.tile_m == 128 && g.tile_n == 128 && gp.map.tiles_per_xcd > 32;
-    if (g.stage_k == 64 && waves == 8 && !(g.tile_m == 256 && g.tile_n == 256) && fits && !paired) {
+    const bool paired = !wide && !whole && g.tile_m == 128 && g.tile_n == 128 && gp.map.tiles_per_xcd > 32;
+    if (wide && !fits) return hipErrorInvalidValue;   // the plan rules this out
+    if (wide || (g.stage_k == 64 && waves == 8 && !(g.tile_m == 256 && g.tile_n == 256) && fits && !paired)) {
       if (whole) {
         gp.ksteps = ks64;
         gp.ksteps_per_split = per64;
       }
-      const bool b_once = g.stream_b && remap;
+      const bool b_once = g.stream_b && remap && gp.map.tiles_m == 1;
 #define CCL_LAUNCH64_AS(BM_, BN_, RAGGED_, BNT_)                                                   \
   hipLaunchKernelGGL((gemm_k64_kernel<BM_, BN_, RAGGED_, BNT_>), grid,                             \
                      dim3(Tile64<BM_, BN_>::THREADS), 0, stream, gp)
@@ -2879,7 +2905,8 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
     else if (b_once) CCL_LAUNCH64_AS(BM_, BN_, true, true);          \
     else CCL_LAUNCH64_AS(BM_, BN_, true, false);                     \
   } while (0)
-      if (g.tile_m == 256 && g.tile_n == 128) CCL_LAUNCH64(256, 128);
+      if (wide) CCL_LAUNCH64(128, 192);
+      else if (g.tile_m == 256 && g.tile_n == 128) CCL_LAUNCH64(256, 128);
       else if (g.tile_m == 128 && g.tile_n == 256) CCL_LAUNCH64(128, 256);
       else if (g.tile_m == 128 && g.tile_n == 128) CCL_LAUNCH64(128, 128);
       else return hipErrorInvalidValue;
