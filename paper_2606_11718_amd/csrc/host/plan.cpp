@@ -430,17 +430,17 @@ Traffic remote_bytes(const Plan& p, Placement pl, int flags) {
 TileMap tile_map(const Plan& p, int splits) {
   const GemmConfig& g = p.gemm;
   const int64_t per_xcd = (g.tiles_m * g.tiles_n * splits + g.xcd_per_chiplet - 1) / g.xcd_per_chiplet;
-  return TileMap{g.xcd_per_chiplet, p.Gc, (int32_t)g.tiles_m, (int32_t)g.tiles_n,
-                 (int32_t)per_xcd, g.group_m, splits};
+  return make_tile_map(g.xcd_per_chiplet, p.Gc, (int32_t)g.tiles_m, (int32_t)g.tiles_n,
+                 (int32_t)per_xcd, g.group_m, splits);
 }
 
 TileMap wide_tile_map(const Plan& p) {
   const GemmConfig& g = p.gemm;
   const int64_t tm = p.part_rows() / 128, tn = p.part_cols() / 192;
   // 8 tile rows per group: 32 resident tiles then cover 1024 x 768 of C
-  return TileMap{g.xcd_per_chiplet, p.Gc, (int32_t)tm, (int32_t)tn,
+  return make_tile_map(g.xcd_per_chiplet, p.Gc, (int32_t)tm, (int32_t)tn,
                  (int32_t)((tm * tn + g.xcd_per_chiplet - 1) / g.xcd_per_chiplet),
-                 (int32_t)std::min<int64_t>(8, tm), 1};
+                 (int32_t)std::min<int64_t>(8, tm), 1);
 }
 
 int64_t gemm_ksteps(const Plan& p) {

@@ -75,6 +75,7 @@ struct GemmParams {
   OperandAddr a, b, c;
   TileMap map;
   int32_t ksteps;       // K / (the kernel's K step)
+  int32_t a_blocks, b_blocks;  // K blocks of A and B (K / kslice)
   int32_t remap;        // 1: XCD-aware map; 0: native raster over the whole C
   int32_t grid_r;       // Gr (native raster)
   int32_t epi;          // epilogue: 0 acc, 1 alpha*acc, 2 alpha*acc + beta*C (C read)
@@ -284,7 +285,7 @@ __device__ __forceinline__ bool tile_of_block(const GemmParams& p, int32_t* pr, 
 // in scalar registers.
 __device__ __forceinline__ void k_start(const OperandAddr& o, int32_t k_elems, int64_t* slice_off,
                                         int32_t* kl) {
-  const int32_t kc = __builtin_amdgcn_readfirstlane(k_elems / o.kslice);
+  const int32_t kc = k_elems == 0 ? 0 : __builtin_amdgcn_readfirstlane(k_elems / o.kslice);
   *slice_off = (int64_t)kc * o.slice;
   *kl = __builtin_amdgcn_readfirstlane(k_elems - kc * o.kslice);
 }
@@ -1094,9 +1095,8 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   // spent 300-800 clocks of a 1000-clock stage on: 1152x2048x3328 28.1 -> 26.5
   // us, 1024x3072x9984 79.3 -> 74.0; whole K blocks (rebuilt every fourth
   // stage) measured the same ----
-  const int32_t K = p.ksteps * kUnit;
-  const int32_t a_extent = (int32_t)(((K / p.a.kslice - 1) * p.a.slice + (int64_t)(BM - 1) * p.a.ld + p.a.kslice) * 2);
-  const int32_t b_extent = (int32_t)(((K / p.b.kslice - 1) * p.b.slice + (int64_t)(p.b.kslice - 1) * p.b.ld + BN) * 2);
+  const int32_t a_extent = (int32_t)(((p.a_blocks - 1) * p.a.slice + (int64_t)(BM - 1) * p.a.ld + p.a.kslice) * 2);
+  const int32_t b_extent = (int32_t)(((p.b_blocks - 1) * p.b.slice + (int64_t)(p.b.kslice - 1) * p.b.ld + BN) * 2);
   i32x4 a_desc = buffer_rsrc(p.A + pr * p.a.part + (int64_t)(ti * BM) * p.a.ld, a_extent);
   i32x4 b_desc = buffer_rsrc(p.B + pc * p.b.part + tj * BN, b_extent);
   // Position in units of kUnit K. RAGGED: B's is this wave's half of the stage.
@@ -1354,7 +1354,7 @@ __global__ void __launch_bounds__(512, 2) gemm_a2_kernel(GemmParams p) {
   // A: one descriptor for the tile's 256 rows over all K blocks of the
   // operand (the launch checks that it fits in 31 bits); the scalar offset
   // selects the pair.
-  const int32_t a_blocks = p.ksteps * kBK / p.a.kslice;
+  const int32_t a_blocks = p.a_blocks;
   const int32_t a_extent = (a_blocks - 1) * p.a.slice * 2 + (BM - 1) * p.a.ld * 2 + p.a.kslice * 2;
   const int32_t b_extent = (kBK - 1) * p.b.ld * 2 + BN * 2;
 
@@ -2181,9 +2181,8 @@ __global__ void __launch_bounds__(512, 2) gemm_fp8p_kernel(GemmParams p) {
   // One descriptor per operand for the whole tile: A's 256 rows and B's
   // 256 columns over all K blocks (the launch checks that both extents fit
   // in 31 bits); a stage is selected by the loads' scalar offset.
-  const int32_t K = p.ksteps * kBK8x;
-  const int32_t a_extent = (K / p.a.kslice - 1) * p.a.slice + (BM - 1) * p.a.ld + p.a.kslice;
-  const int32_t b_extent = (int32_t)((K / p.b.kslice - 1) * p.b.slice +
+  const int32_t a_extent = (p.a_blocks - 1) * p.a.slice + (BM - 1) * p.a.ld + p.a.kslice;
+  const int32_t b_extent = (int32_t)((p.b_blocks - 1) * p.b.slice +
                                      (int64_t)(p.b.kslice - 1) * p.b.ld + BN);
 
   int32_t a_rd[2];
@@ -2509,9 +2508,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 4) gemm_fp8s_kerne
   // One descriptor per operand for the whole tile over all K blocks (the
   // launch checks that both extents fit in 31 bits); a stage is selected by
   // the loads' scalar offset.
-  const int32_t K = p.ksteps * kBK8x;
-  const int32_t a_extent = (K / p.a.kslice - 1) * p.a.slice + (BM - 1) * p.a.ld + p.a.kslice;
-  const int32_t b_extent = (int32_t)((K / p.b.kslice - 1) * p.b.slice +
+  const int32_t a_extent = (p.a_blocks - 1) * p.a.slice + (BM - 1) * p.a.ld + p.a.kslice;
+  const int32_t b_extent = (int32_t)((p.b_blocks - 1) * p.b.slice +
                                      (int64_t)(p.b.kslice - 1) * p.b.ld + BN);
   const char* A = reinterpret_cast<const char*>(p.A);
   const char* B = reinterpret_cast<const char*>(p.B);
@@ -2771,6 +2769,8 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
   gp.a = a;
   gp.b = b;
   gp.c = c;
+  gp.a_blocks = (int32_t)(p.K / a.kslice);
+  gp.b_blocks = (int32_t)(p.K / b.kslice);
   if (splits < 1 || (splits > 1 && (!remap || !ws))) return hipErrorInvalidValue;
   splits = effective_splits(p, splits);      // every K range non-empty
   // 128x192 tiles (the plan's choice, with operands that fit the kernel below)
