@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
 from dataclasses import dataclass
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libccl.so")
@@ -128,9 +129,13 @@ def _ptr(x) -> int:
 
 def _stream(s) -> int:
     if s is None:
-        import sys
         torch = sys.modules.get("torch")
         if torch is not None and torch.cuda.is_initialized():
+            # The current device's current stream as its raw handle, without
+            # building a torch.cuda.Stream: 0.5 against 3.4 us, of 8 us per call.
+            raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+            if raw is not None:
+                return raw(torch._C._cuda_getDevice())
             return int(torch.cuda.current_stream().cuda_stream)
         return 0
     if isinstance(s, int):
