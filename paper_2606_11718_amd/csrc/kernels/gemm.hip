@@ -84,6 +84,7 @@ struct GemmParams {
   int32_t ksteps_per_split;  // K steps of one split (= ksteps without split-K)
   int32_t round_fast;   // bf16: K blocks and split starts are 4-step aligned (rounds path)
   int32_t splits_total; // split-K ranges per tile (reduce kernel)
+  int32_t c_nt;         // a bf16 C is stored non-temporally (kernels that can)
   float* ws;            // split-K: fp32 partial tiles (null: write C directly)
   uint64_t* timeline;   // bf16 kernel: kTimelineWords per wave (null: not recorded)
 };
@@ -415,11 +416,9 @@ struct RowAccess {
 // in distinct banks. Then every wave copies BM / NW whole rows to C, 16
 // bytes per lane. SCALED: alpha != 1 (dequantised fp8 products; staging them
 // too took 4096x1536x2048 fp8 from 18.7 to 15.6 us, 8192x28672x8192 fp8 from
-// 1385 to 1349). NT marks the stores to C non-temporal (C is not read back
-// by the kernel); the 64-K-stage kernel uses it, where its Qwen3-shaped
-// launches (gate/up, dH) ran 1.5-3 % faster with it, measured alternating,
-// and so does the pipelined fp8 kernel.
-template <int BM, int BN, int NW, int TM, int TN, int WM, int WN, bool NT, bool SCALED>
+// 1385 to 1349). Stores to C are non-temporal never (NT = 0), where the launch
+// says so (1: p.c_nt) or always (2).
+template <int BM, int BN, int NW, int TM, int TN, int WM, int WN, int NT, bool SCALED>
 __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32x4 (&acc)[TM][TN],
                                                   char* lo, char* hi, int32_t pr, int32_t pc,
                                                   int32_t ti, int32_t tj, int wm, int wn, int wave,
@@ -466,7 +465,7 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
     const int r = row % HALF;
     const uint4 v = *reinterpret_cast<const uint4*>((row < HALF ? lo : hi) + r * ROWB + ((c ^ swz(r)) << 4));
     uint4* dst = reinterpret_cast<uint4*>(C + (int64_t)row * p.c.ld + c * 8);
-    if constexpr (NT)
+    if (NT == 2 || (NT == 1 && p.c_nt))
       __builtin_nontemporal_store(__builtin_bit_cast(i32x4, v), reinterpret_cast<i32x4*>(dst));
     else
       *dst = v;
@@ -576,7 +575,7 @@ __device__ __forceinline__ void store_tile_staged_f32(const GemmParams& p, const
 
 // The epilogue of the kernels with 16x16 MFMA tiles. lo and hi: the stage
 // arrays of A and B, idle after the K loop, with at least BUF bytes each.
-template <int BM, int BN, int NW, int TM, int TN, int WM, int WN, int BUF, bool NT>
+template <int BM, int BN, int NW, int TM, int TN, int WM, int WN, int BUF, int NT>
 __device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&acc)[TM][TN], char* lo,
                                            char* hi, int32_t pr, int32_t pc, int32_t ti, int32_t tj,
                                            int32_t split, int wm, int wn, int wave, int lane) {
@@ -948,7 +947,7 @@ __global__ void __launch_bounds__(128 * WGN, WGN / 2) gemm_kernel(GemmParams p) 
     tl_clk[1] = __builtin_amdgcn_s_memtime();
   }
   constexpr int kBuf = NS * T::A_BYTES < NS * T::B_BYTES ? NS * T::A_BYTES : NS * T::B_BYTES;
-  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, false>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, 0>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
                                                                     ti, tj, split, wm, wn, wave, lane);
   if (tl_on) record_timeline(p.timeline + ((int64_t)blockIdx.x * T::NW + wave) * kTimelineWords,
                              tl_rt, tl_clk, lane);
@@ -1263,7 +1262,7 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
     tl_clk[1] = __builtin_amdgcn_s_memtime();
   }
   constexpr int kBuf = NS * T::A_BYTES < NS * T::B_BYTES ? NS * T::A_BYTES : NS * T::B_BYTES;
-  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, true>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, BNT ? 2 : 1>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
                                                                     ti, tj, split, wm, wn, wave, lane);
   if (tl_on) record_timeline(p.timeline + ((int64_t)blockIdx.x * T::NW + wave) * kTimelineWords,
                              tl_rt, tl_clk, lane);
@@ -1601,7 +1600,7 @@ __global__ void __launch_bounds__(512, 2) gemm_a2_kernel(GemmParams p) {
     tl_clk[1] = __builtin_amdgcn_s_memtime();
   }
   constexpr int kBuf = T::NP * T::A2_BYTES < T::NSB * T::B_BYTES ? T::NP * T::A2_BYTES : T::NSB * T::B_BYTES;
-  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, false>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, 0>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
                                                                     ti, tj, split, wm, wn, wave, lane);
   if (tl_on) record_timeline(p.timeline + ((int64_t)blockIdx.x * T::NW + wave) * kTimelineWords,
                              tl_rt, tl_clk, lane);
@@ -2098,7 +2097,7 @@ __global__ void __launch_bounds__(128 * WGN, WGN / 2) gemm_fp8x_kernel(GemmParam
   }
 
   constexpr int kBuf = 2 * T::A_BYTES < 2 * T::B_BYTES ? 2 * T::A_BYTES : 2 * T::B_BYTES;
-  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, false>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, 0>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
                                                                     ti, tj, split, wm, wn, wave, lane);
 #endif
 }
@@ -2404,7 +2403,7 @@ __global__ void __launch_bounds__(512, 2) gemm_fp8p_kernel(GemmParams p) {
   // Non-temporal C stores: at the power limit the fp8 GEMMs ran 1-4 % faster
   // with them, at a 1 % higher clock (same box, alternating).
   constexpr int kBuf = T::NSA * T::A_BYTES < T::NSB * T::B_BYTES ? T::NSA * T::A_BYTES : T::NSB * T::B_BYTES;
-  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, true>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, 2>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
                                                                     ti, tj, split, wm, wn, wave, ln);
 #endif
 }
@@ -2667,7 +2666,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 4) gemm_fp8s_kerne
   int ln = lane;
   asm volatile("" : "+v"(ln));
   constexpr int kBuf = NS * T::A_BYTES < NS * T::B_BYTES ? NS * T::A_BYTES : NS * T::B_BYTES;
-  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, true>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, 1>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
                                                                     ti, tj, split, wm, wn, wave, ln);
 #endif
 }
@@ -2790,6 +2789,14 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
                      (splits == 1 || gp.ksteps_per_split % 4 == 0)) ? 1 : 0;
   }
   gp.splits_total = splits;
+  // Non-temporal stores of C: always in the pipelined fp8 kernel (1-4 % faster
+  // at the power limit) and where B streams, in the other 64- and 128-K-stage
+  // launches where C is above the Infinity Cache size. Elsewhere what reads C next (the unpack or
+  // the next GEMM) finds it in the cache: whole passes, 4096x1536x2048 44.9 ->
+  // 44.2 us, 4096x768x2048 30.2 -> 29.5, 256x512x256 10.7 -> 10.4. The decode
+  // FFN, whose launches stream their weights, takes 198.6 us with these, 200.1
+  // with plain ones.
+  gp.c_nt = p.M * p.N * 2 > kInfinityCacheBytes ? 1 : 0;
   gp.ws = splits > 1 ? ws : nullptr;
   gp.remap = remap ? 1 : 0;
   gp.grid_r = p.Gr;
