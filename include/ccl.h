@@ -351,7 +351,7 @@ const char* ccl_last_error(void);
  * is round-robin: wg mod 8) and which kernel output tile (tile_m, tile_n)
  * it computes, in units of the kernel tile (tile_rows x tile_cols, see
  * ccl_debug_gemm_config); -1 for both when the workgroup has no tile.
- * An unsplit bf16 launch may run 128x192 tiles instead, numbered the same way
+ * An unsplit bf16 launch may run 128x192 or 128x320 tiles instead, numbered the same way
  * over the same partitions (every tile on an XCD of the chiplet owning it, and
  * C the same bit for bit); the hooks, the timeline launch, the dispatch probe
  * and split-K describe and use the tile that ccl_debug_gemm_config names.
@@ -360,12 +360,13 @@ ccl_status ccl_debug_tile_of_wg(ccl_plan_t plan, int64_t wg, int* xcd, int64_t* 
                                 int64_t* tile_n);
 
 /* Test hook: the GEMM kernel tile and launch size the plan uses (but see
- * ccl_debug_tile_of_wg about 128x192 tiles). */
+ * ccl_debug_tile_of_wg about wider tiles). */
 ccl_status ccl_debug_gemm_config(ccl_plan_t plan, int* tile_rows, int* tile_cols,
                                  int64_t* workgroups);
 
 /*
- * Profiling hook: ccl_gemm (same kernel, but for 128x192 tiles; same C) on a
+ * Profiling hook: ccl_gemm (same kernel, but for tiles of 128x192 or 128x320;
+ * same C) on a
  * bf16 plan, with each
  * wave of every workgroup that has a tile recording its phase timeline.
  * `timeline` is a device buffer of at least workgroups * waves * 64 bytes

@@ -190,24 +190,37 @@ void choose_gemm_config(Plan* p) {
   g.fp8_pipe = p->ab_type == DT_FP8_E4M3 && g.waves == 8 && btm == 256 && btn == 256;
   if (const char* e = std::getenv("CCL_GEMM_FP8_PIPE"))
     if (std::atoi(e) == 0) g.fp8_pipe = false;
-  // 128x192 tiles for unsplit bf16 launches where their waves of 32 per XCD
-  // cost less than the tile above (same estimate). They fill partitions whose
-  // 128- or 256-wide tiles leave CUs idle: 4096x1536x2048 (2048x384 per XCD, 24
-  // tiles of 256x128, now 32) 33.9 -> 30.9 us, 256x16896x1280 (33 tiles of
-  // 128x128, now 22) 25.7 -> 18.0. The kernel has 64-K stages, K blocks of at
-  // least one, and 31-bit extents. CCL_GEMM_WIDE=0|1 forbids / takes them
-  // wherever they exist.
+  // 128x192 and 128x320 tiles for unsplit bf16 launches where their waves of
+  // 32 per XCD cost less than the tile above (same estimate). They fill
+  // partitions whose 128- or 256-wide tiles leave CUs idle: 4096x1536x2048
+  // (2048x384 per XCD, 24 tiles of 256x128, now 32) 33.9 -> 31.9 us,
+  // 256x16896x1280 (33 tiles of 128x128, now 22) 27.6 -> 17.9; 1920x5120x1792
+  // (75 tiles of 128x128, now 30 of 128x320) 52.5 -> 42.4, 2048x5120x2048 54 ->
+  // 44.5, 4096x2560x4096 90 -> 73. Efficiency 0.75: at 0.8, 4096x3072x2048 left
+  // its 24 tiles of 256x256 for 192-wide ones, 52.6 -> 54.8; 1024x5120x4096 (20
+  // tiles of 256x128) would take 57.1 instead of 47.2 with 320-wide ones. The
+  // kernel has 64-K stages, K blocks of at least one, and 31-bit extents.
+  // CCL_GEMM_WIDE=0|192|320 forbids them / takes that one wherever it exists.
   {
     const int64_t lim = ((int64_t)1 << 31) - 4096;
     const Layout &la = p->lay[OP_A], &lb = p->lay[OP_B];
-    const bool exists = p->ab_type == DT_BF16 && pr % 128 == 0 && pc % 192 == 0 && g.waves == 8 &&
+    const bool exists = p->ab_type == DT_BF16 && pr % 128 == 0 && g.waves == 8 &&
                         (g.stage_k == 64 || (btm == 256 && btn == 256 && !stage32)) && !forced &&
                         p->K / p->Gc >= 64 && p->K / p->Gr >= 64 &&
                         la.strip_stride_bytes * p->Gc + 512 * p->K < lim && lb.total_bytes + 512 < lim;
-    const int64_t tiles = (pr / 128) * (pc / 192);
-    const int64_t waves = ((tiles + g.xcd_per_chiplet - 1) / g.xcd_per_chiplet + 31) / 32;
-    g.wide = exists && (double)waves * 128 * 192 / 0.75 < best;
-    if (const char* e = std::getenv("CCL_GEMM_WIDE")) g.wide = exists && std::atoi(e) != 0;
+    const char* e = std::getenv("CCL_GEMM_WIDE");
+    const int forced_n = e ? std::atoi(e) : -1;
+    double t = best;
+    for (int n : {192, 320}) {
+      if (!exists || pc % n || (e && n != forced_n)) continue;
+      const int64_t tiles = (pr / 128) * (pc / n);
+      const int64_t waves = ((tiles + g.xcd_per_chiplet - 1) / g.xcd_per_chiplet + 31) / 32;
+      const double tn = (double)waves * 128 * n / 0.75;
+      if (e || tn < t) {
+        t = tn;
+        g.wide_n = n;
+      }
+    }
   }
   if (g.workgroups > 0x7fffffff) {
     g.why_unsupported = "launch too large";
@@ -436,8 +449,8 @@ TileMap tile_map(const Plan& p, int splits) {
 
 TileMap wide_tile_map(const Plan& p) {
   const GemmConfig& g = p.gemm;
-  const int64_t tm = p.part_rows() / 128, tn = p.part_cols() / 192;
-  // 8 tile rows per group: 32 resident tiles then cover 1024 x 768 of C
+  const int64_t tm = p.part_rows() / 128, tn = p.part_cols() / g.wide_n;
+  // 8 tile rows per group: 32 resident tiles of 128x192 then cover 1024 x 768 of C
   return make_tile_map(g.xcd_per_chiplet, p.Gc, (int32_t)tm, (int32_t)tn,
                  (int32_t)((tm * tn + g.xcd_per_chiplet - 1) / g.xcd_per_chiplet),
                  (int32_t)std::min<int64_t>(8, tm), 1);

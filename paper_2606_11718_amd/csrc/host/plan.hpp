@@ -51,7 +51,7 @@ struct GemmConfig {
   bool a_pairs = false;             // bf16 256x256: A staged in 64-K pairs (whole lines)
   bool fp8_pipe = false;            // fp8 256x256: fragment reads pipelined across steps
   bool stream_b = false;            // bf16 64-K stages: B read past the L2 (non-temporal)
-  bool wide = false;                // bf16, unsplit: 128x192 tiles instead (wide_tile_map)
+  int wide_n = 0;                   // bf16, unsplit: 128 x wide_n tiles instead (192 or 320; 0: none)
   bool supported = false;           // whether ccl_gemm can run this plan
   std::string why_unsupported;
 };
@@ -106,7 +106,7 @@ Traffic remote_bytes(const Plan& p, Placement pl, int flags);
 // Parameters of the workgroup -> tile map of the GEMM launch (splits > 1:
 // the split-K launch).
 TileMap tile_map(const Plan& p, int splits = 1);
-// The same for launches on 128x192 tiles (GemmConfig::wide).
+// The same for launches on 128 x wide_n tiles.
 TileMap wide_tile_map(const Plan& p);
 
 // GEMM main-loop steps over K (32 bf16 or 64 fp8 elements each).

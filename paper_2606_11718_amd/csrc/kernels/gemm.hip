@@ -109,9 +109,9 @@ __device__ __forceinline__ int swz_a16(int row) { return ((row >> 2) & 1) << 1; 
 // 2 * ((row & 3) | (row & 8) >> 1) sends these 16 (row, chunk) pairs to 16
 // distinct 16-byte bank slots.
 __device__ __forceinline__ int swz_b(int row) { return ((row & 3) << 1) | (((row >> 3) & 1) << 3); }
-// Rows of 24 chunks (BN = 192) already put odd rows 8 slots after even ones;
-// XOR-ing the chunk with 2 * ((row & 2) >> 1 | (row & 8) >> 2) stays within
-// groups of 8 chunks and sends the same 16 pairs to distinct slots.
+// Rows of 24 or 40 chunks (BN = 192, 320) already put odd rows 8 slots after
+// even ones; XOR-ing the chunk with 2 * ((row & 2) >> 1 | (row & 8) >> 2) stays
+// within groups of 8 chunks and sends the same 16 pairs to distinct slots.
 template <int BN>
 __device__ __forceinline__ int swz_bn(int row) {
   if constexpr (BN % 128 == 0) return swz_b(row);
@@ -999,14 +999,21 @@ struct Tile64 {
   static constexpr int NB = B_BYTES / (1024 * NW);     // B loads per wave per stage
   static constexpr int NL = NA + NB;
   // as many stages as 160 KiB holds, at most 4: 3 for 256x128 and
-  // 128x256, 4 for 128x192 and 128x128 (5 measured the same there)
-  static constexpr int NS = (160 * 1024) / (A_BYTES + B_BYTES) >= 4 ? 4 : 3;
+  // 128x256, 4 for 128x192 and 128x128 (5 measured the same there), 2 for
+  // 128x320
+  static constexpr int kFit = (160 * 1024) / (A_BYTES + B_BYTES);
+  static constexpr int NS = kFit >= 4 ? 4 : kFit;
+  // Stages loaded ahead of the one a step works on. With two stage buffers a
+  // step's loads go out behind its barrier, into the buffer it has just read,
+  // so that they have a whole step to land; otherwise before it.
+  static constexpr bool kLate = NS == 2;
+  static constexpr int AHEAD = kLate ? 2 : NS - 1;
   static_assert(BM * BN < 256 * 256, "256x256 tiles use the 32-K stages");
   static_assert(NA >= 1 && NB >= 1 && TN >= 1 && TM >= 1, "tile too small for the wave grid");
   static_assert(NS * (A_BYTES + B_BYTES) <= 160 * 1024, "LDS stages exceed 160 KiB");
-  static_assert((NS - 2) * NL <= 63, "the stage wait count exceeds vmcnt's range");
+  static_assert(NS >= 2 && (NS - 2) * NL <= 63, "the stage wait count exceeds vmcnt's range");
   static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "whole loads per wave");
-  static_assert(BN == 128 || BN == 192 || BN == 256, "B swizzle is defined for 16-, 24- and 32-chunk rows");
+  static_assert(BN == 128 || BN == 192 || BN == 256 || BN == 320, "B swizzle is defined for 16-, 24-, 32- and 40-chunk rows");
 };
 
 template <int BM, int BN, bool RAGGED, bool BNT>
@@ -1190,7 +1197,7 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
                   const char* nB, const StageSrc& d) __attribute__((always_inline)) {
     constexpr int kMfma = T::TM * T::TN;
     constexpr int kReads = T::TM + 2 * T::TN;
-    constexpr int kOps1 = kReads + T::NL;
+    constexpr int kOps1 = kReads + (T::kLate ? 0 : T::NL);
 #pragma unroll
     for (int i = 0; i < kMfma; ++i) {
       mfma_one(fa0, fb0, i / T::TN, i % T::TN);
@@ -1212,6 +1219,7 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
       mfma_one(fa1, fb1, i / T::TN, i % T::TN);
       if (i < T::TM) read_a(nA, fa0, 0, i);
       else if (i < kReads) read_b(nB, fb0, 0, i - T::TM);
+      if (T::kLate && i < T::NL) load_one(d, lA, lB, i);
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
@@ -1222,32 +1230,39 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  // Prologue: the first NS-1 stages in flight, then stage 0's sub-step 0.
+  // Prologue: the first AHEAD stages in flight, then stage 0's sub-step 0.
 #pragma unroll
-  for (int j = 0; j < NS - 1; ++j) {
+  for (int j = 0; j < T::AHEAD; ++j) {
     const StageSrc d = next_src(j, false);
 #pragma unroll
     for (int i = 0; i < T::NL; ++i) load_one(d, smA[j], smB[j], i);
   }
-  stage_barrier();
+  if constexpr (T::kLate) {
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(T::NL, 0));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  } else {
+    stage_barrier();
+  }
   if (tl_on) tl_rt[1] = __builtin_amdgcn_s_memrealtime();
 #pragma unroll
   for (int mt = 0; mt < T::TM; ++mt) read_a(smA[0], fa0, 0, mt);
 #pragma unroll
   for (int i = 0; i < 2 * T::TN; ++i) read_b(smB[0], fb0, 0, i);
   // Step s (phase ph = s % NS) works on stage s % NS, loads stage
-  // (s + NS - 1) % NS and reads stage (s + 1) % NS. live: the stage it loads
+  // (s + AHEAD) % NS and reads stage (s + 1) % NS. live: the stage it loads
   // is a whole one of the range.
   auto phase_step = [&](int ph, int32_t s, bool live) __attribute__((always_inline)) {
-    const StageSrc d = next_src(s + NS - 1, live);
-    step(smA[ph], smB[ph], smA[(ph + NS - 1) % NS], smB[(ph + NS - 1) % NS], smA[(ph + 1) % NS],
+    const StageSrc d = next_src(s + T::AHEAD, live);
+    step(smA[ph], smB[ph], smA[(ph + T::AHEAD) % NS], smB[(ph + T::AHEAD) % NS], smA[(ph + 1) % NS],
          smB[(ph + 1) % NS], d);
   };
   // Rounds of NS steps whose loads are all whole stages, branch-free; then
   // the rest, each behind a (uniform) bound check.
   const int32_t whole = RAGGED ? units / 2 : ksteps;
   int32_t s = 0;
-  for (; s + 2 * NS - 1 <= whole; s += NS) {
+  for (; s + NS + T::AHEAD <= whole; s += NS) {
 #pragma unroll
     for (int j = 0; j < NS; ++j) phase_step(j, s + j, true);
   }
@@ -1261,8 +1276,13 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
     tl_rt[2] = __builtin_amdgcn_s_memrealtime();
     tl_clk[1] = __builtin_amdgcn_s_memtime();
   }
-  constexpr int kBuf = NS * T::A_BYTES < NS * T::B_BYTES ? NS * T::A_BYTES : NS * T::B_BYTES;
-  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, BNT ? 2 : 1>(p, acc, &smA[0][0], &smB[0][0], pr, pc,
+  // C's halves are staged in A's and B's buffers, or in two halves of B's
+  // where A's are too small.
+  constexpr bool kInB = NS * T::A_BYTES < (BM / 2) * BN * 2;
+  constexpr int kBuf = kInB ? NS * T::B_BYTES / 2
+                            : NS * T::A_BYTES < NS * T::B_BYTES ? NS * T::A_BYTES : NS * T::B_BYTES;
+  char* const lo = kInB ? &smB[0][0] + kBuf : &smA[0][0];
+  epilogue16<BM, BN, T::NW, T::TM, T::TN, T::WM, T::WN, kBuf, BNT ? 2 : 1>(p, acc, lo, &smB[0][0], pr, pc,
                                                                     ti, tj, split, wm, wn, wave, lane);
   if (tl_on) record_timeline(p.timeline + ((int64_t)blockIdx.x * T::NW + wave) * kTimelineWords,
                              tl_rt, tl_clk, lane);
@@ -2772,8 +2792,9 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
   gp.b_blocks = (int32_t)(p.K / b.kslice);
   if (splits < 1 || (splits > 1 && (!remap || !ws))) return hipErrorInvalidValue;
   splits = effective_splits(p, splits);      // every K range non-empty
-  // 128x192 tiles (the plan's choice, with operands that fit the kernel below)
-  const bool wide = g.wide && remap && splits == 1 && !timeline;
+  // 128x192 or 128x320 tiles (the plan's choice, with operands that fit the
+  // kernel below)
+  const bool wide = g.wide_n && remap && splits == 1 && !timeline;
   gp.map = wide ? wide_tile_map(p) : tile_map(p, splits);
   const bool fp8 = p.ab_type == DT_FP8_E4M3;
   if (timeline && (fp8 || splits > 1)) return hipErrorInvalidValue;   // bf16 kernel only
@@ -2912,7 +2933,8 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
     else if (b_once) CCL_LAUNCH64_AS(BM_, BN_, true, true);          \
     else CCL_LAUNCH64_AS(BM_, BN_, true, false);                     \
   } while (0)
-      if (wide) CCL_LAUNCH64(128, 192);
+      if (wide && g.wide_n == 192) CCL_LAUNCH64(128, 192);
+      else if (wide) CCL_LAUNCH64(128, 320);
       else if (g.tile_m == 256 && g.tile_n == 128) CCL_LAUNCH64(256, 128);
       else if (g.tile_m == 128 && g.tile_n == 256) CCL_LAUNCH64(128, 256);
       else if (g.tile_m == 128 && g.tile_n == 128) CCL_LAUNCH64(128, 128);

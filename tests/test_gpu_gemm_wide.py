@@ -1,5 +1,5 @@
-"""bf16 GEMM on 128x192 tiles (CCL_GEMM_WIDE=1 takes them wherever they exist,
-0 the 128- and 256-wide ones). Plain C against the other tiles bit for bit (the
+"""bf16 GEMM on 128x192 and 128x320 tiles (CCL_GEMM_WIDE=192|320 takes them
+wherever they exist, 0 the 128- and 256-wide ones). Plain C against the other tiles bit for bit (the
 same MFMAs in the same order, at every K) on normal inputs; scaled, fp32 and
 read C against the oracle, exact on ternary inputs."""
 import numpy as np
@@ -15,7 +15,7 @@ from tests.test_gpu_splitk import BF16, FP32, _dev_bytes, _from_dev, _to_dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("G,Gr,M,N,K", [
+@pytest.mark.parametrize("wide,G,Gr,M,N,K", [("192",) + c for c in [
     (1, 1, 128, 384, 64), (1, 1, 128, 384, 64 * 3), (1, 1, 128, 384, 64 * 4), (1, 1, 128, 384, 64 * 7),
     (1, 1, 128, 384, 64 * 8), (1, 1, 128, 384, 64 * 13), (1, 1, 256, 768, 96), (1, 1, 128, 384, 32 * 15),
     (8, 2, 2048, 1536, 4 * 128),        # 32 tiles per XCD, whole K blocks
@@ -23,28 +23,34 @@ pytestmark = pytest.mark.gpu
     (8, 8, 2048, 384, 8 * 96),          # B: blocks of 3 steps
     (8, 1, 128, 8 * 1152, 8 * 64),      # one tile row, 6 tile columns
     (4, 2, 2560, 768, 256),             # 10 tile rows: a whole raster group and a short one
-])
-def test_equals_other_tiles(G, Gr, M, N, K, monkeypatch):
+]] + [("320",) + c for c in [
+    (1, 1, 128, 640, 64), (1, 1, 128, 640, 64 * 2), (1, 1, 128, 640, 64 * 3), (1, 1, 128, 640, 64 * 4),
+    (1, 1, 128, 640, 64 * 5), (1, 1, 128, 640, 64 * 8), (1, 1, 256, 640, 96), (1, 1, 128, 640, 32 * 15),
+    (8, 1, 1920, 5120, 1792),           # 30 tiles per XCD, K blocks of 7 steps
+    (8, 2, 512, 2560, 4 * 160), (8, 8, 2048, 640, 8 * 96), (8, 1, 128, 8 * 1280, 8 * 64),
+]])
+def test_equals_other_tiles(wide, G, Gr, M, N, K, monkeypatch):
     A = W.draw_array(9100 + K, M, K, "normal", 1.0)
     B = W.draw_array(9101 + K, K, N, "normal", 0.05)
     got = {}
-    for wide in ("0", "1"):
-        monkeypatch.setenv("CCL_GEMM_WIDE", wide)
-        got[wide] = _gemm(A, B, M, N, K, G, Gr)
-    assert np.array_equal(got["0"], got["1"])
-    assert OG.within_tolerance(OG.errors(OG.decode_bf16(got["1"]), OG.gemm_fp64(A, B)))
+    for n in ("0", wide):
+        monkeypatch.setenv("CCL_GEMM_WIDE", n)
+        got[n] = _gemm(A, B, M, N, K, G, Gr)
+    assert np.array_equal(got["0"], got[wide])
+    assert OG.within_tolerance(OG.errors(OG.decode_bf16(got[wide]), OG.gemm_fp64(A, B)))
 
 
+@pytest.mark.parametrize("wide", ["192", "320"])
 @pytest.mark.parametrize("c,alpha,beta", [(BF16, -0.5, 0.0), (BF16, 1.0, 2.0), (FP32, 1.0, 0.0),
                                           (FP32, 2.0, 0.0), (FP32, 0.5, -1.0)])
-def test_epilogues(c, alpha, beta, monkeypatch):
-    monkeypatch.setenv("CCL_GEMM_WIDE", "1")
-    M, N, K, G, Gr = 512, 1536, 512, 4, 2
+def test_epilogues(wide, c, alpha, beta, monkeypatch):
+    monkeypatch.setenv("CCL_GEMM_WIDE", wide)
+    M, N, K, G, Gr = 512, 4 * int(wide) * 2, 512, 4, 2
     A, B = W.draw_array(9200, M, K, "ternary"), W.draw_array(9201, K, N, "ternary")
     C0 = W.draw_array(9202, M, N, "ternary")
     plan = ccl.ccl_plan_typed(M, N, K, G, Gr, 4096, BF16, c)
     gr, gc = ccl.ccl_plan_grid(plan)
-    print(f"wide epilogue c={c} alpha={alpha} beta={beta}", flush=True)
+    print(f"wide epilogue {wide} c={c} alpha={alpha} beta={beta}", flush=True)
     Ac, Bc = (_dev_bytes(ccl.ccl_plan_layout(plan, op).total_bytes) for op in (ccl.CCL_A, ccl.CCL_B))
     ccl.ccl_pack(plan, ccl.CCL_A, _to_dev(A), K, 0, Ac)
     ccl.ccl_pack(plan, ccl.CCL_B, _to_dev(B), N, 0, Bc)
@@ -61,10 +67,11 @@ def test_epilogues(c, alpha, beta, monkeypatch):
         assert np.array_equal(OG.decode_bf16(got), OG.decode_bf16(W.round_to_bf16_bits(want)))
 
 
-def test_rowmajor(monkeypatch):
+@pytest.mark.parametrize("wide", ["192", "320"])
+def test_rowmajor(wide, monkeypatch):
     """Row-major operands under the XCD-aware map (one K block)."""
-    monkeypatch.setenv("CCL_GEMM_WIDE", "1")
-    M, N, K = 512, 1536, 320
+    monkeypatch.setenv("CCL_GEMM_WIDE", wide)
+    M, N, K = 512, 4 * int(wide) * 2, 320
     A, B = W.draw_array(9300, M, K, "ternary"), W.draw_array(9301, K, N, "ternary")
     plan = ccl.ccl_plan(M, N, K, 4, 2, 4096)
     C = _dev_bytes(M * N * 2)

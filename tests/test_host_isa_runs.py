@@ -9,7 +9,8 @@ import pytest
 from tests.test_host_isa import _body, _lds_offset, asm  # noqa: F401
 
 
-@pytest.mark.parametrize("bm,bn,lengths", [(256, 128, {2, 4}), (128, 256, {2, 4}), (128, 128, {2}), (128, 192, {2, 3})])
+@pytest.mark.parametrize("bm,bn,lengths", [(256, 128, {2, 4}), (128, 256, {2, 4}), (128, 128, {2}), (128, 192, {2, 3}),
+                                           (128, 320, {1, 2, 4})])
 @pytest.mark.parametrize("ragged", [0, 1])
 @pytest.mark.parametrize("nt", [0, 1])
 def test_k64_runs(asm, bm, bn, lengths, ragged, nt):  # noqa: F811
