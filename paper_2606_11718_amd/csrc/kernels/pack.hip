@@ -135,14 +135,13 @@ __global__ void __launch_bounds__(256) copy_kernel(PackArgs a) {
 // Measured on the 134 MB pack of X from HBM: 5.39-5.41 TB/s against
 // 5.05-5.14 for copy_kernel; inside the FFN step 46 us against 54 us. U as
 // in copy_kernel.
-template <typename U, bool UNPACK, bool EXACT>
+template <typename U, bool UNPACK, bool EXACT, int UNROLL>
 __global__ void __launch_bounds__(256) copy_stream_kernel(PackArgs a) {
   const int32_t b = blockIdx.y;                      // strip / chiplet
   const int64_t pr = b / a.grid_c, pc = b % a.grid_c;
   const int64_t rm_base = pr * a.hr * a.ld_bytes + pc * a.row_bytes;
   const char* src = UNPACK ? a.ccl + (int64_t)b * a.strip : a.rm + rm_base;
   char* dst = UNPACK ? a.rm_out + rm_base : a.ccl_out + (int64_t)b * a.strip;
-  constexpr int UNROLL = 4;
   constexpr uint32_t kRound = 256u * UNROLL;         // units per workgroup round
   const uint32_t stride = gridDim.x * kRound;
   auto load = [&](uint32_t base, U* v) {
@@ -304,16 +303,26 @@ typedef uint8_t u8_any __attribute__((aligned(1)));
 typedef uint16_t u16_any __attribute__((aligned(1)));
 typedef uint32_t u32_any __attribute__((aligned(1)));
 
+template <typename U, bool UNPACK, int UNROLL>
+void copy_stream_launch(dim3 grid, const PackArgs& a, bool exact, hipStream_t stream) {
+  if (exact)
+    hipLaunchKernelGGL((copy_stream_kernel<U, UNPACK, true, UNROLL>), grid, dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL((copy_stream_kernel<U, UNPACK, false, UNROLL>), grid, dim3(256), 0, stream, a);
+}
+
 template <typename U, bool UNPACK>
-void copy_launch_as(dim3 grid, const PackArgs& a, bool big, bool exact, hipStream_t stream) {
+void copy_launch_as(dim3 grid, const PackArgs& a, bool big, int unroll, bool exact, hipStream_t stream) {
   if (big && exact)
     hipLaunchKernelGGL((copy_kernel<U, UNPACK, true>), grid, dim3(256), 0, stream, a);
   else if (big)
     hipLaunchKernelGGL((copy_kernel<U, UNPACK, false>), grid, dim3(256), 0, stream, a);
-  else if (exact)
-    hipLaunchKernelGGL((copy_stream_kernel<U, UNPACK, true>), grid, dim3(256), 0, stream, a);
+  else if (unroll == 1)
+    copy_stream_launch<U, UNPACK, 1>(grid, a, exact, stream);
+  else if (unroll == 2)
+    copy_stream_launch<U, UNPACK, 2>(grid, a, exact, stream);
   else
-    hipLaunchKernelGGL((copy_stream_kernel<U, UNPACK, false>), grid, dim3(256), 0, stream, a);
+    copy_stream_launch<U, UNPACK, 4>(grid, a, exact, stream);
 }
 
 // Units of type U: fills in the unit counts and picks the kernel by size.
@@ -324,14 +333,20 @@ void copy_launch(const Layout& L, PackArgs a, bool unpack, hipStream_t stream) {
   a.units_per_block = (uint32_t)(L.block_rows * per_row);
   a.units_per_row = make_div((uint32_t)per_row);
   const unsigned strips = (unsigned)(L.grid_r * L.grid_c);
-  dim3 grid(grid_x_for(a.units_per_block, 4), strips);
   // above the cache size both sides stream (measured: +10 % on 470 MB);
   // below it a resident grid: kResidentWgs workgroups in all, at most one
-  // round each per strip
+  // round each per strip. Where that grid holds the whole tensor at one or two
+  // units per thread, threads take that many instead of four: such copies wait
+  // on latency, and four units per thread left half or more of the CUs without
+  // a workgroup. Whole passes of pack, GEMM and unpack: 256x512x256 10.4 -> 9.5
+  // us, 4096x1536x2048 44.1 -> 42.9, in fp8 32.6 -> 30.8, 4096x768x2048 30.3 -> 29.9.
   const bool big = L.rows * L.cols * L.elem_bytes > kInfinityCacheBytes;
-  if (!big) grid.x = std::min(std::max(1u, kResidentWgs / strips), grid.x);
-  if (unpack) copy_launch_as<U, true>(grid, a, big, exact, stream);
-  else copy_launch_as<U, false>(grid, a, big, exact, stream);
+  const unsigned resident = std::max(1u, kResidentWgs / strips);
+  const int unroll = big ? 4 : a.units_per_block <= resident * 256ull ? 1 : a.units_per_block <= resident * 512ull ? 2 : 4;
+  dim3 grid(grid_x_for(a.units_per_block, unroll), strips);
+  if (!big) grid.x = std::min(resident, grid.x);
+  if (unpack) copy_launch_as<U, true>(grid, a, big, unroll, exact, stream);
+  else copy_launch_as<U, false>(grid, a, big, unroll, exact, stream);
 }
 
 // aligned: src, ld, dst and strips are multiples of 16 bytes.
