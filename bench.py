@@ -493,8 +493,8 @@ def _time_ccl_and_vendor(name, M, N, K, G, grid_rows, reps):
         return e0.elapsed_time(e1) / reps
 
     ms = timed(lambda: ccl.ccl_gemm(plan, A, B, C, st))
-    tm, tn, _ = ccl.ccl_debug_gemm_config(plan)
-    rec = {"MNK": f"{M}x{N}x{K}", "grid": f"{gr}x{gc}", "tile": f"{tm}x{tn}",
+    run = ccl.ccl_debug_launch(plan)
+    rec = {"MNK": f"{M}x{N}x{K}", "grid": f"{gr}x{gc}", "tile": f"{run.tile_rows}x{run.tile_cols}",
            "ms": round(ms, 4), "tflops": round(flops / ms / 1e9, 1)}
     # the vendor library on the same shape, box and power limit:
     # torch.matmul of contiguous row-major bf16 operands
@@ -539,7 +539,7 @@ def workload_gemms(reps: int):
 
 def gemm_timeline(reps: int):
     """Phase timeline of the bf16 GEMM on every workload shape and the Llama
-    forward pair (ccl_debug_gemm_timeline: per-wave real-time counter at
+    forward pair (ccl_debug_launch_timeline: per-wave real-time counter at
     start, after the prologue, after the K loop, after the stores' issue;
     shader clock over the loop). reps launches back to back after 3 warm-up
     launches; medians over those launches of per-launch figures."""
@@ -553,7 +553,8 @@ def gemm_timeline(reps: int):
     for name in names:
         _, g = W.gemm_by_name(name)
         plan = ccl.ccl_plan(g.M, g.N, g.K, g.chiplets, g.grids[0], 4096)
-        tm, tn, wgs = ccl.ccl_debug_gemm_config(plan)
+        run = ccl.ccl_debug_launch(plan)
+        tm, tn, wgs = run.tile_rows, run.tile_cols, run.workgroups
         lay = [ccl.ccl_plan_layout(plan, op) for op in (ccl.CCL_A, ccl.CCL_B, ccl.CCL_C)]
         gen = torch.Generator(device="cuda").manual_seed(5)
         A = torch.randn(lay[0].total_bytes // 2, device="cuda", generator=gen).to(torch.bfloat16)
@@ -565,7 +566,7 @@ def gemm_timeline(reps: int):
         for _ in range(3):
             ccl.ccl_gemm(plan, A, B, C, st)
         for r in range(reps):
-            ccl.ccl_debug_gemm_timeline(plan, A, B, C, tl[r * words:], words * 8, st)
+            ccl.ccl_debug_launch_timeline(plan, A, B, C, tl[r * words:], words * 8, st)
         torch.cuda.synchronize()
         rec = tl.cpu().numpy().reshape(reps, wgs, 8, 8)
         live = rec[:, :, 0, 0] > 0

@@ -347,28 +347,50 @@ const char* ccl_status_string(ccl_status status);
 const char* ccl_last_error(void);
 
 /*
- * Test hook: which XCD runs workgroup `wg` of ccl_gemm's launch (dispatch
- * is round-robin: wg mod 8) and which kernel output tile (tile_m, tile_n)
- * it computes, in units of the kernel tile (tile_rows x tile_cols, see
- * ccl_debug_gemm_config); -1 for both when the workgroup has no tile.
- * An unsplit bf16 launch may run 128x192 or 128x320 tiles instead, numbered the same way
- * over the same partitions (every tile on an XCD of the chiplet owning it, and
- * C the same bit for bit); the hooks, the timeline launch, the dispatch probe
- * and split-K describe and use the tile that ccl_debug_gemm_config names.
+ * Test hooks. A plan has one GEMM kernel tile, which split-K cuts K for and
+ * whose partials fill the workspace: ccl_debug_gemm_config gives it, with the
+ * workgroups of an unsplit launch on it, and ccl_debug_tile_of_wg the map of
+ * that launch. An unsplit bf16 ccl_gemm may run 128x192 or 128x320 tiles
+ * instead (C is the same bit for bit); what it does launch is given by the
+ * ccl_debug_launch hooks. Both maps put every tile on an XCD of the chiplet
+ * owning it.
  */
+
+/* Which XCD runs workgroup `wg` (dispatch is round-robin: wg mod 8) and which
+ * kernel output tile (tile_m, tile_n) it computes, in units of the kernel
+ * tile; -1 for both when the workgroup has no tile. */
 ccl_status ccl_debug_tile_of_wg(ccl_plan_t plan, int64_t wg, int* xcd, int64_t* tile_m,
                                 int64_t* tile_n);
 
-/* Test hook: the GEMM kernel tile and launch size the plan uses (but see
- * ccl_debug_tile_of_wg about wider tiles). */
+/* The plan's GEMM kernel tile and the workgroups of an unsplit launch on it. */
 ccl_status ccl_debug_gemm_config(ccl_plan_t plan, int* tile_rows, int* tile_cols,
                                  int64_t* workgroups);
 
+/* What one GEMM call on the plan launches: the kernel of its main launch, its
+ * tile and workgroups, and which of the kernel's forms runs. */
+typedef struct ccl_launch {
+  char kernel[32];      /* name of the kernel template */
+  int64_t workgroups;
+  int tile_rows, tile_cols;
+  int waves;            /* per workgroup */
+  int k_ranges;         /* split-K ranges (1: none) */
+  int ragged;           /* 64-K stages that may straddle K blocks */
+  int stream_b;         /* B read past the L2 */
+} ccl_launch;
+
+/* The launch of ccl_gemm / ccl_gemm_scaled (splits 1, operands 0), of
+ * ccl_gemm_splitk with `splits` K ranges (1..16, operands 0), or of
+ * ccl_gemm_rowmajor with remap 0 or 1 (splits 1, operands 1 or 2). Errors:
+ * CCL_ERR_INVALID_ARG; CCL_ERR_UNSUPPORTED as ccl_gemm. */
+ccl_status ccl_debug_launch(ccl_plan_t plan, int splits, int operands, ccl_launch* out);
+
+/* ccl_debug_tile_of_wg for ccl_gemm's own launch. */
+ccl_status ccl_debug_launch_tile_of_wg(ccl_plan_t plan, int64_t wg, int* xcd, int64_t* tile_m,
+                                       int64_t* tile_n);
+
 /*
- * Profiling hook: ccl_gemm (same kernel, but for tiles of 128x192 or 128x320;
- * same C) on a
- * bf16 plan, with each
- * wave of every workgroup that has a tile recording its phase timeline.
+ * Profiling hook: a bf16 GEMM on the plan's tile (the C of ccl_gemm), with
+ * each wave of every workgroup that has a tile recording its phase timeline.
  * `timeline` is a device buffer of at least workgroups * waves * 64 bytes
  * (ccl_debug_gemm_config gives the workgroups; waves per workgroup is 8,
  * or 4 under CCL_GEMM_WAVES=4), 16-byte aligned, owned by the caller.
@@ -386,13 +408,22 @@ ccl_status ccl_debug_gemm_timeline(ccl_plan_t plan, const void* A_ccl, const voi
                                    void* C_ccl, uint64_t* timeline, int64_t timeline_bytes,
                                    void* stream);
 
+/* The same for ccl_gemm's own launch (workgroups and waves as
+ * ccl_debug_launch gives them). */
+ccl_status ccl_debug_launch_timeline(ccl_plan_t plan, const void* A_ccl, const void* B_ccl,
+                                     void* C_ccl, uint64_t* timeline, int64_t timeline_bytes,
+                                     void* stream);
+
 /*
- * Test hook: launch a kernel with ccl_gemm's grid in which every workgroup
- * records, at out[4*wg .. 4*wg+3], the hardware XCD id it ran on, its tile
- * (tile_m, tile_n; -1 if none) and the chiplet owning that tile. `out` is a
- * device buffer of 4 * workgroups int32. Errors as ccl_gemm.
+ * Test hook: launch a kernel with the grid of a GEMM on the plan's tile, in
+ * which every workgroup records, at out[4*wg .. 4*wg+3], the hardware XCD id
+ * it ran on, its tile (tile_m, tile_n; -1 if none) and the chiplet owning that
+ * tile. `out` is a device buffer of 4 * workgroups int32. Errors as ccl_gemm.
  */
 ccl_status ccl_debug_dispatch(ccl_plan_t plan, int32_t* out, void* stream);
+
+/* The same with the grid and map of ccl_gemm's own launch. */
+ccl_status ccl_debug_launch_dispatch(ccl_plan_t plan, int32_t* out, void* stream);
 
 #ifdef __cplusplus
 }

@@ -29,7 +29,8 @@ EXPORTED = ("ccl_plan", "ccl_plan_typed", "ccl_plan_destroy", "ccl_plan_grid", "
             "ccl_pack", "ccl_unpack", "ccl_gemm", "ccl_gemm_scaled", "ccl_gemm_splitk_workspace",
             "ccl_gemm_splitk", "ccl_gemm_splitk_noalloc", "ccl_gemm_rowmajor", "ccl_remote_bytes", "ccl_remote_bytes_l2", "ccl_status_string", "ccl_last_error",
             "ccl_debug_tile_of_wg", "ccl_debug_gemm_config", "ccl_debug_dispatch",
-            "ccl_debug_gemm_timeline")
+            "ccl_debug_gemm_timeline", "ccl_debug_launch", "ccl_debug_launch_tile_of_wg",
+            "ccl_debug_launch_dispatch", "ccl_debug_launch_timeline")
 
 
 class CCLError(RuntimeError):
@@ -61,6 +62,11 @@ class _L2Traffic(ctypes.Structure):
     _fields_ = [("accesses", ctypes.c_uint64 * 2), ("misses", ctypes.c_uint64 * 2),
                 ("remote", ctypes.c_uint64 * 3),
                 ("remote_per_chiplet", ctypes.c_uint64 * MAX_CHIPLETS), ("chiplets", ctypes.c_int32)]
+
+
+class _Launch(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_char * 32), ("workgroups", ctypes.c_int64)] + \
+               [(n, ctypes.c_int) for n in ("tile_rows", "tile_cols", "waves", "k_ranges", "ragged", "stream_b")]
 
 
 _lib = None
@@ -101,6 +107,10 @@ def library() -> ctypes.CDLL:
         "ccl_debug_gemm_config": [vp, ctypes.POINTER(i32), ctypes.POINTER(i32), ctypes.POINTER(i64)],
         "ccl_debug_dispatch": [vp, vp, vp],
         "ccl_debug_gemm_timeline": [vp, vp, vp, vp, vp, i64, vp],
+        "ccl_debug_launch": [vp, i32, i32, ctypes.POINTER(_Launch)],
+        "ccl_debug_launch_tile_of_wg": [vp, i64, ctypes.POINTER(i32), ctypes.POINTER(i64), ctypes.POINTER(i64)],
+        "ccl_debug_launch_dispatch": [vp, vp, vp],
+        "ccl_debug_launch_timeline": [vp, vp, vp, vp, vp, i64, vp],
     }
     for name, args in sig.items():
         f = getattr(lib, name)
@@ -303,3 +313,38 @@ def ccl_debug_gemm_timeline(plan: Plan, A_ccl, B_ccl, C_ccl, timeline, timeline_
                             stream=None) -> None:
     _check(library().ccl_debug_gemm_timeline(plan, _ptr(A_ccl), _ptr(B_ccl), _ptr(C_ccl),
                                              _ptr(timeline), timeline_bytes, _stream(stream)))
+
+
+@dataclass
+class Launch:
+    kernel: str
+    workgroups: int
+    tile_rows: int
+    tile_cols: int
+    waves: int
+    k_ranges: int
+    ragged: bool
+    stream_b: bool
+
+
+def ccl_debug_launch(plan: Plan, splits: int = 1, operands: int = 0) -> Launch:
+    out = _Launch()
+    _check(library().ccl_debug_launch(plan, splits, operands, ctypes.byref(out)))
+    return Launch(out.kernel.decode(), out.workgroups, out.tile_rows, out.tile_cols, out.waves, out.k_ranges,
+                  bool(out.ragged), bool(out.stream_b))
+
+
+def ccl_debug_launch_tile_of_wg(plan: Plan, wg: int) -> tuple[int, int, int]:
+    x, tm, tn = ctypes.c_int(), ctypes.c_int64(), ctypes.c_int64()
+    _check(library().ccl_debug_launch_tile_of_wg(plan, wg, ctypes.byref(x), ctypes.byref(tm), ctypes.byref(tn)))
+    return x.value, tm.value, tn.value
+
+
+def ccl_debug_launch_dispatch(plan: Plan, out, stream=None) -> None:
+    _check(library().ccl_debug_launch_dispatch(plan, _ptr(out), _stream(stream)))
+
+
+def ccl_debug_launch_timeline(plan: Plan, A_ccl, B_ccl, C_ccl, timeline, timeline_bytes: int,
+                              stream=None) -> None:
+    _check(library().ccl_debug_launch_timeline(plan, _ptr(A_ccl), _ptr(B_ccl), _ptr(C_ccl),
+                                               _ptr(timeline), timeline_bytes, _stream(stream)))

@@ -63,28 +63,6 @@ ccl_status hip_status(hipError_t e, const char* what) {
 
 bool valid_op(ccl_operand op) { return op == CCL_A || op == CCL_B || op == CCL_C; }
 
-// CCL addressing of the GEMM operands (in elements of each operand's type).
-void ccl_addressing(const ccl::Plan& p, ccl::OperandAddr* a, ccl::OperandAddr* b,
-                    ccl::OperandAddr* c) {
-  const int64_t sa = p.lay[ccl::OP_A].strip_stride_bytes / p.lay[ccl::OP_A].elem_bytes;
-  const int64_t sb = p.lay[ccl::OP_B].strip_stride_bytes / p.lay[ccl::OP_B].elem_bytes;
-  const int64_t sc = p.lay[ccl::OP_C].strip_stride_bytes / p.lay[ccl::OP_C].elem_bytes;
-  // A block (pr, kc) = pr*Gc + kc; B block (kr, pc) = kr*Gc + pc; C block (pr, pc).
-  *a = {p.Gc * sa, sa, (int32_t)(p.K / p.Gc), (int32_t)(p.K / p.Gc)};
-  *b = {sb, p.Gc * sb, (int32_t)(p.N / p.Gc), (int32_t)(p.K / p.Gr)};
-  *c = {p.Gc * sc, sc, (int32_t)(p.N / p.Gc), 0};
-}
-
-// Row-major addressing of the same operands (Eq. 2): A (M x K), B (K x N),
-// C (M x N), leading dimensions K, N, N.
-void rowmajor_addressing(const ccl::Plan& p, ccl::OperandAddr* a, ccl::OperandAddr* b,
-                         ccl::OperandAddr* c) {
-  const int64_t hr = p.M / p.Gr;
-  *a = {hr * p.K, p.K / p.Gc, (int32_t)p.K, (int32_t)(p.K / p.Gc)};
-  *b = {p.N / p.Gc, (p.K / p.Gr) * p.N, (int32_t)p.N, (int32_t)(p.K / p.Gr)};
-  *c = {hr * p.N, p.N / p.Gc, (int32_t)p.N, 0};
-}
-
 // Whether every element the GEMM kernel can touch through this addressing
 // lies inside buffers of a_bytes, b_bytes and c_bytes (the kernel's own
 // formulas: A at pr*part + kslice_index*slice + row*ld + k, B at
@@ -207,7 +185,7 @@ ccl_status ccl_gemm_scaled(ccl_plan_t plan, float alpha, const void* A_ccl, cons
   const ccl::Plan& p = plan->plan;
   if (!p.gemm.supported) return fail(CCL_ERR_UNSUPPORTED, p.gemm.why_unsupported);
   ccl::OperandAddr a, b, c;
-  ccl_addressing(p, &a, &b, &c);
+  ccl::ccl_addressing(p, &a, &b, &c);
   if (!offsets_fit(p, a, b)) return fail(CCL_ERR_UNSUPPORTED, "CCL blocks too wide for 32-bit in-tile offsets");
   if (!addressing_in_bounds(p, a, b, c, p.lay[ccl::OP_A].total_bytes, p.lay[ccl::OP_B].total_bytes,
                             p.lay[ccl::OP_C].total_bytes))
@@ -257,7 +235,7 @@ ccl_status ccl_gemm_splitk(ccl_plan_t plan, float alpha, const void* A_ccl, cons
   if (!aligned16(A_ccl) || !aligned16(B_ccl) || !aligned16(C_ccl) || !aligned16(workspace))
     return fail(CCL_ERR_MISALIGNED_POINTER, "A, B, C and the workspace must be 16-byte aligned");
   ccl::OperandAddr a, b, c;
-  ccl_addressing(p, &a, &b, &c);
+  ccl::ccl_addressing(p, &a, &b, &c);
   if (!offsets_fit(p, a, b)) return fail(CCL_ERR_UNSUPPORTED, "CCL blocks too wide for 32-bit in-tile offsets");
   if (!addressing_in_bounds(p, a, b, c, p.lay[ccl::OP_A].total_bytes, p.lay[ccl::OP_B].total_bytes,
                             p.lay[ccl::OP_C].total_bytes))
@@ -309,7 +287,7 @@ ccl_status ccl_gemm_rowmajor(ccl_plan_t plan, const void* A, const void* B, void
   const ccl::Plan& p = plan->plan;
   if (!p.gemm.supported) return fail(CCL_ERR_UNSUPPORTED, p.gemm.why_unsupported);
   ccl::OperandAddr a, b, c;
-  rowmajor_addressing(p, &a, &b, &c);
+  ccl::rowmajor_addressing(p, &a, &b, &c);
   if (!offsets_fit(p, a, b)) return fail(CCL_ERR_UNSUPPORTED, "rows too long for 32-bit in-tile offsets");
   if (!addressing_in_bounds(p, a, b, c, p.M * p.K * p.lay[ccl::OP_A].elem_bytes,
                             p.K * p.N * p.lay[ccl::OP_B].elem_bytes,
@@ -407,23 +385,57 @@ ccl_status ccl_debug_gemm_config(ccl_plan_t plan, int* tile_rows, int* tile_cols
   return ok();
 }
 
-ccl_status ccl_debug_gemm_timeline(ccl_plan_t plan, const void* A_ccl, const void* B_ccl,
-                                   void* C_ccl, uint64_t* timeline, int64_t timeline_bytes,
-                                   void* stream) {
-  if (!plan || !A_ccl || !B_ccl || !C_ccl || !timeline)
-    return fail(CCL_ERR_INVALID_ARG, "NULL argument");
+ccl_status ccl_debug_launch(ccl_plan_t plan, int splits, int operands, ccl_launch* out) {
+  if (!plan || !out) return fail(CCL_ERR_INVALID_ARG, "NULL argument");
   const ccl::Plan& p = plan->plan;
   if (!p.gemm.supported) return fail(CCL_ERR_UNSUPPORTED, p.gemm.why_unsupported);
+  if (splits < 1 || splits > ccl::kMaxSplits || operands < 0 || operands > 2 || (operands && splits > 1))
+    return fail(CCL_ERR_INVALID_ARG, "splits must be in 1..16 (1 for row-major operands), operands in 0..2");
+  ccl::OperandAddr a, b, c;
+  if (operands) ccl::rowmajor_addressing(p, &a, &b, &c);
+  else ccl::ccl_addressing(p, &a, &b, &c);
+  const ccl::GemmForm f = ccl::gemm_form(p, a, b, operands != 1, splits);
+  std::memset(out, 0, sizeof(*out));
+  std::strncpy(out->kernel, ccl::kernel_name(f.kernel), sizeof(out->kernel) - 1);
+  out->workgroups = f.workgroups;
+  out->tile_rows = f.tile_m;
+  out->tile_cols = f.tile_n;
+  out->waves = f.waves;
+  out->k_ranges = f.splits;
+  out->ragged = f.ragged;
+  out->stream_b = f.stream_b;
+  return ok();
+}
+
+ccl_status ccl_debug_launch_tile_of_wg(ccl_plan_t plan, int64_t wg, int* xcd, int64_t* tile_m,
+                                       int64_t* tile_n) {
+  if (!plan || !xcd || !tile_m || !tile_n) return fail(CCL_ERR_INVALID_ARG, "NULL argument");
+  if (!plan->plan.gemm.supported) return fail(CCL_ERR_UNSUPPORTED, plan->plan.gemm.why_unsupported);
+  ccl::launch_tile_of_wg(plan->plan, wg, xcd, tile_m, tile_n);
+  return ok();
+}
+
+// The plan without its wider tiles: an unsplit launch then runs the plan's tile.
+static ccl::Plan on_plan_tile(const ccl::Plan& p) {
+  ccl::Plan q = p;
+  q.gemm.wide_n = 0;
+  return q;
+}
+
+// A timeline of p's unsplit launch.
+static ccl_status timeline_launch(const ccl::Plan& p, const void* A_ccl, const void* B_ccl, void* C_ccl,
+                                  uint64_t* timeline, int64_t timeline_bytes, void* stream) {
   if (p.ab_type != ccl::DT_BF16)
-    return fail(CCL_ERR_UNSUPPORTED, "the timeline is recorded by the bf16 GEMM kernel only");
-  const int64_t need = p.gemm.workgroups * p.gemm.waves * ccl::kTimelineWords * 8;
+    return fail(CCL_ERR_UNSUPPORTED, "the timeline is recorded by the bf16 GEMM kernels only");
+  ccl::OperandAddr a, b, c;
+  ccl::ccl_addressing(p, &a, &b, &c);
+  const ccl::GemmForm f = ccl::gemm_form(p, a, b, true, 1);
+  const int64_t need = f.workgroups * f.waves * ccl::kTimelineWords * 8;
   if (timeline_bytes < need)
     return fail(CCL_ERR_INVALID_ARG, "timeline smaller than workgroups * waves * 64 bytes (" +
                                          std::to_string(need) + ")");
   if (!aligned16(A_ccl) || !aligned16(B_ccl) || !aligned16(C_ccl) || !aligned16(timeline))
     return fail(CCL_ERR_MISALIGNED_POINTER, "A, B, C and the timeline must be 16-byte aligned");
-  ccl::OperandAddr a, b, c;
-  ccl_addressing(p, &a, &b, &c);
   if (!offsets_fit(p, a, b)) return fail(CCL_ERR_UNSUPPORTED, "CCL blocks too wide for 32-bit in-tile offsets");
   if (!addressing_in_bounds(p, a, b, c, p.lay[ccl::OP_A].total_bytes, p.lay[ccl::OP_B].total_bytes,
                             p.lay[ccl::OP_C].total_bytes))
@@ -434,12 +446,40 @@ ccl_status ccl_debug_gemm_timeline(ccl_plan_t plan, const void* A_ccl, const voi
                     "gemm timeline launch");
 }
 
+ccl_status ccl_debug_gemm_timeline(ccl_plan_t plan, const void* A_ccl, const void* B_ccl,
+                                   void* C_ccl, uint64_t* timeline, int64_t timeline_bytes,
+                                   void* stream) {
+  if (!plan || !A_ccl || !B_ccl || !C_ccl || !timeline)
+    return fail(CCL_ERR_INVALID_ARG, "NULL argument");
+  if (!plan->plan.gemm.supported) return fail(CCL_ERR_UNSUPPORTED, plan->plan.gemm.why_unsupported);
+  return timeline_launch(on_plan_tile(plan->plan), A_ccl, B_ccl, C_ccl, timeline, timeline_bytes, stream);
+}
+
+ccl_status ccl_debug_launch_timeline(ccl_plan_t plan, const void* A_ccl, const void* B_ccl,
+                                     void* C_ccl, uint64_t* timeline, int64_t timeline_bytes,
+                                     void* stream) {
+  if (!plan || !A_ccl || !B_ccl || !C_ccl || !timeline)
+    return fail(CCL_ERR_INVALID_ARG, "NULL argument");
+  if (!plan->plan.gemm.supported) return fail(CCL_ERR_UNSUPPORTED, plan->plan.gemm.why_unsupported);
+  return timeline_launch(plan->plan, A_ccl, B_ccl, C_ccl, timeline, timeline_bytes, stream);
+}
+
+static ccl_status dispatch_launch(const ccl::Plan& p, int32_t* out, void* stream) {
+  if (ccl_status s = check_device()) return s;
+  return hip_status(ccl::launch_dispatch_probe(p, out, static_cast<hipStream_t>(stream)),
+                    "dispatch probe launch");
+}
+
 ccl_status ccl_debug_dispatch(ccl_plan_t plan, int32_t* out, void* stream) {
   if (!plan || !out) return fail(CCL_ERR_INVALID_ARG, "NULL argument");
   if (!plan->plan.gemm.supported) return fail(CCL_ERR_UNSUPPORTED, plan->plan.gemm.why_unsupported);
-  if (ccl_status s = check_device()) return s;
-  return hip_status(ccl::launch_dispatch_probe(plan->plan, out, static_cast<hipStream_t>(stream)),
-                    "dispatch probe launch");
+  return dispatch_launch(on_plan_tile(plan->plan), out, stream);
+}
+
+ccl_status ccl_debug_launch_dispatch(ccl_plan_t plan, int32_t* out, void* stream) {
+  if (!plan || !out) return fail(CCL_ERR_INVALID_ARG, "NULL argument");
+  if (!plan->plan.gemm.supported) return fail(CCL_ERR_UNSUPPORTED, plan->plan.gemm.why_unsupported);
+  return dispatch_launch(plan->plan, out, stream);
 }
 
 }  // extern "C"

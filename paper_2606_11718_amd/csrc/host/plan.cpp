@@ -495,14 +495,145 @@ int64_t splitk_workspace_bytes(const Plan& p, int splits) {
   return s > 1 ? (int64_t)p.G * g.tiles_m * g.tiles_n * s * g.tile_m * g.tile_n * 4 : 0;
 }
 
-void tile_of_wg(const Plan& p, int64_t wg, int* xcd, int64_t* tile_m, int64_t* tile_n) {
+static void tile_of(const Plan& p, const TileMap& map, int64_t workgroups, int64_t wg, int* xcd,
+                    int64_t* tile_m, int64_t* tile_n) {
   *xcd = (int)(wg % kNumXcd);
   *tile_m = *tile_n = -1;
-  if (!p.gemm.supported || wg < 0 || wg >= p.gemm.workgroups) return;
   int32_t pr, pc, ti, tj;
-  if (!map_tile(tile_map(p), wg, &pr, &pc, &ti, &tj)) return;
-  *tile_m = (int64_t)pr * p.gemm.tiles_m + ti;
-  *tile_n = (int64_t)pc * p.gemm.tiles_n + tj;
+  if (wg < 0 || wg >= workgroups || !map_tile(map, wg, &pr, &pc, &ti, &tj)) return;
+  *tile_m = (int64_t)pr * map.tiles_m + ti;
+  *tile_n = (int64_t)pc * map.tiles_n + tj;
+}
+
+void tile_of_wg(const Plan& p, int64_t wg, int* xcd, int64_t* tile_m, int64_t* tile_n) {
+  tile_of(p, tile_map(p), p.gemm.workgroups, wg, xcd, tile_m, tile_n);
+}
+
+void launch_tile_of_wg(const Plan& p, int64_t wg, int* xcd, int64_t* tile_m, int64_t* tile_n) {
+  OperandAddr a, b, c;
+  ccl_addressing(p, &a, &b, &c);
+  const GemmForm f = gemm_form(p, a, b, true, 1);
+  tile_of(p, f.map, f.workgroups, wg, xcd, tile_m, tile_n);
+}
+
+// A block (pr, kc) = pr*Gc + kc; B block (kr, pc) = kr*Gc + pc; C block (pr, pc).
+void ccl_addressing(const Plan& p, OperandAddr* a, OperandAddr* b, OperandAddr* c) {
+  const int64_t sa = p.lay[OP_A].strip_stride_bytes / p.lay[OP_A].elem_bytes;
+  const int64_t sb = p.lay[OP_B].strip_stride_bytes / p.lay[OP_B].elem_bytes;
+  const int64_t sc = p.lay[OP_C].strip_stride_bytes / p.lay[OP_C].elem_bytes;
+  *a = {p.Gc * sa, sa, (int32_t)(p.K / p.Gc), (int32_t)(p.K / p.Gc)};
+  *b = {sb, p.Gc * sb, (int32_t)(p.N / p.Gc), (int32_t)(p.K / p.Gr)};
+  *c = {p.Gc * sc, sc, (int32_t)(p.N / p.Gc), 0};
+}
+
+void rowmajor_addressing(const Plan& p, OperandAddr* a, OperandAddr* b, OperandAddr* c) {
+  const int64_t hr = p.M / p.Gr;
+  *a = {hr * p.K, p.K / p.Gc, (int32_t)p.K, (int32_t)(p.K / p.Gc)};
+  *b = {p.N / p.Gc, (p.K / p.Gr) * p.N, (int32_t)p.N, (int32_t)(p.K / p.Gr)};
+  *c = {hr * p.N, p.N / p.Gc, (int32_t)p.N, 0};
+}
+
+const char* kernel_name(GemmKernel k) {
+  switch (k) {
+    case GemmKernel::K32: return "gemm_kernel";
+    case GemmKernel::K64: return "gemm_k64_kernel";
+    case GemmKernel::A2: return "gemm_a2_kernel";
+    case GemmKernel::FP8: return "gemm_fp8_kernel";
+    case GemmKernel::FP8S: return "gemm_fp8s_kernel";
+    case GemmKernel::FP8X: return "gemm_fp8x_kernel";
+    case GemmKernel::FP8P: return "gemm_fp8p_kernel";
+  }
+  return "";
+}
+
+GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bool remap, int splits) {
+  const GemmConfig& g = p.gemm;
+  const bool fp8 = p.ab_type == DT_FP8_E4M3;
+  const int64_t e = fp8 ? 1 : 2;
+  const bool full = g.tile_m == 256 && g.tile_n == 256;
+  GemmForm f;
+  f.splits = effective_splits(p, splits);      // every K range non-empty
+  f.tile_m = g.tile_m;
+  f.tile_n = g.tile_n;
+  f.waves = g.waves;
+  f.map = tile_map(p, f.splits);
+  f.ksteps = (int32_t)gemm_ksteps(p);
+  f.ksteps_per_split = (f.ksteps + f.splits - 1) / f.splits;
+  const auto set_grid = [&] {
+    f.workgroups = remap ? 8 * (int64_t)f.map.tiles_per_xcd : (int64_t)f.map.tiles_m * f.map.tiles_n * p.G;
+  };
+  set_grid();
+  // One descriptor per operand for a tile over all K blocks: both extents
+  // within the 31 bits of its offsets.
+  const int64_t lim = ((int64_t)1 << 31) - 4096;
+  const bool fits = ((p.K / a.kslice - 1) * a.slice + 256 * (int64_t)a.ld) * e < lim &&
+                    ((p.K / b.kslice - 1) * b.slice + (int64_t)b.kslice * b.ld + 256) * e < lim;
+  // Steps of bk (twice the plan's), and whether they lie in one K block each
+  // and cut K into the same ranges: the workspace and the reduce do not
+  // depend on the kernel.
+  const auto whole_steps = [&](int bk, int32_t* steps, int32_t* per) {
+    *steps = (int32_t)(p.K / bk);
+    *per = (*steps + f.splits - 1) / f.splits;
+    return a.kslice % bk == 0 && b.kslice % bk == 0 && (f.splits == 1 || 2 * *per == f.ksteps_per_split);
+  };
+  int32_t steps, per;
+  if (fp8) {
+    const bool whole = whole_steps(kGemmBK8x, &steps, &per);
+    // 256x256 tiles with 8 waves: the 16x16x128 kernels (no split-K), the
+    // pipelined one where its descriptors reach. Below 256x256 (8 waves, the
+    // plan's choice where both K blocks are multiples of 128): 128-K stages.
+    // Other plans run the 32x32x64 kernel.
+    if (full && f.splits == 1 && g.waves == 8 && whole) {
+      f.kernel = g.fp8_pipe && fits ? GemmKernel::FP8P : GemmKernel::FP8X;
+    } else if (!full && g.waves == 8 && whole && fits) {
+      f.kernel = GemmKernel::FP8S;
+    } else {
+      f.kernel = GemmKernel::FP8;
+      if (!full) f.waves = 4;
+      return f;
+    }
+    f.ksteps = steps;
+    f.ksteps_per_split = per;
+    return f;
+  }
+  const bool whole = whole_steps(kGemmBK64, &steps, &per);
+  // 128x192 or 128x320 tiles: the plan's choice for unsplit launches under the
+  // XCD-aware map, with operands that fit.
+  const bool wide = g.wide_n && remap && f.splits == 1 && fits;
+  if (wide) {
+    f.tile_m = 128;
+    f.tile_n = g.wide_n;
+    f.map = wide_tile_map(p);
+    set_grid();
+  }
+  // 64-K stages (the plan's choice for the bf16 tiles below 256x256), with the
+  // operands' extents within the descriptors' 31 bits. Where both K blocks are
+  // multiples of 64 and split-K cuts K at whole stages, a stage lies in one K
+  // block; otherwise the ragged form, whose K ranges are the 32-K ranges and
+  // whose K blocks hold at least a stage.
+  // More than 32 ragged 128x128 tiles per XCD stay with the 32-K stages, whose
+  // 64 KiB let two workgroups share a CU (1920x5120x1792, 75 tiles: 44.7
+  // against 51.5 us); up to 32 there is one per CU and the 64-K stages win
+  // (1152x2048x3328, 18 tiles: 27.4 -> 26.5 us; 1024x3072x9984, 24 tiles:
+  // 104.6 -> 88.3).
+  const bool paired = !wide && !whole && g.tile_m == 128 && g.tile_n == 128 && f.map.tiles_per_xcd > 32;
+  const bool blocks = whole || (a.kslice >= kGemmBK64 && b.kslice >= kGemmBK64);
+  if (wide || (g.stage_k == 64 && g.waves == 8 && !full && fits && blocks && !paired)) {
+    f.kernel = GemmKernel::K64;
+    f.ragged = !whole;
+    f.stream_b = g.stream_b && remap && f.map.tiles_m == 1;
+    if (whole) {
+      f.ksteps = steps;
+      f.ksteps_per_split = per;
+    }
+    return f;
+  }
+  // The 64-K-pair kernel's A descriptor spans the tile's 256 rows over all
+  // K blocks of A.
+  if (g.a_pairs && f.splits == 1 && g.waves == 8 && full && a.kslice % kGemmBK64 == 0 &&
+      (p.K / a.kslice - 1) * a.slice * 2 + 256 * (int64_t)a.ld * 2 + 4096 < ((int64_t)1 << 31))
+    f.kernel = GemmKernel::A2;
+  return f;
 }
 
 }  // namespace ccl

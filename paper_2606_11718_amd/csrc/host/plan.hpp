@@ -16,6 +16,8 @@ constexpr int kMaxChiplets = 64;
 constexpr int64_t kInfinityCacheBytes = 256ll << 20;  // MI355X MALL
 constexpr int kGemmBK = 32;       // K extent of one GEMM main-loop step (bf16)
 constexpr int kGemmBK8 = 64;      // the same for fp8 operands
+constexpr int kGemmBK64 = 64;     // one stage of the 64-K bf16 kernel
+constexpr int kGemmBK8x = 128;    // one stage of the 128-K fp8 kernels
 constexpr int kMaxSplits = 16;    // split-K ranges per tile
 
 enum Op { OP_A = 0, OP_B = 1, OP_C = 2 };
@@ -125,7 +127,41 @@ int64_t splitk_workspace_bytes(const Plan& p, int splits);
 int64_t splitk_workgroups(const Plan& p, int splits);
 int64_t splitk_reduce_workgroups(const Plan& p);
 
-// Workgroup -> (xcd, kernel tile) of the GEMM launch; tile = (-1, -1) if idle.
+// Workgroup -> (xcd, kernel tile) of a launch on the plan's tile; tile =
+// (-1, -1) if idle.
 void tile_of_wg(const Plan& p, int64_t wg, int* xcd, int64_t* tile_m, int64_t* tile_n);
+
+// Operand addressing of the GEMM kernels, in elements. Logical element
+// (m, k) of A with m in partition row pr and k in K-slice kc sits at
+//   A + pr * a_part + kc * a_slice + (m - pr*hr) * a_ld + (k - kc*a_kslice)
+// (B and C likewise). CCL: a_part = Gc*S, a_slice = S, a_ld = K/Gc.
+struct OperandAddr {
+  int64_t part;     // stride between partition blocks along the tile grid
+  int64_t slice;    // stride between K slices (A, B) / grid columns (C)
+  int32_t ld;       // leading dimension inside a block
+  int32_t kslice;   // K extent of one block (A, B); unused for C
+};
+// CCL operands, and row-major ones (Eq. 2: A M x K, B K x N, C M x N).
+void ccl_addressing(const Plan& p, OperandAddr* a, OperandAddr* b, OperandAddr* c);
+void rowmajor_addressing(const Plan& p, OperandAddr* a, OperandAddr* b, OperandAddr* c);
+
+// The kernels of gemm.hip.
+enum class GemmKernel { K32, K64, A2, FP8, FP8S, FP8X, FP8P };
+// What one GEMM call launches: chosen here, launched by launch_gemm as it is.
+struct GemmForm {
+  GemmKernel kernel = GemmKernel::K32;
+  int tile_m = 0, tile_n = 0, waves = 0;
+  int splits = 1;                   // non-empty K ranges
+  bool ragged = false;              // K64: stages that may straddle K blocks
+  bool stream_b = false;            // K64: B read past the L2
+  int32_t ksteps = 0, ksteps_per_split = 0;   // in the kernel's K steps
+  TileMap map;
+  int64_t workgroups = 0;
+};
+GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bool remap, int splits);
+const char* kernel_name(GemmKernel k);
+
+// tile_of_wg of an unsplit ccl_gemm's own launch.
+void launch_tile_of_wg(const Plan& p, int64_t wg, int* xcd, int64_t* tile_m, int64_t* tile_n);
 
 }  // namespace ccl

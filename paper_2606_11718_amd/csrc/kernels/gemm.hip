@@ -2778,7 +2778,9 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
                        const OperandAddr& a, const OperandAddr& b, const OperandAddr& c,
                        bool remap, float alpha, float beta, int splits, float* ws,
                        hipStream_t stream, uint64_t* timeline) {
-  const GemmConfig& g = p.gemm;
+  if (splits < 1 || (splits > 1 && (!remap || !ws))) return hipErrorInvalidValue;
+  const GemmForm f = gemm_form(p, a, b, remap, splits);
+  if (timeline && (p.ab_type != DT_BF16 || f.splits > 1)) return hipErrorInvalidValue;   // bf16 kernels only
   GemmParams gp;
   gp.timeline = timeline;
   gp.A = static_cast<const uint16_t*>(A);
@@ -2790,26 +2792,20 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
   gp.c = c;
   gp.a_blocks = (int32_t)(p.K / a.kslice);
   gp.b_blocks = (int32_t)(p.K / b.kslice);
-  if (splits < 1 || (splits > 1 && (!remap || !ws))) return hipErrorInvalidValue;
-  splits = effective_splits(p, splits);      // every K range non-empty
-  // 128x192 or 128x320 tiles (the plan's choice, with operands that fit the
-  // kernel below)
-  const bool wide = g.wide_n && remap && splits == 1 && !timeline;
-  gp.map = wide ? wide_tile_map(p) : tile_map(p, splits);
-  const bool fp8 = p.ab_type == DT_FP8_E4M3;
-  if (timeline && (fp8 || splits > 1)) return hipErrorInvalidValue;   // bf16 kernel only
-  gp.ksteps = (int32_t)(p.K / (fp8 ? kBK8 : kBK));
-  gp.ksteps_per_split = (gp.ksteps + splits - 1) / splits;
-  // Rounds path of the bf16 kernel: each operand's K blocks are a multiple
-  // of 4 steps (or it has one block), and every split starts 4-aligned.
+  gp.map = f.map;
+  gp.ksteps = f.ksteps;
+  gp.ksteps_per_split = f.ksteps_per_split;
+  // Rounds path of the 32-K bf16 kernels: each operand's K blocks are a
+  // multiple of 4 steps (or it has one block), and every split starts
+  // 4-aligned.
   {
     const auto aligned = [&](const OperandAddr& o) {
       return (int64_t)o.kslice == p.K || (o.kslice / kBK) % 4 == 0;
     };
-    gp.round_fast = (!fp8 && kStagesBf16 == 4 && aligned(a) && aligned(b) &&
-                     (splits == 1 || gp.ksteps_per_split % 4 == 0)) ? 1 : 0;
+    gp.round_fast = (kStagesBf16 == 4 && aligned(a) && aligned(b) &&
+                     (f.splits == 1 || gp.ksteps_per_split % 4 == 0)) ? 1 : 0;
   }
-  gp.splits_total = splits;
+  gp.splits_total = f.splits;
   // Non-temporal stores of C: always in the pipelined fp8 kernel (1-4 % faster
   // at the power limit) and where B streams, in the other 64- and 128-K-stage
   // launches where C is above the Infinity Cache size. Elsewhere what reads C next (the unpack or
@@ -2818,168 +2814,98 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
   // FFN, whose launches stream their weights, takes 198.6 us with these, 200.1
   // with plain ones.
   gp.c_nt = p.M * p.N * 2 > kInfinityCacheBytes ? 1 : 0;
-  gp.ws = splits > 1 ? ws : nullptr;
+  gp.ws = f.splits > 1 ? ws : nullptr;
   gp.remap = remap ? 1 : 0;
   gp.grid_r = p.Gr;
   gp.alpha = alpha;
   gp.beta = beta;
   gp.epi = beta != 0.f ? 2 : (alpha != 1.f ? 1 : 0);
-  const unsigned wgs = remap ? (unsigned)(8 * (int64_t)gp.map.tiles_per_xcd)
-                             : (unsigned)(g.tiles_m * g.tiles_n * p.G);
-  dim3 grid(wgs);
-  const int waves = g.waves;
-  // fp8 on 256x256 tiles with 8 waves: the 16x16x128 kernel, where every
-  // K block is a multiple of its 128-wide step (no split-K). Other fp8
-  // plans run the 32x32x64 kernel.
-  if (fp8 && splits == 1 && waves == 8 && g.tile_m == 256 && g.tile_n == 256 &&
-      a.kslice % kBK8x == 0 && b.kslice % kBK8x == 0) {
-    gp.ksteps = (int32_t)(p.K / kBK8x);
-    gp.ksteps_per_split = gp.ksteps;
-    // the pipelined kernel's descriptors span the tile's rows of A and
-    // columns of B over all K blocks
-    const int64_t lim = ((int64_t)1 << 31) - 4096;
-    const bool fits = (p.K / a.kslice - 1) * a.slice + 256 * (int64_t)a.ld < lim &&
-                      (p.K / b.kslice - 1) * b.slice + (int64_t)b.kslice * b.ld + 256 < lim;
-    if (g.fp8_pipe && fits) {
+  const dim3 grid((unsigned)f.workgroups);
+  // MFMA tile and rows of the wave grid, for the reduce of split-K partials
+  int md = 16, wgm = 2;
+  const auto tile = [&](int m, int n) { return f.tile_m == m && f.tile_n == n; };
+  switch (f.kernel) {
+    case GemmKernel::FP8P:
       hipLaunchKernelGGL(gemm_fp8p_kernel, grid, dim3(TileFp8P::THREADS), 0, stream, gp);
-      return hipGetLastError();
-    }
-    hipLaunchKernelGGL((gemm_fp8x_kernel<256, 256, 4>), grid, dim3(Tile8x<256, 256, 4>::THREADS), 0,
-                       stream, gp);
-    return hipGetLastError();
-  }
-  // fp8 below 256x256 with 8 waves (the plan's choice where both K blocks are
-  // multiples of 128): 128-K stages, with split-K only where the K ranges of
-  // 64-K steps are whole stages, and extents within the descriptors' 31 bits.
-  const int waves8 = g.tile_m == 256 && g.tile_n == 256 ? waves : 4;
-  if (fp8 && waves == 8 && !(g.tile_m == 256 && g.tile_n == 256) && a.kslice % kBK8x == 0 &&
-      b.kslice % kBK8x == 0) {
-    const int64_t lim = ((int64_t)1 << 31) - 4096;
-    const bool fits = (p.K / a.kslice - 1) * a.slice + 256 * (int64_t)a.ld < lim &&
-                      (p.K / b.kslice - 1) * b.slice + (int64_t)b.kslice * b.ld + 256 < lim;
-    const int32_t ks128 = (int32_t)(p.K / kBK8x);
-    const int32_t per128 = (ks128 + splits - 1) / splits;
-    if (fits && (splits == 1 || 2 * per128 == gp.ksteps_per_split)) {
-      gp.ksteps = ks128;
-      gp.ksteps_per_split = per128;
+      break;
+    case GemmKernel::FP8X:
+      hipLaunchKernelGGL((gemm_fp8x_kernel<256, 256, 4>), grid, dim3(Tile8x<256, 256, 4>::THREADS), 0,
+                         stream, gp);
+      break;
+    case GemmKernel::FP8S:
 #define CCL_LAUNCH8S(BM_, BN_, WGM_, WGN_)                                                  \
   hipLaunchKernelGGL((gemm_fp8s_kernel<BM_, BN_, WGM_, WGN_>), grid,                        \
                      dim3(Tile8s<BM_, BN_, WGM_, WGN_>::THREADS), 0, stream, gp)
       // wave tiles of 64x64 for 256x128 (a 4 x 2 grid reads 176 KiB of LDS per
       // stage, 2 x 4 208 KiB: 1.5-3.5 % faster), 64x64 and 64x32 otherwise
-      const bool tall = g.tile_m == 256;
-      if (tall && g.tile_n == 128) CCL_LAUNCH8S(256, 128, 4, 2);
-      else if (g.tile_m == 128 && g.tile_n == 256) CCL_LAUNCH8S(128, 256, 2, 4);
-      else if (g.tile_m == 128 && g.tile_n == 128) CCL_LAUNCH8S(128, 128, 2, 4);
+      wgm = f.tile_m == 256 ? 4 : 2;
+      if (tile(256, 128)) CCL_LAUNCH8S(256, 128, 4, 2);
+      else if (tile(128, 256)) CCL_LAUNCH8S(128, 256, 2, 4);
+      else if (tile(128, 128)) CCL_LAUNCH8S(128, 128, 2, 4);
       else return hipErrorInvalidValue;
 #undef CCL_LAUNCH8S
-      return splits > 1 ? launch_splitk_reduce(p, gp, 16, waves, stream, tall ? 4 : 2)
-                        : hipGetLastError();
-    }
-  }
-  if (fp8) {
+      break;
+    case GemmKernel::FP8:
 #define CCL_LAUNCH8(BM_, BN_, WGN_)                                                    \
   hipLaunchKernelGGL((gemm_fp8_kernel<BM_, BN_, WGN_>), grid, dim3(Tile8<BM_, BN_, WGN_>::THREADS), \
                      0, stream, gp)
-    if (g.tile_m == 256 && g.tile_n == 256 && waves8 == 8)
-      CCL_LAUNCH8(256, 256, 4);
-    else if (g.tile_m == 256 && g.tile_n == 256)
-      CCL_LAUNCH8(256, 256, 2);
-    else if (g.tile_m == 256 && g.tile_n == 128)
-      CCL_LAUNCH8(256, 128, 2);
-    else if (g.tile_m == 128 && g.tile_n == 256)
-      CCL_LAUNCH8(128, 256, 2);
-    else if (g.tile_m == 128 && g.tile_n == 128)
-      CCL_LAUNCH8(128, 128, 2);
-    else
-      return hipErrorInvalidValue;
+      md = 32;
+      if (tile(256, 256) && f.waves == 8) CCL_LAUNCH8(256, 256, 4);
+      else if (tile(256, 256)) CCL_LAUNCH8(256, 256, 2);
+      else if (tile(256, 128)) CCL_LAUNCH8(256, 128, 2);
+      else if (tile(128, 256)) CCL_LAUNCH8(128, 256, 2);
+      else if (tile(128, 128)) CCL_LAUNCH8(128, 128, 2);
+      else return hipErrorInvalidValue;
 #undef CCL_LAUNCH8
-    return splits > 1 ? launch_splitk_reduce(p, gp, 32, waves8, stream) : hipGetLastError();
-  }
-  // 64-K stages (plan's choice for the bf16 tiles below 256x256), with the
-  // operands' extents within the descriptors' 31 bits. Where both K blocks are
-  // multiples of 64 and split-K cuts K at whole stages, a stage lies in one K
-  // block; otherwise the ragged form, whose K ranges are the 32-K ranges, so
-  // that the workspace and the reduce do not depend on the kernel, and whose K
-  // blocks hold at least a stage.
-  {
-    const int64_t lim = ((int64_t)1 << 31) - 4096;
-    const int32_t ks64 = (int32_t)(p.K / kBK64);
-    const int32_t per64 = (ks64 + splits - 1) / splits;
-    const bool whole = a.kslice % kBK64 == 0 && b.kslice % kBK64 == 0 && 2 * per64 == gp.ksteps_per_split;
-    const bool fits = ((p.K / a.kslice - 1) * a.slice + 256 * (int64_t)a.ld) * 2 < lim &&
-                      ((p.K / b.kslice - 1) * b.slice + (int64_t)b.kslice * b.ld + 256) * 2 < lim &&
-                      (whole || (a.kslice >= kBK64 && b.kslice >= kBK64));
-    // More than 32 ragged 128x128 tiles per XCD stay with the 32-K stages, whose
-    // 64 KiB let two workgroups share a CU (1920x5120x1792, 75 tiles: 44.7
-    // against 51.5 us); up to 32 there is one per CU and the 64-K stages win
-    // (1152x2048x3328, 18 tiles: 27.4 -> 26.5 us; 1024x3072x9984, 24 tiles:
-    // 104.6 -> 88.3).
-    const bool paired = !wide && !whole && g.tile_m == 128 && g.tile_n == 128 && gp.map.tiles_per_xcd > 32;
-    if (wide && !fits) return hipErrorInvalidValue;   // the plan rules this out
-    if (wide || (g.stage_k == 64 && waves == 8 && !(g.tile_m == 256 && g.tile_n == 256) && fits && !paired)) {
-      if (whole) {
-        gp.ksteps = ks64;
-        gp.ksteps_per_split = per64;
-      }
-      const bool b_once = g.stream_b && remap && gp.map.tiles_m == 1;
+      break;
+    case GemmKernel::K64:
 #define CCL_LAUNCH64_AS(BM_, BN_, RAGGED_, BNT_)                                                   \
   hipLaunchKernelGGL((gemm_k64_kernel<BM_, BN_, RAGGED_, BNT_>), grid,                             \
                      dim3(Tile64<BM_, BN_>::THREADS), 0, stream, gp)
-#define CCL_LAUNCH64(BM_, BN_)                                       \
-  do {                                                               \
-    if (whole && b_once) CCL_LAUNCH64_AS(BM_, BN_, false, true);     \
-    else if (whole) CCL_LAUNCH64_AS(BM_, BN_, false, false);         \
-    else if (b_once) CCL_LAUNCH64_AS(BM_, BN_, true, true);          \
-    else CCL_LAUNCH64_AS(BM_, BN_, true, false);                     \
+#define CCL_LAUNCH64(BM_, BN_)                                            \
+  do {                                                                    \
+    if (!f.ragged && f.stream_b) CCL_LAUNCH64_AS(BM_, BN_, false, true);  \
+    else if (!f.ragged) CCL_LAUNCH64_AS(BM_, BN_, false, false);          \
+    else if (f.stream_b) CCL_LAUNCH64_AS(BM_, BN_, true, true);           \
+    else CCL_LAUNCH64_AS(BM_, BN_, true, false);                          \
   } while (0)
-      if (wide && g.wide_n == 192) CCL_LAUNCH64(128, 192);
-      else if (wide) CCL_LAUNCH64(128, 320);
-      else if (g.tile_m == 256 && g.tile_n == 128) CCL_LAUNCH64(256, 128);
-      else if (g.tile_m == 128 && g.tile_n == 256) CCL_LAUNCH64(128, 256);
-      else if (g.tile_m == 128 && g.tile_n == 128) CCL_LAUNCH64(128, 128);
+      if (tile(128, 192)) CCL_LAUNCH64(128, 192);
+      else if (tile(128, 320)) CCL_LAUNCH64(128, 320);
+      else if (tile(256, 128)) CCL_LAUNCH64(256, 128);
+      else if (tile(128, 256)) CCL_LAUNCH64(128, 256);
+      else if (tile(128, 128)) CCL_LAUNCH64(128, 128);
       else return hipErrorInvalidValue;
 #undef CCL_LAUNCH64
 #undef CCL_LAUNCH64_AS
-      return splits > 1 ? launch_splitk_reduce(p, gp, 16, waves, stream) : hipGetLastError();
-    }
-  }
-  // The 64-K-pair kernel's A descriptor spans the tile's 256 rows over all
-  // K blocks of A.
-  if (g.a_pairs && !fp8 && splits == 1 && waves == 8 && g.tile_m == 256 && g.tile_n == 256 &&
-      a.kslice % 64 == 0 &&
-      (p.K / a.kslice - 1) * a.slice * 2 + 256 * (int64_t)a.ld * 2 + 4096 < ((int64_t)1 << 31)) {
-    hipLaunchKernelGGL(gemm_a2_kernel, grid, dim3(TileA2::THREADS), 0, stream, gp);
-    return hipGetLastError();
-  }
+      break;
+    case GemmKernel::A2:
+      hipLaunchKernelGGL(gemm_a2_kernel, grid, dim3(TileA2::THREADS), 0, stream, gp);
+      break;
+    case GemmKernel::K32:
 #define CCL_LAUNCH(BM_, BN_, WGN_)                                                     \
   hipLaunchKernelGGL((gemm_kernel<BM_, BN_, WGN_>), grid, dim3(Tile<BM_, BN_, WGN_>::THREADS), 0, \
                      stream, gp)
-  if (g.tile_m == 256 && g.tile_n == 256 && waves == 8)
-    CCL_LAUNCH(256, 256, 4);
-  else if (g.tile_m == 256 && g.tile_n == 128 && waves == 8)
-    CCL_LAUNCH(256, 128, 4);
-  else if (g.tile_m == 128 && g.tile_n == 256 && waves == 8)
-    CCL_LAUNCH(128, 256, 4);
-  else if (g.tile_m == 128 && g.tile_n == 128 && waves == 8)
-    CCL_LAUNCH(128, 128, 4);
-  else if (g.tile_m == 256 && g.tile_n == 256)
-    CCL_LAUNCH(256, 256, 2);
-  else if (g.tile_m == 256 && g.tile_n == 128)
-    CCL_LAUNCH(256, 128, 2);
-  else if (g.tile_m == 128 && g.tile_n == 256)
-    CCL_LAUNCH(128, 256, 2);
-  else if (g.tile_m == 128 && g.tile_n == 128)
-    CCL_LAUNCH(128, 128, 2);
-  else
-    return hipErrorInvalidValue;
+      if (tile(256, 256) && f.waves == 8) CCL_LAUNCH(256, 256, 4);
+      else if (tile(256, 128) && f.waves == 8) CCL_LAUNCH(256, 128, 4);
+      else if (tile(128, 256) && f.waves == 8) CCL_LAUNCH(128, 256, 4);
+      else if (tile(128, 128) && f.waves == 8) CCL_LAUNCH(128, 128, 4);
+      else if (tile(256, 256)) CCL_LAUNCH(256, 256, 2);
+      else if (tile(256, 128)) CCL_LAUNCH(256, 128, 2);
+      else if (tile(128, 256)) CCL_LAUNCH(128, 256, 2);
+      else if (tile(128, 128)) CCL_LAUNCH(128, 128, 2);
+      else return hipErrorInvalidValue;
 #undef CCL_LAUNCH
-  return splits > 1 ? launch_splitk_reduce(p, gp, 16, waves, stream) : hipGetLastError();
+      break;
+  }
+  return f.splits > 1 ? launch_splitk_reduce(p, gp, md, f.waves, stream, wgm) : hipGetLastError();
 }
 
 hipError_t launch_dispatch_probe(const Plan& p, int32_t* out, hipStream_t stream) {
-  hipLaunchKernelGGL(dispatch_probe_kernel, dim3((unsigned)p.gemm.workgroups), dim3(64), 0, stream,
-                     tile_map(p), (int32_t)p.gemm.tiles_m, (int32_t)p.gemm.tiles_n, out);
+  OperandAddr a, b, c;
+  ccl_addressing(p, &a, &b, &c);
+  const GemmForm f = gemm_form(p, a, b, true, 1);
+  hipLaunchKernelGGL(dispatch_probe_kernel, dim3((unsigned)f.workgroups), dim3(64), 0, stream, f.map,
+                     f.map.tiles_m, f.map.tiles_n, out);
   return hipGetLastError();
 }
 

@@ -1,0 +1,77 @@
+"""What ccl_gemm itself launches (ccl_debug_launch), against the plan's tile:
+the 128x192 and 128x320 tiles' workgroup map against its definition in plain
+integers, every tile once and on an XCD of its chiplet; and the kernel form the
+dispatch chooses at its edges. No GPU needed."""
+import pytest
+
+from oracle import plan as OP
+from paper_2606_11718_amd import ccl
+from tests.test_host_tile_map import _expected
+
+FP8, BF16 = ccl.CCL_DT_FP8_E4M3, ccl.CCL_DT_BF16
+
+
+@pytest.mark.parametrize("wide,G,Gr,tiles_m,tiles_n", [
+    (192, 8, 2, 16, 2), (192, 1, 1, 9, 5), (192, 4, 2, 10, 2), (192, 2, 1, 3, 7), (192, 8, 8, 17, 4),
+    (320, 8, 1, 15, 2), (320, 1, 1, 11, 3), (320, 4, 1, 8, 5), (320, 8, 4, 19, 2), (320, 2, 2, 1, 9)])
+def test_wide_map(wide, G, Gr, tiles_m, tiles_n, monkeypatch):
+    monkeypatch.setenv("CCL_GEMM_WIDE", str(wide))
+    Gc = G // Gr
+    M, N, K = 128 * tiles_m * Gr, wide * 2 * tiles_n * Gc, 512
+    tiles_n *= 2                              # partitions hold whole 128-column model tiles
+    plan = ccl.ccl_plan(M, N, K, G, Gr, 4096)
+    run = ccl.ccl_debug_launch(plan)
+    assert (run.kernel, run.tile_rows, run.tile_cols, run.waves) == ("gemm_k64_kernel", 128, wide, 8)
+    per_xcd = -(-tiles_m * tiles_n // (8 // G))
+    assert run.workgroups == 8 * per_xcd
+    seen = set()
+    for wg in range(run.workgroups + 8):
+        xcd, ti, tj = ccl.ccl_debug_launch_tile_of_wg(plan, wg)
+        assert (xcd, (ti, tj)) == (wg % 8, _expected(wg, G, Gr, tiles_m, tiles_n, min(8, tiles_m))), wg
+        if ti >= 0:
+            assert (ti, tj) not in seen
+            seen.add((ti, tj))
+            owners = {OP.owner(ti, c // 128, M, N, Gr, Gc) for c in (tj * wide, (tj + 1) * wide - 1)}
+            assert len(owners) == 1 and xcd in OP.xcds_of_chiplet(owners.pop(), G)
+    assert len(seen) == G * tiles_m * tiles_n
+
+
+def test_chosen_wide_tiles_and_the_plan_tile():
+    """The plan's tile stays what split-K uses; the launch hook says what runs."""
+    plan = ccl.ccl_plan(4096, 1536, 2048, 8, 2, 4096)
+    assert ccl.ccl_debug_gemm_config(plan)[:2] == (256, 128)
+    run = ccl.ccl_debug_launch(plan)
+    assert (run.tile_rows, run.tile_cols, run.workgroups, run.k_ranges) == (128, 192, 256, 1)
+    split = ccl.ccl_debug_launch(plan, 2)
+    assert (split.kernel, split.tile_rows, split.tile_cols, split.k_ranges) == ("gemm_k64_kernel", 256, 128, 2)
+    assert ccl.ccl_debug_launch(plan, 1, 2).tile_cols == 192           # row-major, XCD-aware map
+    assert ccl.ccl_debug_launch(plan, 1, 1).tile_cols == 128           # row-major, native order
+
+
+@pytest.mark.parametrize("shape,env,kernel,ragged", [
+    ((1024, 1024, 1024, 8, 2, BF16), {"CCL_GEMM_TILE": "128x128"}, "gemm_k64_kernel", False),
+    ((1024, 1024, 1024, 8, 2, BF16), {"CCL_GEMM_TILE": "128x128", "CCL_GEMM_STAGE_K": "32"}, "gemm_kernel", False),
+    ((1024, 1024, 1024, 8, 2, BF16), {"CCL_GEMM_TILE": "128x128", "CCL_GEMM_WAVES": "4"}, "gemm_kernel", False),
+    ((256, 256, 32, 1, 1, BF16), {}, "gemm_kernel", False),            # K blocks of one 32-K step
+    ((256, 256, 96, 1, 1, BF16), {"CCL_GEMM_TILE": "128x128"}, "gemm_k64_kernel", True),
+    ((8192, 28672, 8192, 8, 2, BF16), {}, "gemm_a2_kernel", False),
+    ((8192, 28672, 8192, 8, 2, FP8), {}, "gemm_fp8p_kernel", False),
+    ((8192, 28672, 8192, 8, 2, FP8), {"CCL_GEMM_FP8_PIPE": "0"}, "gemm_fp8x_kernel", False),
+    ((4096, 1536, 2048, 8, 2, FP8), {}, "gemm_fp8s_kernel", False),
+    ((4096, 1536, 2112 * 4, 8, 2, FP8), {"CCL_GEMM_TILE": "256x128"}, "gemm_fp8_kernel", False),  # 64 mod 128
+])
+def test_form(shape, env, kernel, ragged, monkeypatch):
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    M, N, K, G, Gr, ab = shape
+    run = ccl.ccl_debug_launch(ccl.ccl_plan_typed(M, N, K, G, Gr, 4096, ab, BF16))
+    assert (run.kernel, run.ragged) == (kernel, ragged)
+
+
+def test_arguments():
+    plan = ccl.ccl_plan(1024, 1024, 1024, 8, 2, 4096)
+    for splits, operands in ((0, 0), (17, 0), (1, 3), (1, -1), (2, 1)):
+        with pytest.raises(ccl.CCLError, match="CCL_ERR_INVALID_ARG"):
+            ccl.ccl_debug_launch(plan, splits, operands)
+    with pytest.raises(ccl.CCLError, match="CCL_ERR_UNSUPPORTED"):
+        ccl.ccl_debug_launch(ccl.ccl_plan_typed(384, 768, 384, 3, 1, 4096, BF16, BF16))
