@@ -135,7 +135,10 @@ void choose_gemm_config(Plan* p) {
   // Measured on 8192x28672x8192 (28 tile columns, 8 rows chosen): 9 % less
   // L2-miss traffic than 4 rows, 1 % faster.
   int gm = panels_touched(g, 8) < panels_touched(g, 4) ? 8 : 4;
-  if (const char* e = std::getenv("CCL_GEMM_GROUP_M")) gm = std::max(1, std::atoi(e));
+  // Wider tiles (below) take 8 rows: 32 resident tiles of 128x192 then cover
+  // 1024 x 768 of C.
+  g.wide_group_m = 8;
+  if (const char* e = std::getenv("CCL_GEMM_GROUP_M")) gm = g.wide_group_m = std::max(1, std::atoi(e));
   g.group_m = (int)std::min<int64_t>(gm, g.tiles_m);
   // Waves per workgroup: 8 (two per SIMD) for every bf16 tile, for fp8
   // 256x256 tiles and for the other fp8 tiles where both K blocks are
@@ -450,10 +453,9 @@ TileMap tile_map(const Plan& p, int splits) {
 TileMap wide_tile_map(const Plan& p) {
   const GemmConfig& g = p.gemm;
   const int64_t tm = p.part_rows() / 128, tn = p.part_cols() / g.wide_n;
-  // 8 tile rows per group: 32 resident tiles of 128x192 then cover 1024 x 768 of C
   return make_tile_map(g.xcd_per_chiplet, p.Gc, (int32_t)tm, (int32_t)tn,
                  (int32_t)((tm * tn + g.xcd_per_chiplet - 1) / g.xcd_per_chiplet),
-                 (int32_t)std::min<int64_t>(8, tm), 1);
+                 (int32_t)std::min<int64_t>(g.wide_group_m, tm), 1);
 }
 
 int64_t gemm_ksteps(const Plan& p) {

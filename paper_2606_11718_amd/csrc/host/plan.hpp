@@ -54,6 +54,7 @@ struct GemmConfig {
   bool fp8_pipe = false;            // fp8 256x256: fragment reads pipelined across steps
   bool stream_b = false;            // bf16 64-K stages: B read past the L2 (non-temporal)
   int wide_n = 0;                   // bf16, unsplit: 128 x wide_n tiles instead (192 or 320; 0: none)
+  int wide_group_m = 8;             // raster group height of those launches
   bool supported = false;           // whether ccl_gemm can run this plan
   std::string why_unsupported;
 };

@@ -36,6 +36,16 @@ def test_wide_map(wide, G, Gr, tiles_m, tiles_n, monkeypatch):
     assert len(seen) == G * tiles_m * tiles_n
 
 
+@pytest.mark.parametrize("group", [1, 3, 4, 8, 16])
+def test_raster_override_reaches_wide_tiles(group, monkeypatch):
+    """CCL_GEMM_GROUP_M sets the raster height of every launch."""
+    monkeypatch.setenv("CCL_GEMM_GROUP_M", str(group))
+    plan = ccl.ccl_plan(4096, 1536, 2048, 8, 2, 4096)
+    assert ccl.ccl_debug_launch(plan).tile_cols == 192
+    for wg in range(256):
+        assert ccl.ccl_debug_launch_tile_of_wg(plan, wg)[1:] == _expected(wg, 8, 2, 16, 2, group), wg
+
+
 def test_chosen_wide_tiles_and_the_plan_tile():
     """The plan's tile stays what split-K uses; the launch hook says what runs."""
     plan = ccl.ccl_plan(4096, 1536, 2048, 8, 2, 4096)
