@@ -163,19 +163,23 @@ void choose_gemm_config(Plan* p) {
   const char* stage_env = std::getenv("CCL_GEMM_STAGE_K");
   const bool stage32 = stage_env && std::atoi(stage_env) == 32;
   if (stage32) g.stage_k = 32;
-  // B streams past the L2 where each of its lines is read by one workgroup of
-  // the XCD only (one tile row per partition), and it is above the Infinity
-  // Cache size (non-temporal lines do not stay there either): 128x28672x8192
-  // 98.4 -> 96.0 us, 128x8192x28672 in 4 ranges 101.9 -> 93.3. Below that
-  // size a weight that is in the cache must be read from there: the
-  // 256x16896x1280 forward pass (43 MB) took 42.0 us streamed, 37.1 not.
-  // Where tile rows share B it is 20-50 % slower. CCL_GEMM_STREAM_B=0|1
-  // overrides the size rule.
+  // B streams past the L2 where each of its lines is read by one workgroup
+  // only (one tile row per partition, one partition row), and it is above the
+  // Infinity Cache size (non-temporal lines do not stay there either). Us per
+  // launch, not streamed -> streamed: 128x28672x8192 on 1x8 104.4 -> 98.2, on
+  // one partition 103.1 -> 96.5. With two, four and eight partition rows the
+  // Infinity Cache serves all reads of B but one, and streaming loses:
+  // 256x28672x8192 on 2x4 144.6 -> 161.6, 512x28672x8192 on 4x2 282.5 ->
+  // 320.5, 1024x28672x8192 on 8x1 571.7 -> 660.6. Below that size a weight
+  // that is in the cache must be read from there: the 256x16896x1280 pass
+  // (43 MB, pack, GEMM and unpack) took 42.0 us streamed, 37.1 not. Where tile
+  // rows share B it is 20-50 % slower. CCL_GEMM_STREAM_B=0|1 overrides the
+  // size and partition rules.
   g.stream_b = p->ab_type == DT_BF16 && g.tiles_m == 1;
   if (const char* e = std::getenv("CCL_GEMM_STREAM_B"))
     g.stream_b = g.stream_b && std::atoi(e) != 0;
   else
-    g.stream_b = g.stream_b && p->K * p->N * 2 > kInfinityCacheBytes;
+    g.stream_b = g.stream_b && p->Gr == 1 && p->K * p->N * 2 > kInfinityCacheBytes;
   // 256x256 keeps 32-K steps for B and the MFMA schedule but stages A in
   // 64-K pairs of steps: whole 128-byte lines per A load, and loads four
   // steps ahead in a ring of three pair buffers. Same box, alternating:

@@ -78,6 +78,19 @@ def test_form(shape, env, kernel, ragged, monkeypatch):
     assert (run.kernel, run.ragged) == (kernel, ragged)
 
 
+@pytest.mark.parametrize("M,N,K,G,Gr,stream", [
+    (128, 28672, 8192, 8, 1, True), (128, 28672, 8192, 1, 1, True),
+    (128, 16384, 8192, 8, 1, False),          # 256 MiB: stays in the Infinity Cache
+    (128, 16384, 8448, 8, 1, True),
+    (256, 28672, 8192, 8, 1, False),          # two tile rows
+    (256, 28672, 8192, 8, 2, False), (512, 28672, 8192, 8, 4, False), (1024, 28672, 8192, 8, 8, False),
+    (256, 24576, 8192, 8, 2, False), (512, 20480, 8192, 8, 4, False)])
+def test_b_streams_where_one_workgroup_reads_it(M, N, K, G, Gr, stream, monkeypatch):
+    if M == 256 and Gr == 1:
+        monkeypatch.setenv("CCL_GEMM_TILE", "128x256")
+    assert ccl.ccl_debug_launch(ccl.ccl_plan(M, N, K, G, Gr, 4096)).stream_b == stream
+
+
 def test_arguments():
     plan = ccl.ccl_plan(1024, 1024, 1024, 8, 2, 4096)
     for splits, operands in ((0, 0), (17, 0), (1, 3), (1, -1), (2, 1)):
