@@ -376,6 +376,7 @@ typedef struct ccl_launch {
   int k_ranges;         /* split-K ranges (1: none) */
   int ragged;           /* 64-K stages that may straddle K blocks */
   int stream_b;         /* B read past the L2 */
+  int c_nt;             /* C stored non-temporally for its size */
 } ccl_launch;
 
 /* The launch of ccl_gemm / ccl_gemm_scaled (splits 1, operands 0), of

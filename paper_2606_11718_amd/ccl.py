@@ -66,7 +66,7 @@ class _L2Traffic(ctypes.Structure):
 
 class _Launch(ctypes.Structure):
     _fields_ = [("kernel", ctypes.c_char * 32), ("workgroups", ctypes.c_int64)] + \
-               [(n, ctypes.c_int) for n in ("tile_rows", "tile_cols", "waves", "k_ranges", "ragged", "stream_b")]
+               [(n, ctypes.c_int) for n in ("tile_rows", "tile_cols", "waves", "k_ranges", "ragged", "stream_b", "c_nt")]
 
 
 _lib = None
@@ -325,13 +325,14 @@ class Launch:
     k_ranges: int
     ragged: bool
     stream_b: bool
+    c_nt: bool
 
 
 def ccl_debug_launch(plan: Plan, splits: int = 1, operands: int = 0) -> Launch:
     out = _Launch()
     _check(library().ccl_debug_launch(plan, splits, operands, ctypes.byref(out)))
     return Launch(out.kernel.decode(), out.workgroups, out.tile_rows, out.tile_cols, out.waves, out.k_ranges,
-                  bool(out.ragged), bool(out.stream_b))
+                  bool(out.ragged), bool(out.stream_b), bool(out.c_nt))
 
 
 def ccl_debug_launch_tile_of_wg(plan: Plan, wg: int) -> tuple[int, int, int]:

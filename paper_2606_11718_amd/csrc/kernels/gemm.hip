@@ -84,7 +84,7 @@ struct GemmParams {
   int32_t ksteps_per_split;  // K steps of one split (= ksteps without split-K)
   int32_t round_fast;   // bf16: K blocks and split starts are 4-step aligned (rounds path)
   int32_t splits_total; // split-K ranges per tile (reduce kernel)
-  int32_t c_nt;         // a bf16 C is stored non-temporally (kernels that can)
+  int32_t c_nt;         // C is stored non-temporally (kernels that can)
   float* ws;            // split-K: fp32 partial tiles (null: write C directly)
   uint64_t* timeline;   // bf16 kernel: kTimelineWords per wave (null: not recorded)
 };
@@ -481,8 +481,11 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
 // together. Against 16-row pieces straight from the registers, us per launch
 // on one box: 8192x28672x8192, fp32 C += 2842 -> 2764 (a plain bf16 C: 2570);
 // 8192x8192x3584, fp32 C 359 -> 353, C += 412 -> 396; 4096x1536x2048, bf16
-// C += 31.3 -> 27.6, fp32 C 30.0 -> 28.4. Plain stores instead of
-// non-temporal ones: 0-3 % slower on a C that is not read, else the same.
+// C += 31.3 -> 27.6, fp32 C 30.0 -> 28.4. An fp32 C is stored non-temporally
+// only from the Infinity Cache size on (p.c_nt). Below it a launch alone is 0-15
+// % faster with non-temporal stores, but what reads C next then misses: pack, GEMM and
+// unpack with them -> with plain ones, 2048x4096x1024 39.4 -> 36.1 us,
+// 5888x1024x1024 36.1 -> 33.5; accumulating launches take the same.
 template <int BM, int BN, int NW, int TM, int TN, int WM, int WN, int BUF, bool F32>
 __device__ __forceinline__ void store_tile_staged_f32(const GemmParams& p, const f32x4 (&acc)[TM][TN],
                                                       char* lo, char* hi, int32_t pr, int32_t pc,
@@ -556,7 +559,9 @@ __device__ __forceinline__ void store_tile_staged_f32(const GemmParams& p, const
       }
       const int64_t idx = at + (int64_t)X::row(i, lane) * p.c.ld + 4 * c;
       if constexpr (F32) {
-        __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + idx));
+        f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + idx);
+        if (p.c_nt) __builtin_nontemporal_store(o, dst);
+        else *dst = o;
       } else {
         uint2 v;
         v.x = bf16_rne(o[0]) | (bf16_rne(o[1]) << 16);
@@ -2806,14 +2811,7 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
                      (f.splits == 1 || gp.ksteps_per_split % 4 == 0)) ? 1 : 0;
   }
   gp.splits_total = f.splits;
-  // Non-temporal stores of C: always in the pipelined fp8 kernel (1-4 % faster
-  // at the power limit) and where B streams, in the other 64- and 128-K-stage
-  // launches where C is above the Infinity Cache size. Elsewhere what reads C next (the unpack or
-  // the next GEMM) finds it in the cache: whole passes, 4096x1536x2048 44.9 ->
-  // 44.2 us, 4096x768x2048 30.2 -> 29.5, 256x512x256 10.7 -> 10.4. The decode
-  // FFN, whose launches stream their weights, takes 198.6 us with these, 200.1
-  // with plain ones.
-  gp.c_nt = p.M * p.N * 2 > kInfinityCacheBytes ? 1 : 0;
+  gp.c_nt = f.c_nt ? 1 : 0;
   gp.ws = f.splits > 1 ? ws : nullptr;
   gp.remap = remap ? 1 : 0;
   gp.grid_r = p.Gr;

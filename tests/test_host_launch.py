@@ -8,7 +8,7 @@ from oracle import plan as OP
 from paper_2606_11718_amd import ccl
 from tests.test_host_tile_map import _expected
 
-FP8, BF16 = ccl.CCL_DT_FP8_E4M3, ccl.CCL_DT_BF16
+FP8, BF16, FP32 = ccl.CCL_DT_FP8_E4M3, ccl.CCL_DT_BF16, ccl.CCL_DT_FP32
 
 
 @pytest.mark.parametrize("wide,G,Gr,tiles_m,tiles_n", [
@@ -89,6 +89,15 @@ def test_b_streams_where_one_workgroup_reads_it(M, N, K, G, Gr, stream, monkeypa
     if M == 256 and Gr == 1:
         monkeypatch.setenv("CCL_GEMM_TILE", "128x256")
     assert ccl.ccl_debug_launch(ccl.ccl_plan(M, N, K, G, Gr, 4096)).stream_b == stream
+
+
+@pytest.mark.parametrize("M,N,c,nt", [
+    (2048, 4096, FP32, False), (8192, 4096, FP32, False), (8192, 8192 - 128 * 8, FP32, False),
+    (8192, 8192, FP32, True), (8192, 28672, FP32, True),
+    (8192, 16384, BF16, False), (8192, 28672, BF16, True)])
+@pytest.mark.parametrize("ab", [BF16, FP8])
+def test_c_leaves_the_cache_only_above_its_size(M, N, c, nt, ab):
+    assert ccl.ccl_debug_launch(ccl.ccl_plan_typed(M, N, 1024, 8, 2, 4096, ab, c)).c_nt == nt
 
 
 def test_arguments():
