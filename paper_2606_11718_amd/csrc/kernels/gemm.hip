@@ -2216,17 +2216,19 @@ __global__ void __launch_bounds__(512, 2) gemm_fp8p_kernel(GemmParams p) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) a_rd[h] = row * kBK8x + (((4 * h + g) ^ swz_a8x(row)) * 16);
   }
-  int32_t b_rd[T::TN][4];
+  // Read r of B fragment nt: rows 64 (r / 2) + 8 (r % 2) below its first, whose
+  // swizzle they share. The first rows' LDS addresses in buffer 0 are opaque, so
+  // that r and the buffer go into the instruction offset: left to itself the
+  // compiler kept three registers per fragment, and 3 of them spilled.
+  uint32_t b_rd[T::TN];
   {
-    const int g = lane >> 4, s = lane & 15;
+    const int krow = 16 * (lane >> 4) + ((lane & 15) >> 1);
 #pragma unroll
     for (int nt = 0; nt < T::TN; ++nt) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int krow = 64 * (r >> 1) + 16 * g + 8 * (r & 1) + (s >> 1);
-        const int col = wn * T::WN + nt * 16 + 8 * (s & 1);
-        b_rd[nt][r] = krow * BN + (((col >> 4) ^ swz_b8x<BN>(krow)) * 16) + (col & 15);
-      }
+      const int col = wn * T::WN + nt * 16 + 8 * (lane & 1);
+      b_rd[nt] = (uint32_t)(uintptr_t)(const lds_char*)&smB[0][0] + krow * BN +
+                 (((col >> 4) ^ swz_b8x<BN>(krow)) * 16) + (col & 15);
+      asm volatile("" : "+v"(b_rd[nt]));
     }
   }
 
@@ -2290,7 +2292,8 @@ __global__ void __launch_bounds__(512, 2) gemm_fp8p_kernel(GemmParams p) {
   auto read_b = [&](const char* sB, int nt, i32x8& f) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const i32x2 v = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)(sB + b_rd[nt][r]));
+      const uint32_t at = (uint32_t)(sB - &smB[0][0]) + (64 * (r >> 1) + 8 * (r & 1)) * BN;
+      const i32x2 v = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)(b_rd[nt] + at));
       f[2 * r] = v[0];
       f[2 * r + 1] = v[1];
     }

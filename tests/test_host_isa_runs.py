@@ -6,7 +6,7 @@ import re
 
 import pytest
 
-from tests.test_host_isa import _body, _lds_offset, asm  # noqa: F401
+from tests.test_host_isa import KERNELS, _body, _lds_offset, asm  # noqa: F401
 
 
 @pytest.mark.parametrize("bm,bn,lengths", [(256, 128, {2, 4}), (128, 256, {2, 4}), (128, 128, {2}), (128, 192, {2, 3}),
@@ -26,3 +26,10 @@ def test_k64_runs(asm, bm, bn, lengths, ragged, nt):  # noqa: F811
     assert {len(r) for r in runs} == lengths
     assert all(r == [1024 * i for i in range(len(r))] for r in runs)
     assert not any("scratch_" in ln for ln in body)
+
+
+@pytest.mark.parametrize("kernel", list(KERNELS))
+def test_pipelined_kernels_do_not_spill(asm, kernel):  # noqa: F811
+    """No scratch access in the whole kernel: epilogues included, whose values
+    must not stay live through the K loop."""
+    assert not [ln for ln in _body(asm, kernel) if ln.startswith("scratch_")][:4]
