@@ -585,15 +585,20 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&ac
                                            char* hi, int32_t pr, int32_t pc, int32_t ti, int32_t tj,
                                            int32_t split, int wm, int wn, int wave, int lane) {
   static_assert((BM / 2) * BN * 2 <= BUF, "each half of the bf16 C tile fits in one operand's buffers");
-  const bool direct = NW == 4 && (p.c_f32 || p.epi == 2);   // 4 waves: 256 accumulators, no registers left
-  if (!p.ws && !p.c_f32 && p.epi == 0)
+  if (!p.ws && !p.c_f32 && p.epi == 0) {
     store_tile_staged<BM, BN, NW, TM, TN, WM, WN, NT, false>(p, acc, lo, hi, pr, pc, ti, tj, wm, wn, wave, lane);
-  else if (p.ws || direct)
+    return;
+  }
+  // With 4 waves (up to 256 accumulators each) there are no registers for more
+  // than one staged form: a second spilled 8 more (gemm_kernel<256, 256, 2>).
+  if (NW == 4 || p.ws) {
     store_tile<BM, BN, 16, TM, TN, WM, WN>(p, acc, pr, pc, ti, tj, split, wm, wn, lane);
-  else if (!p.c_f32 && p.epi == 1)
-    store_tile_staged<BM, BN, NW, TM, TN, WM, WN, NT, true>(p, acc, lo, hi, pr, pc, ti, tj, wm, wn, wave, lane);
-  else if constexpr (NW == 8) {
-    if (p.c_f32)
+    return;
+  }
+  if constexpr (NW == 8) {
+    if (!p.c_f32 && p.epi == 1)
+      store_tile_staged<BM, BN, NW, TM, TN, WM, WN, NT, true>(p, acc, lo, hi, pr, pc, ti, tj, wm, wn, wave, lane);
+    else if (p.c_f32)
       store_tile_staged_f32<BM, BN, NW, TM, TN, WM, WN, BUF, true>(p, acc, lo, hi, pr, pc, ti, tj, wm, wn,
                                                                    wave, lane);
     else

@@ -33,3 +33,11 @@ def test_pipelined_kernels_do_not_spill(asm, kernel):  # noqa: F811
     """No scratch access in the whole kernel: epilogues included, whose values
     must not stay live through the K loop."""
     assert not [ln for ln in _body(asm, kernel) if ln.startswith("scratch_")][:4]
+
+
+def test_four_wave_kernel_spills_no_more_than_its_k_loop_needs(asm):  # noqa: F811
+    """gemm_kernel<256, 256, 2> holds 256 accumulators per lane; 88 bytes of
+    scratch with one staged epilogue, 120 with two."""
+    name = "_ZN3ccl12_GLOBAL__N_111gemm_kernelILi256ELi256ELi2EEEvNS0_10GemmParamsE"
+    size = re.search(rf"\.name:\s+{name}\n\s+\.private_segment_fixed_size:\s+(\d+)", asm)
+    assert int(size.group(1)) <= 88
