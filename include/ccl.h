@@ -375,6 +375,7 @@ typedef struct ccl_launch {
   int waves;            /* per workgroup */
   int k_ranges;         /* split-K ranges (1: none) */
   int ragged;           /* 64-K stages that may straddle K blocks */
+  int far;              /* 64-K stages of operands of 2 GiB and more */
   int stream_b;         /* B read past the L2 */
   int c_nt;             /* C stored non-temporally for its size */
 } ccl_launch;

@@ -66,7 +66,7 @@ class _L2Traffic(ctypes.Structure):
 
 class _Launch(ctypes.Structure):
     _fields_ = [("kernel", ctypes.c_char * 32), ("workgroups", ctypes.c_int64)] + \
-               [(n, ctypes.c_int) for n in ("tile_rows", "tile_cols", "waves", "k_ranges", "ragged", "stream_b", "c_nt")]
+               [(n, ctypes.c_int) for n in ("tile_rows", "tile_cols", "waves", "k_ranges", "ragged", "far", "stream_b", "c_nt")]
 
 
 _lib = None
@@ -324,6 +324,7 @@ class Launch:
     waves: int
     k_ranges: int
     ragged: bool
+    far: bool
     stream_b: bool
     c_nt: bool
 
@@ -332,7 +333,7 @@ def ccl_debug_launch(plan: Plan, splits: int = 1, operands: int = 0) -> Launch:
     out = _Launch()
     _check(library().ccl_debug_launch(plan, splits, operands, ctypes.byref(out)))
     return Launch(out.kernel.decode(), out.workgroups, out.tile_rows, out.tile_cols, out.waves, out.k_ranges,
-                  bool(out.ragged), bool(out.stream_b), bool(out.c_nt))
+                  bool(out.ragged), bool(out.far), bool(out.stream_b), bool(out.c_nt))
 
 
 def ccl_debug_launch_tile_of_wg(plan: Plan, wg: int) -> tuple[int, int, int]:

@@ -403,6 +403,7 @@ ccl_status ccl_debug_launch(ccl_plan_t plan, int splits, int operands, ccl_launc
   out->waves = f.waves;
   out->k_ranges = f.splits;
   out->ragged = f.ragged;
+  out->far = f.far;
   out->stream_b = f.stream_b;
   out->c_nt = f.c_nt;
   return ok();

@@ -163,6 +163,8 @@ void choose_gemm_config(Plan* p) {
   const char* stage_env = std::getenv("CCL_GEMM_STAGE_K");
   const bool stage32 = stage_env && std::atoi(stage_env) == 32;
   if (stage32) g.stage_k = 32;
+  // CCL_GEMM_FAR=1 takes the form for operands of 2 GiB and more at any size.
+  if (const char* e = std::getenv("CCL_GEMM_FAR")) g.far = std::atoi(e) == 1;
   // B streams past the L2 where each of its lines is read by one workgroup
   // only (one tile row per partition, one partition row), and it is above the
   // Infinity Cache size (non-temporal lines do not stay there either). Us per
@@ -617,28 +619,29 @@ GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bo
   const bool whole = whole_steps(kGemmBK64, &steps, &per);
   // 128x192 or 128x320 tiles: the plan's choice for unsplit launches under the
   // XCD-aware map, with operands that fit.
-  const bool wide = g.wide_n && remap && f.splits == 1 && fits;
+  const bool wide = g.wide_n && remap && f.splits == 1 && fits && !g.far;
   if (wide) {
     f.tile_m = 128;
     f.tile_n = g.wide_n;
     f.map = wide_tile_map(p);
     set_grid();
   }
-  // 64-K stages (the plan's choice for the bf16 tiles below 256x256), with the
-  // operands' extents within the descriptors' 31 bits. Where both K blocks are
-  // multiples of 64 and split-K cuts K at whole stages, a stage lies in one K
-  // block; otherwise the ragged form, whose K ranges are the 32-K ranges and
-  // whose K blocks hold at least a stage.
+  // 64-K stages (the plan's choice for the bf16 tiles below 256x256). Where
+  // both K blocks are multiples of 64 and split-K cuts K at whole stages, a
+  // stage lies in one K block, and operands of 2 GiB and more take the far
+  // form; otherwise the ragged form, whose K ranges are the 32-K ranges, whose
+  // K blocks hold at least a stage and whose extents fit in 31 bits.
   // More than 32 ragged 128x128 tiles per XCD stay with the 32-K stages, whose
   // 64 KiB let two workgroups share a CU (1920x5120x1792, 75 tiles: 44.7
   // against 51.5 us); up to 32 there is one per CU and the 64-K stages win
   // (1152x2048x3328, 18 tiles: 27.4 -> 26.5 us; 1024x3072x9984, 24 tiles:
   // 104.6 -> 88.3).
   const bool paired = !wide && !whole && g.tile_m == 128 && g.tile_n == 128 && f.map.tiles_per_xcd > 32;
-  const bool blocks = whole || (a.kslice >= kGemmBK64 && b.kslice >= kGemmBK64);
-  if (wide || (g.stage_k == 64 && g.waves == 8 && !full && fits && blocks && !paired)) {
+  const bool exists = whole || (fits && a.kslice >= kGemmBK64 && b.kslice >= kGemmBK64);
+  if (wide || (g.stage_k == 64 && g.waves == 8 && !full && exists && !paired)) {
     f.kernel = GemmKernel::K64;
     f.ragged = !whole;
+    f.far = whole && (!fits || g.far);
     f.stream_b = g.stream_b && remap && f.map.tiles_m == 1;
     if (whole) {
       f.ksteps = steps;

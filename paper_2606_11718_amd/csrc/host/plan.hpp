@@ -50,6 +50,7 @@ struct GemmConfig {
   int group_m = 0;                  // raster group height (tiles) inside a partition
   int waves = 4;                    // waves per workgroup (4 or 8)
   int stage_k = 32;                 // bf16: K extent of one LDS stage (32 or 64)
+  bool far = false;                 // bf16 64-K stages: the far form at any size (override)
   bool a_pairs = false;             // bf16 256x256: A staged in 64-K pairs (whole lines)
   bool fp8_pipe = false;            // fp8 256x256: fragment reads pipelined across steps
   bool stream_b = false;            // bf16 64-K stages: B read past the L2 (non-temporal)
@@ -154,6 +155,7 @@ struct GemmForm {
   int tile_m = 0, tile_n = 0, waves = 0;
   int splits = 1;                   // non-empty K ranges
   bool ragged = false;              // K64: stages that may straddle K blocks
+  bool far = false;                 // K64: operands of 2 GiB and more
   bool stream_b = false;            // K64: B read past the L2
   bool c_nt = false;                // C above the cache size: non-temporal stores
   int32_t ksteps = 0, ksteps_per_split = 0;   // in the kernel's K steps

@@ -988,6 +988,9 @@ __global__ void __launch_bounds__(128 * WGN, WGN / 2) gemm_kernel(GemmParams p) 
 // loaded by waves of their own (4-7), and a last half stage is filled with
 // zeros. The MFMAs and their order are the 32-K kernel's (C is identical
 // bit for bit).
+// FAR (whole K blocks only): operands whose tile spans 2 GiB or more over all
+// K blocks, beyond one descriptor's offsets. The descriptors' base moves by a
+// stage at a time.
 // ---------------------------------------------------------------------------
 
 constexpr int kBK64 = 64;        // K extent of one stage of gemm_k64_kernel
@@ -1026,9 +1029,10 @@ struct Tile64 {
   static_assert(BN == 128 || BN == 192 || BN == 256 || BN == 320, "B swizzle is defined for 16-, 24-, 32- and 40-chunk rows");
 };
 
-template <int BM, int BN, bool RAGGED, bool BNT>
-__global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
+template <int BM, int BN, bool RAGGED, bool BNT, bool FAR>
+__device__ __forceinline__ void k64_tile(const GemmParams& p) {
+  static_assert(!(RAGGED && FAR), "a ragged stage's jump to the next K block is a 31-bit offset");
   using T = Tile64<BM, BN>;
   constexpr int NS = T::NS;
   __shared__ __attribute__((aligned(1024))) char smA[NS][T::A_BYTES];
@@ -1110,9 +1114,11 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   // offset. Against descriptors rebuilt for every stage, which the ragged form
   // spent 300-800 clocks of a 1000-clock stage on: 1152x2048x3328 28.1 -> 26.5
   // us, 1024x3072x9984 79.3 -> 74.0; whole K blocks (rebuilt every fourth
-  // stage) measured the same ----
-  const int32_t a_extent = (int32_t)(((p.a_blocks - 1) * p.a.slice + (int64_t)(BM - 1) * p.a.ld + p.a.kslice) * 2);
-  const int32_t b_extent = (int32_t)(((p.b_blocks - 1) * p.b.slice + (int64_t)(p.b.kslice - 1) * p.b.ld + BN) * 2);
+  // stage) measured the same. FAR: a stage's own rows, from its corner ----
+  const int32_t a_extent = FAR ? (int32_t)(((int64_t)(BM - 1) * p.a.ld + kBK64) * 2)
+                               : (int32_t)(((p.a_blocks - 1) * p.a.slice + (int64_t)(BM - 1) * p.a.ld + p.a.kslice) * 2);
+  const int32_t b_extent = FAR ? (int32_t)(((int64_t)(kBK64 - 1) * p.b.ld + BN) * 2)
+                               : (int32_t)(((p.b_blocks - 1) * p.b.slice + (int64_t)(p.b.kslice - 1) * p.b.ld + BN) * 2);
   i32x4 a_desc = buffer_rsrc(p.A + pr * p.a.part + (int64_t)(ti * BM) * p.a.ld, a_extent);
   i32x4 b_desc = buffer_rsrc(p.B + pc * p.b.part + tj * BN, b_extent);
   // Position in units of kUnit K. RAGGED: B's is this wave's half of the stage.
@@ -1121,14 +1127,20 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   int32_t a_kl, b_kl;
   k_start(p.a, k0 * kUnit, &a_slice_off, &a_kl);
   k_start(p.b, kb * kUnit, &b_slice_off, &b_kl);
-  uint32_t a_so = (uint32_t)((a_slice_off + a_kl) * 2);
-  uint32_t b_so = (uint32_t)((b_slice_off + (int64_t)b_kl * p.b.ld) * 2);
+  // Byte position of the next stage: in the operand, or FAR in memory.
+  using Pos = std::conditional_t<FAR, uint64_t, uint32_t>;
+  Pos a_so = (Pos)((a_slice_off + a_kl) * 2);
+  Pos b_so = (Pos)((b_slice_off + (int64_t)b_kl * p.b.ld) * 2);
+  if constexpr (FAR) {
+    a_so += reinterpret_cast<uint64_t>(p.A + pr * p.a.part + (int64_t)(ti * BM) * p.a.ld);
+    b_so += reinterpret_cast<uint64_t>(p.B + pc * p.b.part + tj * BN);
+  }
   const int32_t a_steps = p.a.kslice / kUnit, b_steps = p.b.kslice / kUnit;
   int32_t a_left = a_steps - a_kl / kUnit, b_left = b_steps - b_kl / kUnit;
   constexpr int kStep = kBK64 / kUnit;          // units per stage
-  const uint32_t a_adv = kBK64 * 2, b_adv = (uint32_t)(kBK64 * p.b.ld * 2);
-  const uint32_t a_jump = (uint32_t)((p.a.slice - p.a.kslice) * 2);
-  const uint32_t b_jump = (uint32_t)((p.b.slice - (int64_t)p.b.kslice * p.b.ld) * 2);
+  const Pos a_adv = kBK64 * 2, b_adv = (Pos)((int64_t)kBK64 * p.b.ld * 2);
+  const Pos a_jump = (Pos)((p.a.slice - p.a.kslice) * 2);
+  const Pos b_jump = (Pos)((p.b.slice - (int64_t)p.b.kslice * p.b.ld) * 2);
 
   // Scalar offsets of a stage; da (RAGGED) is added to A's lanes of the
   // second 32 K: the jump where the first 32 K end a K block, or an offset
@@ -1139,8 +1151,16 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
   // The next stage, number s. Past the range the descriptors stay empty.
   auto next_src = [&](int32_t s, bool live) __attribute__((always_inline)) {
     StageSrc d;
-    d.sa = a_so;
-    d.sb = b_so;
+    if constexpr (FAR) {
+      a_desc[0] = (int)(uint32_t)a_so;
+      a_desc[1] = (int)((a_so >> 32) & 0xffffu);
+      b_desc[0] = (int)(uint32_t)b_so;
+      b_desc[1] = (int)((b_so >> 32) & 0xffffu);
+      d.sa = d.sb = 0;
+    } else {
+      d.sa = a_so;
+      d.sb = b_so;
+    }
     d.da = 0;
     if constexpr (RAGGED) {
       if (!live) {
@@ -1156,9 +1176,9 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
     a_left -= kStep;
     b_left -= kStep;
     const bool a_wrap = a_left <= 0, b_wrap = b_left <= 0;
-    a_so += a_adv + (a_wrap ? a_jump : 0u);
+    a_so += a_adv + (a_wrap ? a_jump : Pos(0));
     a_left += a_wrap ? a_steps : 0;
-    b_so += b_adv + (b_wrap ? b_jump : 0u);
+    b_so += b_adv + (b_wrap ? b_jump : Pos(0));
     b_left += b_wrap ? b_steps : 0;
     return d;
   };
@@ -1296,6 +1316,20 @@ __global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
                                                                     ti, tj, split, wm, wn, wave, lane);
   if (tl_on) record_timeline(p.timeline + ((int64_t)blockIdx.x * T::NW + wave) * kTimelineWords,
                              tl_rt, tl_clk, lane);
+}
+#endif
+
+template <int BM, int BN, bool RAGGED, bool BNT>
+__global__ void __launch_bounds__(512, 2) gemm_k64_kernel(GemmParams p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  k64_tile<BM, BN, RAGGED, BNT, false>(p);
+#endif
+}
+
+template <int BM, int BN, bool BNT>
+__global__ void __launch_bounds__(512, 2) gemm_k64_far_kernel(GemmParams p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  k64_tile<BM, BN, false, BNT, true>(p);
 #endif
 }
 
@@ -2875,7 +2909,18 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
     else if (f.stream_b) CCL_LAUNCH64_AS(BM_, BN_, true, true);           \
     else CCL_LAUNCH64_AS(BM_, BN_, true, false);                          \
   } while (0)
-      if (tile(128, 192)) CCL_LAUNCH64(128, 192);
+#define CCL_LAUNCH64_FAR(BM_, BN_)                                                                 \
+  do {                                                                                             \
+    if (f.stream_b)                                                                                \
+      hipLaunchKernelGGL((gemm_k64_far_kernel<BM_, BN_, true>), grid, dim3(Tile64<BM_, BN_>::THREADS), 0, stream, gp);  \
+    else                                                                                           \
+      hipLaunchKernelGGL((gemm_k64_far_kernel<BM_, BN_, false>), grid, dim3(Tile64<BM_, BN_>::THREADS), 0, stream, gp); \
+  } while (0)
+      if (f.far && tile(256, 128)) CCL_LAUNCH64_FAR(256, 128);
+      else if (f.far && tile(128, 256)) CCL_LAUNCH64_FAR(128, 256);
+      else if (f.far && tile(128, 128)) CCL_LAUNCH64_FAR(128, 128);
+      else if (f.far) return hipErrorInvalidValue;
+      else if (tile(128, 192)) CCL_LAUNCH64(128, 192);
       else if (tile(128, 320)) CCL_LAUNCH64(128, 320);
       else if (tile(256, 128)) CCL_LAUNCH64(256, 128);
       else if (tile(128, 256)) CCL_LAUNCH64(128, 256);
@@ -2883,6 +2928,7 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
       else return hipErrorInvalidValue;
 #undef CCL_LAUNCH64
 #undef CCL_LAUNCH64_AS
+#undef CCL_LAUNCH64_FAR
       break;
     case GemmKernel::A2:
       hipLaunchKernelGGL(gemm_a2_kernel, grid, dim3(TileA2::THREADS), 0, stream, gp);

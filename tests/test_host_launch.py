@@ -100,6 +100,25 @@ def test_c_leaves_the_cache_only_above_its_size(M, N, c, nt, ab):
     assert ccl.ccl_debug_launch(ccl.ccl_plan_typed(M, N, 1024, 8, 2, 4096, ab, c)).c_nt == nt
 
 
+@pytest.mark.parametrize("M,N,K,G,Gr,splits,far,stream", [
+    (128, 131072, 8192, 1, 1, 1, True, True),        # B of 2 GiB in one block: a vocabulary projection in decode
+    (128, 131072, 8192, 1, 1, 4, True, True),
+    (128, 130048, 8192, 1, 1, 1, False, True),
+    (128, 131072, 8192, 8, 1, 1, False, True),       # in 8 column blocks, one to a tile
+    (256, 262144, 8192, 8, 2, 1, True, False),       # in 2 x 4 blocks: a tile spans 5/8 of 4 GiB
+    (131072, 1024, 9728, 8, 1, 1, True, False),      # A in 8 K blocks
+    (131072, 128, 9728, 1, 1, 1, False, False),      # one K block of A: a tile spans 256 rows only
+])
+def test_64k_stages_above_two_gib(M, N, K, G, Gr, splits, far, stream):
+    run = ccl.ccl_debug_launch(ccl.ccl_plan(M, N, K, G, Gr, 4096), splits)
+    assert (run.kernel, run.ragged, run.far, run.stream_b) == ("gemm_k64_kernel", False, far, stream)
+
+
+def test_ragged_blocks_above_two_gib_keep_the_32k_kernel():
+    run = ccl.ccl_debug_launch(ccl.ccl_plan(128, 131072, 8224, 1, 1, 4096))      # 257 steps
+    assert (run.kernel, run.far) == ("gemm_kernel", False)
+
+
 def test_arguments():
     plan = ccl.ccl_plan(1024, 1024, 1024, 8, 2, 4096)
     for splits, operands in ((0, 0), (17, 0), (1, 3), (1, -1), (2, 1)):
