@@ -158,10 +158,12 @@ void choose_gemm_config(Plan* p) {
   // 48-64 B/clk per CU at the matrix cores' rate, so they take 64-K stages
   // (whole-line A rows). 256x256 keeps 32: two 64-K stages would leave one
   // step of load lookahead.
-  // CCL_GEMM_STAGE_K=32 selects the 32-K stages everywhere.
+  // CCL_GEMM_STAGE_K=32 selects the 32-K stages everywhere, 64 the 64-K ones
+  // wherever they exist (gemm_form has the rules for ragged K blocks).
   g.stage_k = (p->ab_type == DT_BF16 && g.waves == 8 && !(btm == 256 && btn == 256)) ? 64 : 32;
   const char* stage_env = std::getenv("CCL_GEMM_STAGE_K");
   const bool stage32 = stage_env && std::atoi(stage_env) == 32;
+  g.stage_64 = stage_env && std::atoi(stage_env) == 64;
   if (stage32) g.stage_k = 32;
   // CCL_GEMM_FAR=1 takes the form for operands of 2 GiB and more at any size.
   if (const char* e = std::getenv("CCL_GEMM_FAR")) g.far = std::atoi(e) == 1;
@@ -631,14 +633,25 @@ GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bo
   // stage lies in one K block, and operands of 2 GiB and more take the far
   // form; otherwise the ragged form, whose K ranges are the 32-K ranges, whose
   // K blocks hold at least a stage and whose extents fit in 31 bits.
-  // More than 32 ragged 128x128 tiles per XCD stay with the 32-K stages, whose
-  // 64 KiB let two workgroups share a CU (1920x5120x1792, 75 tiles: 44.7
-  // against 51.5 us); up to 32 there is one per CU and the 64-K stages win
-  // (1152x2048x3328, 18 tiles: 27.4 -> 26.5 us; 1024x3072x9984, 24 tiles:
-  // 104.6 -> 88.3).
-  const bool paired = !wide && !whole && g.tile_m == 128 && g.tile_n == 128 && f.map.tiles_per_xcd > 32;
+  // The ragged form adds to A's addresses what the next K block takes, which
+  // must pay for itself (us per launch, 32-K stages -> ragged 64-K ones):
+  //  * 128x128, up to 32 tiles per XCD, one per CU: it does (18 tiles,
+  //    1152x2048x3328: 27.4 -> 26.5; 24, 1024x3072x9984: 104.6 -> 88.3). Above
+  //    32, two workgroups of 32-K stages (64 KiB) share a CU: 33 to 105 tiles
+  //    take 6-25 % longer with 64-K stages at K up to 1056, the same at 2080
+  //    and 0-6 % less at 4128.
+  //  * 256x128: from about 2048 K on (24 tiles: K 544 11.5 -> 12.3, 1056 17.1
+  //    -> 17.9, 2080 30.8 -> 29.0, 4128 57.5 -> 52.7; 33 tiles: 22.1 -> 22.9,
+  //    34.8 -> 33.8, 60.7 -> 56.3, 118 -> 106).
+  //  * 128x256: not (8 to 90 tiles, K 224 to 8224: 0-10 % longer), unless the
+  //    operands exceed the Infinity Cache, where whole lines count (33 to 90
+  //    tiles, 3 to 9 tile rows of 22528, K 8448: 241 -> 220, 281 -> 242).
+  const int64_t range_k = (int64_t)f.ksteps_per_split * kGemmBK;
+  const bool ragged_pays =
+      g.tile_n == 256 ? (p.M + p.N) * p.K * e > kInfinityCacheBytes
+                      : g.tile_m == 256 ? range_k >= 1536 : f.map.tiles_per_xcd <= 32;
   const bool exists = whole || (fits && a.kslice >= kGemmBK64 && b.kslice >= kGemmBK64);
-  if (wide || (g.stage_k == 64 && g.waves == 8 && !full && exists && !paired)) {
+  if (wide || (g.stage_k == 64 && g.waves == 8 && !full && exists && (whole || ragged_pays || g.stage_64))) {
     f.kernel = GemmKernel::K64;
     f.ragged = !whole;
     f.far = whole && (!fits || g.far);

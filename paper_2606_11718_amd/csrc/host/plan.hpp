@@ -50,6 +50,7 @@ struct GemmConfig {
   int group_m = 0;                  // raster group height (tiles) inside a partition
   int waves = 4;                    // waves per workgroup (4 or 8)
   int stage_k = 32;                 // bf16: K extent of one LDS stage (32 or 64)
+  bool stage_64 = false;            // bf16 below 256x256: 64-K stages wherever they exist (override)
   bool far = false;                 // bf16 64-K stages: the far form at any size (override)
   bool a_pairs = false;             // bf16 256x256: A staged in 64-K pairs (whole lines)
   bool fp8_pipe = false;            // fp8 256x256: fragment reads pipelined across steps

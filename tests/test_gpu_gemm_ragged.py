@@ -1,7 +1,8 @@
 """bf16 GEMM tiles below 256x256 on K blocks and K ranges that are odd
-multiples of 32: the 64-K stages then straddle K blocks, and the last one may
-be half empty. Against the 32-K kernel (the same MFMAs in the same order, so
-bit for bit) and the oracle."""
+multiples of 32: the 64-K stages (CCL_GEMM_STAGE_K=64, as plans do not take
+them everywhere) then straddle K blocks, and the last one may be half empty.
+Against the 32-K kernel (the same MFMAs in the same order, so bit for bit) and
+the oracle. K blocks of one 32-K step have the 32-K kernel only."""
 import numpy as np
 import pytest
 
@@ -31,6 +32,14 @@ def _gemm(A, B, M, N, K, G, Gr):
     return OL.unpack(from_dev(Cd), M, N, gr, gc, 4096)
 
 
+def _stages(monkeypatch, k, M, N, K, G, Gr, splits=1):
+    """Plans with k-K stages from here on; checks that they run."""
+    monkeypatch.setenv("CCL_GEMM_STAGE_K", str(k))
+    run = ccl.ccl_debug_launch(ccl.ccl_plan(M, N, K, G, Gr, 4096), splits)
+    one_step = min(K // Gr, K // (G // Gr)) < 64
+    assert (run.kernel, run.ragged) == (("gemm_kernel", False) if k == 32 or one_step else ("gemm_k64_kernel", True))
+
+
 @pytest.mark.parametrize("tile", ["256x128", "128x256", "128x128"])
 @pytest.mark.parametrize("G,Gr,M,N,K", [
     (1, 1, 256, 256, 32), (1, 1, 256, 256, 96), (1, 1, 256, 256, 32 * 7), (1, 1, 256, 256, 32 * 19),
@@ -44,8 +53,9 @@ def test_equals_32k_stages(tile, G, Gr, M, N, K, monkeypatch):
     monkeypatch.setenv("CCL_GEMM_TILE", tile)
     A = W.draw_array(5500 + K, M, K, "normal", 1.0)
     B = W.draw_array(5501 + K, K, N, "normal", 0.05)
+    _stages(monkeypatch, 64, M, N, K, G, Gr)
     c64 = _gemm(A, B, M, N, K, G, Gr)
-    monkeypatch.setenv("CCL_GEMM_STAGE_K", "32")
+    _stages(monkeypatch, 32, M, N, K, G, Gr)
     c32 = _gemm(A, B, M, N, K, G, Gr)
     assert np.array_equal(c64, c32)
     assert OG.within_tolerance(OG.errors(OG.decode_bf16(c64), OG.gemm_fp64(A, B)))
@@ -60,8 +70,9 @@ def test_equals_32k_stages(tile, G, Gr, M, N, K, monkeypatch):
 def test_splitk_equals_32k_stages(M, N, K, G, Gr, splits, monkeypatch):
     A = _draw(BF16, 5600 + M + K, M, K)
     B = _draw(BF16, 5700 + N + K, K, N, "normal", 0.05)
+    _stages(monkeypatch, 64, M, N, K, G, Gr, splits)
     C64, r64 = run_splitk(A, B, M, N, K, G, Gr, BF16, FP32, splits)
-    monkeypatch.setenv("CCL_GEMM_STAGE_K", "32")
+    _stages(monkeypatch, 32, M, N, K, G, Gr, splits)
     C32, r32 = run_splitk(A, B, M, N, K, G, Gr, BF16, FP32, splits)
     assert r64 == r32
     assert np.array_equal(C64, C32)

@@ -119,6 +119,24 @@ def test_ragged_blocks_above_two_gib_keep_the_32k_kernel():
     assert (run.kernel, run.far) == ("gemm_kernel", False)
 
 
+@pytest.mark.parametrize("tile,M,N,K,G,Gr,ragged64", [
+    ("128x256", 256, 8192, 2304, 8, 1, False), ("128x256", 640, 12288, 4352, 8, 1, False),
+    ("128x256", 384, 22528, 8448, 8, 1, True),       # 387 MB
+    ("128x256", 2048, 1024, 8224, 1, 1, False),
+    ("256x128", 512, 4096, 768, 8, 1, False), ("256x128", 1024, 4096, 1280, 8, 1, False),
+    ("256x128", 1024, 4096, 1792, 8, 1, True), ("256x128", 1536, 1408, 2080, 1, 1, True),
+    ("128x128", 512, 8192, 768, 8, 1, True),         # 32 tiles per XCD
+    ("128x128", 384, 11264, 768, 8, 1, False),       # 33
+])
+def test_ragged_64k_stages_where_they_pay(tile, M, N, K, G, Gr, ragged64, monkeypatch):
+    monkeypatch.setenv("CCL_GEMM_TILE", tile)
+    run = ccl.ccl_debug_launch(ccl.ccl_plan(M, N, K, G, Gr, 4096))
+    assert (run.kernel, run.ragged) == (("gemm_k64_kernel", True) if ragged64 else ("gemm_kernel", False))
+    monkeypatch.setenv("CCL_GEMM_STAGE_K", "64")
+    run = ccl.ccl_debug_launch(ccl.ccl_plan(M, N, K, G, Gr, 4096))
+    assert (run.kernel, run.ragged) == ("gemm_k64_kernel", True)
+
+
 def test_arguments():
     plan = ccl.ccl_plan(1024, 1024, 1024, 8, 2, 4096)
     for splits, operands in ((0, 0), (17, 0), (1, 3), (1, -1), (2, 1)):
