@@ -22,9 +22,6 @@ namespace ccl {
 namespace {
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // one 16-byte chunk
-// The same at any byte address: gfx950 global memory accesses need no
-// alignment (one dwordx4 instruction either way).
-typedef u32x4 u32x4_any __attribute__((aligned(1)));
 
 // Workgroups of copy_stream_kernel's resident grid: 8 of 256 threads per CU
 // on 256 CUs (2048 measured best of 1024, 2048, 3072 and 4096).
@@ -79,16 +76,26 @@ __device__ __forceinline__ void unit_offsets(const PackArgs& a, uint32_t q, int6
   *ccl = EXACT ? (int64_t)q * US : (int64_t)row * a.row_bytes + col;
 }
 
-// Load / store one unit; NT = non-temporal (streaming) access.
-template <bool NT, typename T>
-__device__ __forceinline__ T ld(const T* p) {
-  if constexpr (NT) return __builtin_nontemporal_load(p);
-  else return *p;
+// Load / store one unit of type T; NT = non-temporal (streaming) access; ANY:
+// at any byte address, which gfx950 global accesses take in one instruction
+// like an aligned one. (A typedef of its own here: a template argument would
+// lose the attribute.)
+template <typename T, bool NT, bool ANY>
+__device__ __forceinline__ T ld(const char* p) {
+  typedef T any __attribute__((aligned(1)));
+  static_assert(alignof(any) == 1, "the compiler may not assume an alignment");
+  if constexpr (ANY && NT) return __builtin_nontemporal_load(reinterpret_cast<const any*>(p));
+  else if constexpr (ANY) return *reinterpret_cast<const any*>(p);
+  else if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const T*>(p));
+  else return *reinterpret_cast<const T*>(p);
 }
-template <bool NT, typename T>
-__device__ __forceinline__ void st(T* p, T v) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
+template <typename T, bool NT, bool ANY>
+__device__ __forceinline__ void st(char* p, T v) {
+  typedef T any __attribute__((aligned(1)));
+  if constexpr (ANY && NT) __builtin_nontemporal_store(v, reinterpret_cast<any*>(p));
+  else if constexpr (ANY) *reinterpret_cast<any*>(p) = v;
+  else if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<T*>(p));
+  else *reinterpret_cast<T*>(p) = v;
 }
 
 // Tensors above the Infinity Cache size, with streaming (non-temporal) loads
@@ -116,11 +123,11 @@ __global__ void __launch_bounds__(256) copy_kernel(PackArgs a) {
       int64_t rm, ccl;
       unit_offsets<sizeof(U), EXACT>(a, q, &rm, &ccl);
       to[u] = UNPACK ? rm : ccl;
-      if (ok[u]) v[u] = ld<true>(reinterpret_cast<const U*>(src + (UNPACK ? ccl : rm)));
+      if (ok[u]) v[u] = ld<U, true, true>(src + (UNPACK ? ccl : rm));
     }
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u)
-      if (ok[u]) st<true>(reinterpret_cast<U*>(dst + to[u]), v[u]);
+      if (ok[u]) st<U, true, true>(dst + to[u], v[u]);
   }
 }
 
@@ -151,7 +158,7 @@ __global__ void __launch_bounds__(256) copy_stream_kernel(PackArgs a) {
       if (q < a.units_per_block) {
         int64_t rm, ccl;
         unit_offsets<sizeof(U), EXACT>(a, q, &rm, &ccl);
-        v[u] = ld<true>(reinterpret_cast<const U*>(src + (UNPACK ? ccl : rm)));
+        v[u] = ld<U, true, true>(src + (UNPACK ? ccl : rm));
       }
     }
   };
@@ -162,7 +169,7 @@ __global__ void __launch_bounds__(256) copy_stream_kernel(PackArgs a) {
       if (q < a.units_per_block) {
         int64_t rm, ccl;
         unit_offsets<sizeof(U), EXACT>(a, q, &rm, &ccl);
-        *reinterpret_cast<U*>(dst + (UNPACK ? rm : ccl)) = v[u];
+        st<U, false, true>(dst + (UNPACK ? rm : ccl), v[u]);
       }
     }
   };
@@ -233,14 +240,13 @@ __global__ void __launch_bounds__(256) pack_trans_reg_kernel(TransArgs a, int32_
   if (wcb >= wb_cols) return;
   const int la = lane & 7, lb = lane >> 3;
   const int64_t R0 = (int64_t)by * WB, C0 = (int64_t)wcb * WB;
-  typedef std::conditional_t<RAGGED, u32x4_any, u32x4> chunk;
   if constexpr (RAGGED)
     if (R0 + EPC * la >= a.rows || C0 + EPC * lb >= a.cols) return;
   const E* src = reinterpret_cast<const E*>(a.src) + (C0 + EPC * lb) * a.ld + R0 + EPC * la;
   ev in[EPC];
 #pragma unroll
   for (int j = 0; j < EPC; ++j)
-    in[j] = __builtin_bit_cast(ev, (u32x4)ld<true>(reinterpret_cast<const chunk*>(src + j * a.ld)));
+    in[j] = __builtin_bit_cast(ev, ld<u32x4, true, RAGGED>(reinterpret_cast<const char*>(src + j * a.ld)));
   const uint32_t r = (uint32_t)R0 + (RAGGED ? EPC * la : 0), c = (uint32_t)C0 + (RAGGED ? EPC * lb : 0);
   const uint32_t pr = fdiv(r, a.div_hr), pc = fdiv(c, a.div_wc);
   E* strip = reinterpret_cast<E*>(a.dst + ((int64_t)pr * a.grid_c + pc) * a.strip);
@@ -250,7 +256,7 @@ __global__ void __launch_bounds__(256) pack_trans_reg_kernel(TransArgs a, int32_
     ev o;
 #pragma unroll
     for (int j = 0; j < EPC; ++j) o[j] = in[j][i];
-    st<NTS>(reinterpret_cast<chunk*>(dst + i * a.wc), (chunk)__builtin_bit_cast(u32x4, o));
+    st<u32x4, NTS, RAGGED>(reinterpret_cast<char*>(dst + i * a.wc), __builtin_bit_cast(u32x4, o));
   }
 }
 
@@ -261,7 +267,6 @@ __global__ void __launch_bounds__(256) pack_trans_reg_kernel(TransArgs a, int32_
 template <typename E>
 __global__ void __launch_bounds__(256) pack_trans_any_kernel(TransArgs a, uint32_t row_tiles,
                                                              uint32_t tiles) {
-  typedef E any_e __attribute__((aligned(1)));
   __shared__ E tile[64][64 + 4 / sizeof(E)];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x) {
@@ -271,7 +276,7 @@ __global__ void __launch_bounds__(256) pack_trans_any_kernel(TransArgs a, uint32
     for (int i = 0; i < 16; ++i) {
       const int c = i * 4 + wave;
       if (r0 + lane < a.rows && c0 + c < a.cols)
-        tile[c][lane] = *reinterpret_cast<const any_e*>(a.src + ((c0 + c) * a.ld + r0 + lane) * (int64_t)sizeof(E));
+        tile[c][lane] = ld<E, false, true>(a.src + ((c0 + c) * a.ld + r0 + lane) * (int64_t)sizeof(E));
     }
     __syncthreads();
     const int64_t col = c0 + lane;
@@ -283,8 +288,8 @@ __global__ void __launch_bounds__(256) pack_trans_any_kernel(TransArgs a, uint32
         if (row >= a.rows) continue;
         const uint32_t pr = fdiv((uint32_t)row, a.div_hr);
         char* strip = a.dst + ((int64_t)pr * a.grid_c + pc) * a.strip;
-        *reinterpret_cast<any_e*>(strip + ((row - pr * a.hr) * a.wc + col - pc * a.wc) * (int64_t)sizeof(E)) =
-            tile[lane][i * 4 + wave];
+        st<E, false, true>(strip + ((row - pr * a.hr) * a.wc + col - pc * a.wc) * (int64_t)sizeof(E),
+                           tile[lane][i * 4 + wave]);
       }
     }
     __syncthreads();
@@ -298,10 +303,6 @@ int grid_x_for(uint32_t units, int unroll) {
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
-
-typedef uint8_t u8_any __attribute__((aligned(1)));
-typedef uint16_t u16_any __attribute__((aligned(1)));
-typedef uint32_t u32_any __attribute__((aligned(1)));
 
 template <typename U, bool UNPACK, int UNROLL>
 void copy_stream_launch(dim3 grid, const PackArgs& a, bool exact, hipStream_t stream) {
@@ -392,13 +393,13 @@ hipError_t launch_copy(const Plan& p, int op, const void* rowmajor, int64_t ld, 
   // dimension 104 -> 50 us, in rows of 1025 elements 108 -> 60 us (unpack 109
   // -> 63), 4096x2048 12.8 -> 7.6 us.
   if (a.row_bytes >= 16)
-    copy_launch<u32x4_any>(L, a, unpack, stream);
+    copy_launch<u32x4>(L, a, unpack, stream);
   else if (e == 1)
-    copy_launch<u8_any>(L, a, unpack, stream);
+    copy_launch<uint8_t>(L, a, unpack, stream);
   else if (e == 2)
-    copy_launch<u16_any>(L, a, unpack, stream);
+    copy_launch<uint16_t>(L, a, unpack, stream);
   else
-    copy_launch<u32_any>(L, a, unpack, stream);
+    copy_launch<uint32_t>(L, a, unpack, stream);
   return hipGetLastError();
 }
 
