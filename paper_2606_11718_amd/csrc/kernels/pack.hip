@@ -199,6 +199,46 @@ struct TransArgs {
   DivMagic div_hr, div_wc;
 };
 
+// One element per thread, for small tensors, which wait on latency alone.
+template <typename E>
+__global__ void __launch_bounds__(256) pack_trans_scalar_kernel(TransArgs a, DivMagic div_cols) {
+  const uint32_t n = (uint32_t)a.rows * (uint32_t)a.cols;
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  if (i < n) {
+    const uint32_t r = fdiv(i, div_cols), c = i - r * div_cols.d;      // write order: along X rows
+    const uint32_t pr = fdiv(r, a.div_hr), pc = fdiv(c, a.div_wc);
+    char* strip = a.dst + ((int64_t)pr * a.grid_c + pc) * a.strip;
+    st<E, false, true>(strip + ((r - pr * a.hr) * a.wc + (c - pc * a.wc)) * (int64_t)sizeof(E),
+                       ld<E, false, true>(a.src + (c * a.ld + r) * (int64_t)sizeof(E)));
+  }
+}
+
+// fp8 through LDS, for blocks whose sides are multiples of 64 but not of the
+// register kernel's 128 below, and 16-byte aligned operands. A 64 x 64 tile is
+// read along X's rows (contiguous in src) in 16-byte chunks, transposed through
+// LDS and written in 16-byte chunks along X's columns. Tiles never straddle
+// blocks.
+__global__ void __launch_bounds__(256) pack_trans_lds_kernel(TransArgs a) {
+  __shared__ uint8_t tile[64][64 + 16];
+  const int64_t r0 = (int64_t)blockIdx.y * 64;        // X rows = src columns
+  const int64_t c0 = (int64_t)blockIdx.x * 64;        // X cols = src rows
+  const int line = threadIdx.x / 4, ch = threadIdx.x % 4;
+  const u32x4 in = ld<u32x4, false, false>(a.src + (c0 + line) * a.ld + r0 + ch * 16);
+  *reinterpret_cast<u32x4*>(&tile[line][ch * 16]) = in;
+  __syncthreads();
+  const int64_t pr = r0 / a.hr, pc = c0 / a.wc;
+  char* strip = a.dst + (pr * a.grid_c + pc) * a.strip;
+  u32x4 out;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t w = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w |= (uint32_t)tile[ch * 16 + 4 * q + j][line] << (8 * j);
+    out[q] = w;
+  }
+  st<u32x4, false, false>(strip + (r0 - pr * a.hr + line) * a.wc + (c0 - pc * a.wc) + ch * 16, out);
+}
+
 // Stored-transpose pack without LDS. With EPC elements per 16-byte chunk,
 // each thread moves an EPC x EPC block: it reads EPC chunks, one from each
 // of EPC consecutive rows of the stored transpose, transposes the block in
@@ -222,20 +262,20 @@ struct TransArgs {
 // one element per thread: 1152x3328 bf16 in 416-column blocks 19.4 -> 5.0 us
 // (odd leading dimension 20.7 -> 6.4), 4096x2112 fp8 37.0 -> 7.4.
 template <typename E, bool RAGGED, bool NTS>
-__global__ void __launch_bounds__(256) pack_trans_reg_kernel(TransArgs a, int32_t wb_cols) {
+__global__ void __launch_bounds__(256) pack_trans_reg_kernel(TransArgs a, int32_t wb_cols, int32_t y0) {
   constexpr int EPC = 16 / (int)sizeof(E);
   constexpr int WB = 8 * EPC;
   typedef E ev __attribute__((ext_vector_type(EPC)));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  // Row block by of column group bx: blockIdx.y skewed by 2 blocks per
-  // column group, so that the workgroups resident at one time read chunks
+  // Row block by of column group bx: y0 (of a launch of at most 65535 row
+  // blocks) plus blockIdx.y skewed by 2 blocks per column group, so that the workgroups resident at one time read chunks
   // spread over the width of the stored rows instead of one 8 KiB band of
   // them (a bijection for each bx). Measured from HBM against no skew:
   // 134 MB X^T 0.663-0.666 of 8 TB/s against 0.627-0.628, 470 MB W_up^T
   // 0.710 against 0.698-0.699; skews of 1, 3 and 4 were 0-1 % slower, 8
   // and 16 (several column groups then share a band) 4 % and 20 % slower.
-  const int32_t bx = blockIdx.x, by = (int32_t)((blockIdx.y + blockIdx.x * 2u) % gridDim.y);
+  const int32_t bx = blockIdx.x, by = y0 + (int32_t)((blockIdx.y + blockIdx.x * 2u) % gridDim.y);
   const int32_t wcb = bx * 4 + wave;
   if (wcb >= wb_cols) return;
   const int la = lane & 7, lb = lane >> 3;
@@ -355,21 +395,54 @@ template <typename E>
 void trans_launch(const Layout& L, const TransArgs& a, bool aligned, hipStream_t stream) {
   constexpr int EPC = 16 / (int)sizeof(E);
   constexpr int WB = 8 * EPC;         // block edge of a wave of the register kernel
-  const int32_t wb_cols = (int32_t)((L.cols + WB - 1) / WB);
-  const int64_t wb_rows = (L.rows + WB - 1) / WB;
-  const bool big = L.rows * L.cols * L.elem_bytes > kInfinityCacheBytes;
-  dim3 grid((unsigned)((wb_cols + 3) / 4), (unsigned)wb_rows);
-  if (aligned && L.block_rows % WB == 0 && L.block_cols % WB == 0 && wb_rows <= 65535) {
-    if (big) hipLaunchKernelGGL((pack_trans_reg_kernel<E, false, true>), grid, dim3(256), 0, stream, a, wb_cols);
-    else hipLaunchKernelGGL((pack_trans_reg_kernel<E, false, false>), grid, dim3(256), 0, stream, a, wb_cols);
-  } else if (L.block_rows % EPC == 0 && L.block_cols % EPC == 0 && wb_rows <= 65535) {
-    if (big) hipLaunchKernelGGL((pack_trans_reg_kernel<E, true, true>), grid, dim3(256), 0, stream, a, wb_cols);
-    else hipLaunchKernelGGL((pack_trans_reg_kernel<E, true, false>), grid, dim3(256), 0, stream, a, wb_cols);
-  } else {
-    const int64_t row_tiles = (L.rows + 63) / 64, tiles = row_tiles * ((L.cols + 63) / 64);
-    hipLaunchKernelGGL((pack_trans_any_kernel<E>), dim3((unsigned)std::min<int64_t>(tiles, 1 << 20)),
-                       dim3(256), 0, stream, a, (uint32_t)row_tiles, (uint32_t)tiles);
+  const int64_t n = L.rows * L.cols;
+  const auto blocks_of = [&](int m) { return L.block_rows % m == 0 && L.block_cols % m == 0; };
+  const bool whole = aligned && blocks_of(WB), chunks = blocks_of(EPC);
+  // Small tensors that the register kernel takes ragged or not at all: few of
+  // its waves, or of the tiles, wait out 16 / sizeof(E) or 16 loads in turn. Us,
+  // one element per thread -> register blocks or tiles: fp8 64 Ki elements 2.0
+  // -> 3.5, 512 Ki 3.5 -> 3.9 (but 1 Mi 5.8 -> 4.2), bf16 64 Ki 2.0 -> 2.6, 181 Ki
+  // 2.3 -> 2.8 (362 Ki 3.3 -> 2.9), fp32 tiles 64 Ki 2.0 -> 4.4, 724 Ki 4.6 -> 5.6
+  // (1448 Ki 10.5 -> 6.8); fp32 register blocks are as fast from the start.
+  const int64_t small = !chunks ? 7 << 17 : sizeof(E) == 1 ? 11 << 16 : sizeof(E) == 2 ? 1 << 18 : 0;
+  if (!whole && !(sizeof(E) == 1 && aligned && blocks_of(64)) && n <= small) {
+    hipLaunchKernelGGL((pack_trans_scalar_kernel<E>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a,
+                       make_div((uint32_t)L.cols));
+    return;
   }
+  if constexpr (sizeof(E) == 1) {
+    // Sides of 64 mod 128: 64 x 64 tiles, of which there are four for each wave
+    // block, up to 8 MiB. Us, tiles -> ragged register blocks: 64 KiB 2.0 -> 3.1,
+    // 1 MiB 2.3 -> 4.0, 4 MiB 3.6 -> 4.5, 8 MiB 5.3 -> 5.4, 14 MiB 7.9 -> 6.8.
+    // Above that where the tile columns are a multiple of the 8 XCDs: the two
+    // tiles that share each 128-byte line of src then run on one XCD (17 MB in
+    // 4608 columns 8.3 -> 11.2, 36 MB in 5120 13.3 -> 17.2, 45 MB in 10240 15.6 ->
+    // 18.7, 48 MB in 8192 17.2 -> 19.8; else 25 MB in 7040 13.3 -> 12.5, 60 MB in
+    // 12416 28.4 -> 24.3).
+    if (!whole && aligned && blocks_of(64) && L.rows / 64 <= 65535 && (n <= 8 << 20 || L.cols % 512 == 0)) {
+      hipLaunchKernelGGL(pack_trans_lds_kernel, dim3((unsigned)(L.cols / 64), (unsigned)(L.rows / 64)), dim3(256), 0,
+                         stream, a);
+      return;
+    }
+  }
+  if (whole || chunks) {
+    const int32_t wb_cols = (int32_t)((L.cols + WB - 1) / WB), wb_rows = (int32_t)((L.rows + WB - 1) / WB);
+    const bool big = n * (int64_t)sizeof(E) > kInfinityCacheBytes;
+    for (int32_t y0 = 0; y0 < wb_rows; y0 += 65535) {
+      const dim3 grid((unsigned)((wb_cols + 3) / 4), (unsigned)std::min(wb_rows - y0, 65535));
+#define CCL_REG(RAGGED_, NTS_) \
+  hipLaunchKernelGGL((pack_trans_reg_kernel<E, RAGGED_, NTS_>), grid, dim3(256), 0, stream, a, wb_cols, y0)
+      if (whole && big) CCL_REG(false, true);
+      else if (whole) CCL_REG(false, false);
+      else if (big) CCL_REG(true, true);
+      else CCL_REG(true, false);
+#undef CCL_REG
+    }
+    return;
+  }
+  const int64_t row_tiles = (L.rows + 63) / 64, tiles = row_tiles * ((L.cols + 63) / 64);
+  hipLaunchKernelGGL((pack_trans_any_kernel<E>), dim3((unsigned)std::min<int64_t>(tiles, 1 << 20)),
+                     dim3(256), 0, stream, a, (uint32_t)row_tiles, (uint32_t)tiles);
 }
 
 }  // namespace

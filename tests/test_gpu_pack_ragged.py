@@ -91,6 +91,29 @@ def test_stored_transpose(e, M, N, K, G, Gr, op, ld_extra, src_off, dst_off):
     _check(e, M, N, K, G, Gr, op, True, ld_extra, src_off, dst_off, False)
 
 
+@pytest.mark.parametrize("e,M,K,G", [
+    (1, 1024, 8 * 64, 8), (1, 8 * 192, 832, 1),       # fp8, sides of 64 mod 128: LDS tiles
+    (1, 2048, 8 * 576, 8), (1, 2048, 4544, 1),        # above 8 MiB: with and without 8 | tile columns
+    (1, 1024, 8 * 48, 8), (1, 4096, 8 * 48, 8),       # ragged blocks of few and of more elements
+    (2, 1024, 8 * 24, 8), (2, 1024, 8 * 40, 8),
+    (1, 768, 8 * 37, 8), (2, 1024, 8 * 111, 8), (4, 1024, 8 * 113, 8),   # neither: 917504 elements the most
+])
+def test_stored_transpose_by_size(e, M, K, G):
+    """Either side of the sizes where one kernel hands over to another."""
+    _check(e, -(-M // 128) * 128, 1024, K, G, 1, "A", True, 0, 0, 0, False)
+
+
+def test_stored_transpose_of_more_than_65535_row_blocks():
+    """fp32 blocks of 32 x 32 to a wave: the rows take two launches."""
+    torch = torch_mod()
+    M, K = 65536 * 32 + 128, 32
+    plan = ccl.ccl_plan_typed(M, 128, K, 1, 1, 4096, ccl.CCL_DT_FP32, ccl.CCL_DT_FP32)
+    src = torch.randint(-2**31, 2**31 - 1, (K, M), dtype=torch.int32, device="cuda")
+    dst = torch.zeros(ccl.ccl_plan_layout(plan, ccl.CCL_A).total_bytes // 4, dtype=torch.int32, device="cuda")
+    ccl.ccl_pack(plan, ccl.CCL_A, src, M, 1, dst)
+    assert torch.equal(dst[:M * K].view(M, K), src.t())
+
+
 def test_above_the_cache_size():
     """fp32 A of 269 MB in block rows of 1026 elements (4104 bytes)."""
     _check(4, 8192, 1024, 8 * 1026, 8, 1, "A", False, 1, 0, 0, True)
