@@ -100,10 +100,10 @@ __device__ __forceinline__ void st(char* p, T v) {
 
 // Tensors above the Infinity Cache size, with streaming (non-temporal) loads
 // and stores (measured: +10 % on a 470 MB copy, -15 % on a 134 MB one that
-// the cache holds). U = unit moved per access, at any byte address: 16 bytes,
-// or one element where rows are shorter than that. UNPACK = false: row-major
-// -> CCL; true: CCL -> row-major.
-template <typename U, bool UNPACK, bool EXACT>
+// the cache holds; NT = false: plain accesses). U = unit moved per access, at
+// any byte address: 16 bytes, or one element. UNPACK = false: row-major -> CCL;
+// true: CCL -> row-major.
+template <typename U, bool UNPACK, bool EXACT, bool NT>
 __global__ void __launch_bounds__(256) copy_kernel(PackArgs a) {
   const int32_t b = blockIdx.y;                      // strip / chiplet
   const int64_t pr = b / a.grid_c, pc = b % a.grid_c;
@@ -123,11 +123,11 @@ __global__ void __launch_bounds__(256) copy_kernel(PackArgs a) {
       int64_t rm, ccl;
       unit_offsets<sizeof(U), EXACT>(a, q, &rm, &ccl);
       to[u] = UNPACK ? rm : ccl;
-      if (ok[u]) v[u] = ld<U, true, true>(src + (UNPACK ? ccl : rm));
+      if (ok[u]) v[u] = ld<U, NT, true>(src + (UNPACK ? ccl : rm));
     }
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u)
-      if (ok[u]) st<U, true, true>(dst + to[u], v[u]);
+      if (ok[u]) st<U, NT, true>(dst + to[u], v[u]);
   }
 }
 
@@ -355,9 +355,9 @@ void copy_stream_launch(dim3 grid, const PackArgs& a, bool exact, hipStream_t st
 template <typename U, bool UNPACK>
 void copy_launch_as(dim3 grid, const PackArgs& a, bool big, int unroll, bool exact, hipStream_t stream) {
   if (big && exact)
-    hipLaunchKernelGGL((copy_kernel<U, UNPACK, true>), grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((copy_kernel<U, UNPACK, true, true>), grid, dim3(256), 0, stream, a);
   else if (big)
-    hipLaunchKernelGGL((copy_kernel<U, UNPACK, false>), grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((copy_kernel<U, UNPACK, false, true>), grid, dim3(256), 0, stream, a);
   else if (unroll == 1)
     copy_stream_launch<U, UNPACK, 1>(grid, a, exact, stream);
   else if (unroll == 2)
@@ -465,7 +465,20 @@ hipError_t launch_copy(const Plan& p, int op, const void* rowmajor, int64_t ld, 
   // Against one element per access: 8192x8192 bf16 with an odd leading
   // dimension 104 -> 50 us, in rows of 1025 elements 108 -> 60 us (unpack 109
   // -> 63), 4096x2048 12.8 -> 7.6 us.
-  if (a.row_bytes >= 16)
+  // fp32 rows off the 16-byte grid stay at one element per access where both
+  // sides fit in the Infinity Cache together but not in the L2s (8 x 4 MiB). Us,
+  // elements -> units, pack and unpack: 40 MB 14.6 -> 18.8 and 14.1 -> 18.1, 77 MB
+  // 26.5 -> 31.1 and 25.4 -> 31.7, 109 MB 36.0 -> 41.3 and 34.3 -> 41.6; outside,
+  // 24 MB 9.8 -> 8.6 and 9.6 -> 8.6, 150 MB 66.6 -> 49.0 and 58.9 -> 48.4.
+  const int64_t bytes = L.rows * L.cols * e;
+  const bool on_grid = (a.row_bytes | a.ld_bytes | a.strip) % 16 == 0 && aligned16(rowmajor) && aligned16(ccl_buf);
+  if (e == 4 && !on_grid && bytes > (32 << 20) && 2 * bytes <= kInfinityCacheBytes) {
+    a.units_per_block = (uint32_t)(L.block_rows * L.block_cols);
+    a.units_per_row = make_div((uint32_t)L.block_cols);
+    const dim3 grid(grid_x_for(a.units_per_block, 4), (unsigned)(L.grid_r * L.grid_c));
+    if (unpack) hipLaunchKernelGGL((copy_kernel<uint32_t, true, true, false>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((copy_kernel<uint32_t, false, true, false>), grid, dim3(256), 0, stream, a);
+  } else if (a.row_bytes >= 16)
     copy_launch<u32x4>(L, a, unpack, stream);
   else if (e == 1)
     copy_launch<uint8_t>(L, a, unpack, stream);

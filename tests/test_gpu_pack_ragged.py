@@ -114,6 +114,12 @@ def test_stored_transpose_of_more_than_65535_row_blocks():
     assert torch.equal(dst[:M * K].view(M, K), src.t())
 
 
+@pytest.mark.parametrize("rows,ld_extra,off", [(8192, 1, 0), (8320, 0, 1), (8192, 0, 0)])
+def test_fp32_above_the_l2s(rows, ld_extra, off):
+    """33 to 34 MB of fp32: one element per access off the 16-byte grid."""
+    _check(4, rows, 1024, 8 * 129 if off or ld_extra else 8 * 130, 8, 1, "A", False, ld_extra, off, 0, True)
+
+
 def test_above_the_cache_size():
     """fp32 A of 269 MB in block rows of 1026 elements (4104 bytes)."""
     _check(4, 8192, 1024, 8 * 1026, 8, 1, "A", False, 1, 0, 0, True)
