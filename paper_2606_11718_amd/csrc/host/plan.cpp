@@ -601,13 +601,20 @@ GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bo
   int32_t steps, per;
   if (fp8) {
     const bool whole = whole_steps(kGemmBK8x, &steps, &per);
+    // More than 32 split-K workgroups of 128x128 per XCD run the 32x32x64 kernel,
+    // two to a CU: short K ranges and fp32 partials wait on memory. Us, 128-K
+    // stages -> it: 9 tiles, K 2048, in 4 ranges 14.1 -> 12.9 (in 2 11.1 -> 11.5),
+    // 25 tiles in 2 ranges 21.6 -> 20.6, 63 tiles, K 4096, in 2 63.0 -> 53.7, in 4
+    // 77.0 -> 68.5. Unsplit launches of 33 to 165 tiles gain up to 15 %, or lose 3 %
+    // at 33 tiles, with 128-K stages.
+    const bool paired = f.splits > 1 && g.tile_m == 128 && g.tile_n == 128 && f.map.tiles_per_xcd > 32;
     // 256x256 tiles with 8 waves: the 16x16x128 kernels (no split-K), the
     // pipelined one where its descriptors reach. Below 256x256 (8 waves, the
     // plan's choice where both K blocks are multiples of 128): 128-K stages.
     // Other plans run the 32x32x64 kernel.
     if (full && f.splits == 1 && g.waves == 8 && whole) {
       f.kernel = g.fp8_pipe && fits ? GemmKernel::FP8P : GemmKernel::FP8X;
-    } else if (!full && g.waves == 8 && whole && fits) {
+    } else if (!full && g.waves == 8 && whole && fits && !paired) {
       f.kernel = GemmKernel::FP8S;
     } else {
       f.kernel = GemmKernel::FP8;

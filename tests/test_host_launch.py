@@ -137,6 +137,16 @@ def test_ragged_64k_stages_where_they_pay(tile, M, N, K, G, Gr, ragged64, monkey
     assert (run.kernel, run.ragged) == ("gemm_k64_kernel", True)
 
 
+@pytest.mark.parametrize("N,K,splits,kernel", [
+    (3072, 2048, 2, "gemm_fp8s_kernel"), (3072, 2048, 4, "gemm_fp8_kernel"),        # 18 and 36 workgroups per XCD
+    (5120, 2048, 2, "gemm_fp8s_kernel"), (5120, 4096, 4, "gemm_fp8_kernel"),        # 30 and 60
+    (11264, 2048, 1, "gemm_fp8s_kernel")])
+def test_fp8_split_ranges_share_cus(N, K, splits, kernel):
+    plan = ccl.ccl_plan_typed(384, N, K, 8, 1, 4096, FP8, BF16)
+    run = ccl.ccl_debug_launch(plan, splits)
+    assert (run.tile_rows, run.tile_cols, run.kernel, run.waves) == (128, 128, kernel, 4 if kernel == "gemm_fp8_kernel" else 8)
+
+
 def test_arguments():
     plan = ccl.ccl_plan(1024, 1024, 1024, 8, 2, 4096)
     for splits, operands in ((0, 0), (17, 0), (1, 3), (1, -1), (2, 1)):
