@@ -377,7 +377,7 @@ typedef struct ccl_launch {
   int ragged;           /* 64-K stages that may straddle K blocks */
   int far;              /* 64-K stages of operands of 2 GiB and more */
   int stream_b;         /* B read past the L2 */
-  int c_nt;             /* C stored non-temporally for its size */
+  int c_nt;             /* C stored non-temporally for its and the operands' size */
 } ccl_launch;
 
 /* The launch of ccl_gemm / ccl_gemm_scaled (splits 1, operands 0), of

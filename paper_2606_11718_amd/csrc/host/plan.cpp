@@ -570,17 +570,18 @@ GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bo
   f.ksteps = (int32_t)gemm_ksteps(p);
   f.ksteps_per_split = (f.ksteps + f.splits - 1) / f.splits;
   // Non-temporal stores of C: always for a bf16 C of the pipelined fp8 kernel
-  // (1-4 % faster at the power limit) and where B streams; elsewhere, in the
-  // 64- and 128-K-stage kernels and for every fp32 C, where C is above the
-  // Infinity Cache size. Below it what reads C next (the unpack, the next GEMM
-  // or the next accumulation) finds it in the cache: whole passes,
-  // 4096x1536x2048 44.9 -> 44.2 us, 4096x768x2048 30.2 -> 29.5, 256x512x256
-  // 10.7 -> 10.4, fp32 C 2048x4096x1024 39.4 -> 36.1 and 5888x1024x1024 36.1 ->
-  // 33.5, while the GEMM alone may take up to 15 % longer. An fp32 C counts
-  // from that size on: fp8 8192x8192x1024 (256 MiB) takes 176 us a pass, 192
-  // with plain stores. The decode FFN, whose launches stream their weights,
-  // takes 198.6 us with these, 200.1 with plain ones.
-  f.c_nt = p.c_type == DT_FP32 ? p.M * p.N * 4 >= kInfinityCacheBytes : p.M * p.N * 2 > kInfinityCacheBytes;
+  // (1-4 % faster at the power limit) and where B streams; elsewhere, for a bf16
+  // C of the 64- and 128-K-stage kernels, where operands and C together exceed
+  // the Infinity Cache. Below that what reads C next (the unpack or the next
+  // GEMM) finds it in the cache, and the operands stay too: whole passes of
+  // pack, GEMM and unpack, non-temporal -> plain, 4096x1536x2048 42.1 -> 40.2 us,
+  // 4096x768x2048 29.2 -> 28.4, 256x512x256 10.7 -> 10.4, while the launch alone
+  // takes 0-12 % longer. Above it plain stores push the operands out:
+  // 640x16384x7168 161.5 -> 172.6, 384x28672x4096 105.4 -> 111.1.
+  // An fp32 C, in every kernel, from the cache's size on: 2048x4096x1024 39.4 ->
+  // 36.1, 5888x1024x1024 36.1 -> 33.5, but fp8 8192x8192x1024 (256 MiB) 176 -> 192.
+  f.c_nt = p.c_type == DT_FP32 ? p.M * p.N * 4 >= kInfinityCacheBytes
+                               : (p.M * p.K + p.K * p.N) * e + p.M * p.N * 2 > kInfinityCacheBytes;
   const auto set_grid = [&] {
     f.workgroups = remap ? 8 * (int64_t)f.map.tiles_per_xcd : (int64_t)f.map.tiles_m * f.map.tiles_n * p.G;
   };

@@ -158,7 +158,7 @@ struct GemmForm {
   bool ragged = false;              // K64: stages that may straddle K blocks
   bool far = false;                 // K64: operands of 2 GiB and more
   bool stream_b = false;            // K64: B read past the L2
-  bool c_nt = false;                // C above the cache size: non-temporal stores
+  bool c_nt = false;                // C (and operands) above the cache size: non-temporal stores
   int32_t ksteps = 0, ksteps_per_split = 0;   // in the kernel's K steps
   TileMap map;
   int64_t workgroups = 0;

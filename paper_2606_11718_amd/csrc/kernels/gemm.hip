@@ -405,6 +405,20 @@ struct RowAccess {
   }
 };
 
+// f with non-temporal stores or with plain ones, chosen at run time. The two
+// calls' code must not be alike at either end: the compiler merges a store of
+// one branch with that of the other into a plain one.
+template <typename F>
+__device__ __forceinline__ void choose_nt(int32_t nt, F&& f) {
+  if (nt) {
+    asm volatile("; non-temporal");
+    f(std::true_type{});
+    asm volatile("; non-temporal end");
+  } else {
+    f(std::false_type{});
+  }
+}
+
 // Epilogue of the kernels with 16x16 MFMA tiles (bf16, fp8 16x16x128) for a
 // bf16 C that is not read (beta 0, no split-K), staged through LDS so that C
 // leaves the CU in whole 128-byte lines. The direct form (store_tile) writes 8 bytes per lane, i.e. 32-byte
@@ -459,16 +473,25 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const f32
   asm volatile("" ::: "memory");
   uint16_t* C = static_cast<uint16_t*>(p.C) + pr * p.c.part + pc * p.c.slice +
                 (int64_t)(ti * BM) * p.c.ld + tj * BN;
-#pragma unroll
-  for (int i = 0; i < RPW * CPR / 64; ++i) {
+  auto copy_out = [&](int i, auto nt) __attribute__((always_inline)) {
     const int row = wave * RPW + X::row(i, lane), c = X::col(i, lane);
     const int r = row % HALF;
     const uint4 v = *reinterpret_cast<const uint4*>((row < HALF ? lo : hi) + r * ROWB + ((c ^ swz(r)) << 4));
     uint4* dst = reinterpret_cast<uint4*>(C + (int64_t)row * p.c.ld + c * 8);
-    if (NT == 2 || (NT == 1 && p.c_nt))
+    if constexpr (decltype(nt)::value)
       __builtin_nontemporal_store(__builtin_bit_cast(i32x4, v), reinterpret_cast<i32x4*>(dst));
     else
       *dst = v;
+  };
+  constexpr int kCopies = RPW * CPR / 64;
+  if constexpr (NT == 1) {
+    choose_nt(p.c_nt, [&](auto nt) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < kCopies; ++i) copy_out(i, nt);
+    });
+  } else {
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) copy_out(i, std::bool_constant<NT == 2>{});
   }
 }
 
@@ -546,8 +569,7 @@ __device__ __forceinline__ void store_tile_staged_f32(const GemmParams& p, const
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
+    auto copy_out = [&](int i, auto nt) __attribute__((always_inline)) {
       const int row = row0 + X::row(i, lane), c = X::col(i, lane);
       const int r = row < RP ? row : row - RP;
       f32x4 o = *reinterpret_cast<const f32x4*>((row < RP ? lo : hi) + r * ROWB + ((c ^ (r & 15)) << 4));
@@ -560,7 +582,7 @@ __device__ __forceinline__ void store_tile_staged_f32(const GemmParams& p, const
       const int64_t idx = at + (int64_t)X::row(i, lane) * p.c.ld + 4 * c;
       if constexpr (F32) {
         f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + idx);
-        if (p.c_nt) __builtin_nontemporal_store(o, dst);
+        if constexpr (decltype(nt)::value) __builtin_nontemporal_store(o, dst);
         else *dst = o;
       } else {
         uint2 v;
@@ -568,6 +590,15 @@ __device__ __forceinline__ void store_tile_staged_f32(const GemmParams& p, const
         v.y = bf16_rne(o[2]) | (bf16_rne(o[3]) << 16);
         *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.C) + idx) = v;
       }
+    };
+    if constexpr (F32) {
+      choose_nt(p.c_nt, [&](auto nt) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) copy_out(i, nt);
+      });
+    } else {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) copy_out(i, std::false_type{});
     }
     if (ps + 1 < P) {
       __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));

@@ -41,3 +41,15 @@ def test_four_wave_kernel_spills_no_more_than_its_k_loop_needs(asm):  # noqa: F8
     name = "_ZN3ccl12_GLOBAL__N_111gemm_kernelILi256ELi256ELi2EEEvNS0_10GemmParamsE"
     size = re.search(rf"\.name:\s+{name}\n\s+\.private_segment_fixed_size:\s+(\d+)", asm)
     assert int(size.group(1)) <= 88
+
+
+@pytest.mark.parametrize("name", [
+    "15gemm_k64_kernelILi128ELi128ELb0ELb0EEEv", "15gemm_k64_kernelILi256ELi128ELb0ELb0EEEv",
+    "15gemm_k64_kernelILi128ELi320ELb1ELb0EEEv", "16gemm_fp8s_kernelILi256ELi128ELi4ELi2EEEv",
+    "14gemm_a2_kernelE", "11gemm_kernelILi256ELi256ELi4EEEv", "16gemm_fp8p_kernelE"])
+def test_store_policy_of_c_stays_a_choice(asm, name):  # noqa: F811
+    """C's non-temporal stores where the launch asks for them beside plain ones:
+    alike, the compiler merges the two into a plain store."""
+    name = re.search(rf"^(_ZN3ccl12_GLOBAL__N_1{name}\w*):", asm, re.M).group(1)
+    stores = [ln for ln in _body(asm, name) if ln.startswith("global_store_dwordx4")]
+    assert any(ln.endswith(" nt") for ln in stores) and any(not ln.endswith(" nt") for ln in stores)

@@ -94,9 +94,10 @@ def test_b_streams_where_one_workgroup_reads_it(M, N, K, G, Gr, stream, monkeypa
 @pytest.mark.parametrize("M,N,c,nt", [
     (2048, 4096, FP32, False), (8192, 4096, FP32, False), (8192, 8192 - 128 * 8, FP32, False),
     (8192, 8192, FP32, True), (8192, 28672, FP32, True),
-    (8192, 16384, BF16, False), (8192, 28672, BF16, True)])
+    (8192, 12288, BF16, False), (8192, 16384, BF16, True), (8192, 28672, BF16, True)])
 @pytest.mark.parametrize("ab", [BF16, FP8])
 def test_c_leaves_the_cache_only_above_its_size(M, N, c, nt, ab):
+    """An fp32 C counts alone, a bf16 C together with the operands (K 1024)."""
     assert ccl.ccl_debug_launch(ccl.ccl_plan_typed(M, N, 1024, 8, 2, 4096, ab, c)).c_nt == nt
 
 
