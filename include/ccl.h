@@ -382,9 +382,10 @@ typedef struct ccl_launch {
 
 /* The launch of ccl_gemm / ccl_gemm_scaled (splits 1, operands 0), of
  * ccl_gemm_splitk with `splits` K ranges (1..16, operands 0), or of
- * ccl_gemm_rowmajor with remap 0 or 1 (splits 1, operands 1 or 2). Errors:
- * CCL_ERR_INVALID_ARG; CCL_ERR_UNSUPPORTED as ccl_gemm. */
-ccl_status ccl_debug_launch(ccl_plan_t plan, int splits, int operands, ccl_launch* out);
+ * ccl_gemm_rowmajor with remap 0 or 1 (splits 1, operands 1 or 2); reads_c:
+ * with beta != 0 (operands 0). Errors: CCL_ERR_INVALID_ARG;
+ * CCL_ERR_UNSUPPORTED as ccl_gemm. */
+ccl_status ccl_debug_launch(ccl_plan_t plan, int splits, int operands, int reads_c, ccl_launch* out);
 
 /* ccl_debug_tile_of_wg for ccl_gemm's own launch. */
 ccl_status ccl_debug_launch_tile_of_wg(ccl_plan_t plan, int64_t wg, int* xcd, int64_t* tile_m,

@@ -107,7 +107,7 @@ def library() -> ctypes.CDLL:
         "ccl_debug_gemm_config": [vp, ctypes.POINTER(i32), ctypes.POINTER(i32), ctypes.POINTER(i64)],
         "ccl_debug_dispatch": [vp, vp, vp],
         "ccl_debug_gemm_timeline": [vp, vp, vp, vp, vp, i64, vp],
-        "ccl_debug_launch": [vp, i32, i32, ctypes.POINTER(_Launch)],
+        "ccl_debug_launch": [vp, i32, i32, i32, ctypes.POINTER(_Launch)],
         "ccl_debug_launch_tile_of_wg": [vp, i64, ctypes.POINTER(i32), ctypes.POINTER(i64), ctypes.POINTER(i64)],
         "ccl_debug_launch_dispatch": [vp, vp, vp],
         "ccl_debug_launch_timeline": [vp, vp, vp, vp, vp, i64, vp],
@@ -329,9 +329,9 @@ class Launch:
     c_nt: bool
 
 
-def ccl_debug_launch(plan: Plan, splits: int = 1, operands: int = 0) -> Launch:
+def ccl_debug_launch(plan: Plan, splits: int = 1, operands: int = 0, reads_c: int = 0) -> Launch:
     out = _Launch()
-    _check(library().ccl_debug_launch(plan, splits, operands, ctypes.byref(out)))
+    _check(library().ccl_debug_launch(plan, splits, operands, reads_c, ctypes.byref(out)))
     return Launch(out.kernel.decode(), out.workgroups, out.tile_rows, out.tile_cols, out.waves, out.k_ranges,
                   bool(out.ragged), bool(out.far), bool(out.stream_b), bool(out.c_nt))
 

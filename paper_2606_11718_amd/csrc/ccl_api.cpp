@@ -385,16 +385,18 @@ ccl_status ccl_debug_gemm_config(ccl_plan_t plan, int* tile_rows, int* tile_cols
   return ok();
 }
 
-ccl_status ccl_debug_launch(ccl_plan_t plan, int splits, int operands, ccl_launch* out) {
+ccl_status ccl_debug_launch(ccl_plan_t plan, int splits, int operands, int reads_c, ccl_launch* out) {
   if (!plan || !out) return fail(CCL_ERR_INVALID_ARG, "NULL argument");
   const ccl::Plan& p = plan->plan;
   if (!p.gemm.supported) return fail(CCL_ERR_UNSUPPORTED, p.gemm.why_unsupported);
   if (splits < 1 || splits > ccl::kMaxSplits || operands < 0 || operands > 2 || (operands && splits > 1))
     return fail(CCL_ERR_INVALID_ARG, "splits must be in 1..16 (1 for row-major operands), operands in 0..2");
+  if (reads_c != 0 && (reads_c != 1 || operands))
+    return fail(CCL_ERR_INVALID_ARG, "reads_c must be 0 or 1, 0 for row-major operands");
   ccl::OperandAddr a, b, c;
   if (operands) ccl::rowmajor_addressing(p, &a, &b, &c);
   else ccl::ccl_addressing(p, &a, &b, &c);
-  const ccl::GemmForm f = ccl::gemm_form(p, a, b, operands != 1, splits);
+  const ccl::GemmForm f = ccl::gemm_form(p, a, b, operands != 1, splits, reads_c == 1);
   std::memset(out, 0, sizeof(*out));
   std::strncpy(out->kernel, ccl::kernel_name(f.kernel), sizeof(out->kernel) - 1);
   out->workgroups = f.workgroups;

@@ -556,7 +556,8 @@ const char* kernel_name(GemmKernel k) {
   return "";
 }
 
-GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bool remap, int splits) {
+GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bool remap, int splits,
+                   bool reads_c) {
   const GemmConfig& g = p.gemm;
   const bool fp8 = p.ab_type == DT_FP8_E4M3;
   const int64_t e = fp8 ? 1 : 2;
@@ -603,12 +604,16 @@ GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bo
   if (fp8) {
     const bool whole = whole_steps(kGemmBK8x, &steps, &per);
     // More than 32 split-K workgroups of 128x128 per XCD run the 32x32x64 kernel,
-    // two to a CU: short K ranges and fp32 partials wait on memory. Us, 128-K
+    // two to a CU: short K ranges and fp32 stores wait on memory. Us, 128-K
     // stages -> it: 9 tiles, K 2048, in 4 ranges 14.1 -> 12.9 (in 2 11.1 -> 11.5),
     // 25 tiles in 2 ranges 21.6 -> 20.6, 63 tiles, K 4096, in 2 63.0 -> 53.7, in 4
-    // 77.0 -> 68.5. Unsplit launches of 33 to 165 tiles gain up to 15 %, or lose 3 %
-    // at 33 tiles, with 128-K stages.
-    const bool paired = f.splits > 1 && g.tile_m == 128 && g.tile_n == 128 && f.map.tiles_per_xcd > 32;
+    // 77.0 -> 68.5. So do unsplit launches that write an fp32 C without reading
+    // it, up to K 2048: pack, GEMM and unpack, 63 tiles, K 256 31.0 -> 28.5, K 1024
+    // 37.1 -> 33.3, 273 tiles, K 2048 168 -> 155 (45 tiles 37.0 -> 38.0). With a
+    // bf16 C they gain up to 15 % from 128-K stages, or lose 3 % at 33 tiles, and
+    // with an fp32 C that is read 4-29 %.
+    const bool partials = f.splits > 1 || (p.c_type == DT_FP32 && !reads_c && p.K <= 2048);
+    const bool paired = partials && g.tile_m == 128 && g.tile_n == 128 && f.map.tiles_per_xcd > 32;
     // 256x256 tiles with 8 waves: the 16x16x128 kernels (no split-K), the
     // pipelined one where its descriptors reach. Below 256x256 (8 waves, the
     // plan's choice where both K blocks are multiples of 128): 128-K stages.

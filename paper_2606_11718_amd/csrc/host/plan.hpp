@@ -163,7 +163,8 @@ struct GemmForm {
   TileMap map;
   int64_t workgroups = 0;
 };
-GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bool remap, int splits);
+GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bool remap, int splits,
+                   bool reads_c = false);
 const char* kernel_name(GemmKernel k);
 
 // tile_of_wg of an unsplit ccl_gemm's own launch.

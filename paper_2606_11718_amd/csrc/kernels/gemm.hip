@@ -2857,7 +2857,7 @@ hipError_t launch_gemm(const Plan& p, const void* A, const void* B, void* C,
                        bool remap, float alpha, float beta, int splits, float* ws,
                        hipStream_t stream, uint64_t* timeline) {
   if (splits < 1 || (splits > 1 && (!remap || !ws))) return hipErrorInvalidValue;
-  const GemmForm f = gemm_form(p, a, b, remap, splits);
+  const GemmForm f = gemm_form(p, a, b, remap, splits, beta != 0.f);
   if (timeline && (p.ab_type != DT_BF16 || f.splits > 1)) return hipErrorInvalidValue;   // bf16 kernels only
   GemmParams gp;
   gp.timeline = timeline;

@@ -148,10 +148,22 @@ def test_fp8_split_ranges_share_cus(N, K, splits, kernel):
     assert (run.tile_rows, run.tile_cols, run.kernel, run.waves) == (128, 128, kernel, 4 if kernel == "gemm_fp8_kernel" else 8)
 
 
+@pytest.mark.parametrize("N,K,c,reads_c,kernel", [
+    (9216, 1024, FP32, 0, "gemm_fp8_kernel"), (9216, 1024, FP32, 1, "gemm_fp8s_kernel"),     # 45 tiles per XCD
+    (9216, 2048, FP32, 0, "gemm_fp8_kernel"), (9216, 3072, FP32, 0, "gemm_fp8s_kernel"),
+    (9216, 1024, BF16, 0, "gemm_fp8s_kernel"), (5120, 1024, FP32, 0, "gemm_fp8s_kernel")])   # 25 tiles
+def test_fp8_tiles_with_an_fp32_c_share_cus(N, K, c, reads_c, kernel):
+    run = ccl.ccl_debug_launch(ccl.ccl_plan_typed(640, N, K, 8, 1, 4096, FP8, c), reads_c=reads_c)
+    assert (run.tile_rows, run.tile_cols, run.kernel) == (128, 128, kernel)
+
+
 def test_arguments():
     plan = ccl.ccl_plan(1024, 1024, 1024, 8, 2, 4096)
     for splits, operands in ((0, 0), (17, 0), (1, 3), (1, -1), (2, 1)):
         with pytest.raises(ccl.CCLError, match="CCL_ERR_INVALID_ARG"):
             ccl.ccl_debug_launch(plan, splits, operands)
+    for operands, reads_c in ((0, 2), (0, -1), (1, 1)):
+        with pytest.raises(ccl.CCLError, match="CCL_ERR_INVALID_ARG"):
+            ccl.ccl_debug_launch(plan, 1, operands, reads_c)
     with pytest.raises(ccl.CCLError, match="CCL_ERR_UNSUPPORTED"):
         ccl.ccl_debug_launch(ccl.ccl_plan_typed(384, 768, 384, 3, 1, 4096, BF16, BF16))
