@@ -659,10 +659,16 @@ GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bo
   //  * 128x256: not (8 to 90 tiles, K 224 to 8224: 0-10 % longer), unless the
   //    operands exceed the Infinity Cache, where whole lines count (33 to 90
   //    tiles, 3 to 9 tile rows of 22528, K 8448: 241 -> 220, 281 -> 242).
+  //  * not where only the K ranges are odd: every second one starts in the middle
+  //    of A's 128-byte lines (2 to 9 tiles, K 6016 in 3 ranges of 63 steps: 20.5
+  //    -> 21.6, 24.1 -> 25.2).
+  const bool blocks_whole = a.kslice % kGemmBK64 == 0 && b.kslice % kGemmBK64 == 0;
   const int64_t range_k = (int64_t)f.ksteps_per_split * kGemmBK;
   const bool ragged_pays =
-      g.tile_n == 256 ? (p.M + p.N) * p.K * e > kInfinityCacheBytes
-                      : g.tile_m == 256 ? range_k >= 1536 : f.map.tiles_per_xcd <= 32;
+      !blocks_whole &&
+      (g.tile_n == 256   ? (p.M + p.N) * p.K * e > kInfinityCacheBytes
+       : g.tile_m == 256 ? range_k >= 1536
+                         : f.map.tiles_per_xcd <= 32);
   const bool exists = whole || (fits && a.kslice >= kGemmBK64 && b.kslice >= kGemmBK64);
   if (wide || (g.stage_k == 64 && g.waves == 8 && !full && exists && (whole || ragged_pays || g.stage_64))) {
     f.kernel = GemmKernel::K64;

@@ -157,6 +157,13 @@ def test_fp8_tiles_with_an_fp32_c_share_cus(N, K, c, reads_c, kernel):
     assert (run.tile_rows, run.tile_cols, run.kernel) == (128, 128, kernel)
 
 
+def test_odd_k_ranges_of_whole_blocks_keep_32k_stages():
+    plan = ccl.ccl_plan(2048, 256, 6016, 4, 2, 4096)
+    assert ccl.ccl_debug_launch(plan, 3).kernel == "gemm_kernel"           # 63 steps
+    run = ccl.ccl_debug_launch(plan, 2)                                    # 94
+    assert (run.kernel, run.ragged) == ("gemm_k64_kernel", False)
+
+
 def test_arguments():
     plan = ccl.ccl_plan(1024, 1024, 1024, 8, 2, 4096)
     for splits, operands in ((0, 0), (17, 0), (1, 3), (1, -1), (2, 1)):
