@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("pad", [0, 3])
 @pytest.mark.parametrize("G,M,K", [
-    (1, 128, 16), (1, 2048, 2048), (1, 2048, 2056), (1, 2048, 4096), (1, 2048, 4104), (1, 2048, 2042),
+    (1, 128, 16), (1, 1536, 2048), (1, 1536, 2056), (1, 2048, 2048), (1, 2048, 2056), (1, 2048, 4096), (1, 2048, 4104), (1, 2048, 2042),
     (8, 128, 16384), (8, 128, 8 * 2052), (8, 2048, 8 * 260), (8, 4096, 8 * 260)])
 def test_pack_and_back(G, M, K, pad):
     plan = ccl.ccl_plan(M, 128 * G, K, G, 1, 4096)
