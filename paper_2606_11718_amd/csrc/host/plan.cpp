@@ -579,10 +579,14 @@ GemmForm gemm_form(const Plan& p, const OperandAddr& a, const OperandAddr& b, bo
   // 4096x768x2048 29.2 -> 28.4, 256x512x256 10.7 -> 10.4, while the launch alone
   // takes 0-12 % longer. Above it plain stores push the operands out:
   // 640x16384x7168 161.5 -> 172.6, 384x28672x4096 105.4 -> 111.1.
+  // Row-major C in native tile order (each XCD writes stretches of every row)
+  // always goes past the cache: the launch alone 4480x5120x512 40.8 -> 33.5 us,
+  // 1920x14336x256 37.3 -> 32.0, with a reader behind it 55.5 -> 51.1 and 52.9 ->
+  // 51.6, up to 12 MB 0-5 % longer.
   // An fp32 C, in every kernel, from the cache's size on: 2048x4096x1024 39.4 ->
   // 36.1, 5888x1024x1024 36.1 -> 33.5, but fp8 8192x8192x1024 (256 MiB) 176 -> 192.
   f.c_nt = p.c_type == DT_FP32 ? p.M * p.N * 4 >= kInfinityCacheBytes
-                               : (p.M * p.K + p.K * p.N) * e + p.M * p.N * 2 > kInfinityCacheBytes;
+                               : !remap || (p.M * p.K + p.K * p.N) * e + p.M * p.N * 2 > kInfinityCacheBytes;
   const auto set_grid = [&] {
     f.workgroups = remap ? 8 * (int64_t)f.map.tiles_per_xcd : (int64_t)f.map.tiles_m * f.map.tiles_n * p.G;
   };

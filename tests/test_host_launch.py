@@ -98,7 +98,10 @@ def test_b_streams_where_one_workgroup_reads_it(M, N, K, G, Gr, stream, monkeypa
 @pytest.mark.parametrize("ab", [BF16, FP8])
 def test_c_leaves_the_cache_only_above_its_size(M, N, c, nt, ab):
     """An fp32 C counts alone, a bf16 C together with the operands (K 1024)."""
-    assert ccl.ccl_debug_launch(ccl.ccl_plan_typed(M, N, 1024, 8, 2, 4096, ab, c)).c_nt == nt
+    plan = ccl.ccl_plan_typed(M, N, 1024, 8, 2, 4096, ab, c)
+    assert ccl.ccl_debug_launch(plan).c_nt == nt
+    assert ccl.ccl_debug_launch(plan, operands=2).c_nt == nt
+    assert ccl.ccl_debug_launch(plan, operands=1).c_nt == (nt or c == BF16)      # row-major, native order
 
 
 @pytest.mark.parametrize("M,N,K,G,Gr,splits,far,stream", [
