@@ -468,13 +468,14 @@ hipError_t launch_copy(const Plan& p, int op, const void* rowmajor, int64_t ld, 
   // dimension 104 -> 50 us, in rows of 1025 elements 108 -> 60 us (unpack 109
   // -> 63), 4096x2048 12.8 -> 7.6 us.
   // fp32 rows off the 16-byte grid stay at one element per access where both
-  // sides fit in the Infinity Cache together but not in the L2s (8 x 4 MiB). Us,
-  // elements -> units, pack and unpack: 40 MB 14.6 -> 18.8 and 14.1 -> 18.1, 77 MB
-  // 26.5 -> 31.1 and 25.4 -> 31.7, 109 MB 36.0 -> 41.3 and 34.3 -> 41.6; outside,
-  // 24 MB 9.8 -> 8.6 and 9.6 -> 8.6, 150 MB 66.6 -> 49.0 and 58.9 -> 48.4.
+  // sides fit in the Infinity Cache together but hardly one in the L2s (8 x 4
+  // MiB). Us, elements -> units, pack and unpack: 31 MB 13.5 -> 15.9, 40 MB 14.6
+  // -> 18.8 and 14.1 -> 18.1, 77 MB 26.5 -> 31.1 and 25.4 -> 31.7, 109 MB 36.0 ->
+  // 41.3 and 34.3 -> 41.6; outside, 24 MB 9.8 -> 8.6 and 9.6 -> 8.6, 150 MB 66.6
+  // -> 49.0 and 58.9 -> 48.4.
   const int64_t bytes = L.rows * L.cols * e;
   const bool on_grid = (a.row_bytes | a.ld_bytes | a.strip) % 16 == 0 && aligned16(rowmajor) && aligned16(ccl_buf);
-  if (e == 4 && !on_grid && bytes > (32 << 20) && 2 * bytes <= kInfinityCacheBytes) {
+  if (e == 4 && !on_grid && bytes > (28 << 20) && 2 * bytes <= kInfinityCacheBytes) {
     a.units_per_block = (uint32_t)(L.block_rows * L.block_cols);
     a.units_per_row = make_div((uint32_t)L.block_cols);
     const dim3 grid(grid_x_for(a.units_per_block, 4), (unsigned)(L.grid_r * L.grid_c));
