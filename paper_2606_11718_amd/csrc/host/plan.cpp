@@ -204,13 +204,18 @@ void choose_gemm_config(Plan* p) {
   // 128x192 and 128x320 tiles for unsplit bf16 launches where their waves of
   // 32 per XCD cost less than the tile above (same estimate). They fill
   // partitions whose 128- or 256-wide tiles leave CUs idle: 4096x1536x2048
-  // (2048x384 per XCD, 24 tiles of 256x128, now 32) 33.9 -> 31.9 us,
+  // (2048x384 per XCD, 24 tiles of 256x128, now 32) 33.9 -> 31.9 us a launch,
   // 256x16896x1280 (33 tiles of 128x128, now 22) 27.6 -> 17.9; 1920x5120x1792
   // (75 tiles of 128x128, now 30 of 128x320) 52.5 -> 42.4, 2048x5120x2048 54 ->
-  // 44.5, 4096x2560x4096 90 -> 73. Efficiency 0.75: at 0.8, 4096x3072x2048 left
-  // its 24 tiles of 256x256 for 192-wide ones, 52.6 -> 54.8; 1024x5120x4096 (20
-  // tiles of 256x128) would take 57.1 instead of 47.2 with 320-wide ones. The
-  // kernel has 64-K stages, K blocks of at least one, and 31-bit extents.
+  // 44.5, 4096x2560x4096 90 -> 73.
+  // The estimate orders the measured launches by their gain, so each width's
+  // efficiency lies between the ones that gain and the ones that do not:
+  //  * 192 (four stages): plans that need 0.700 gain 8-11 % (five shapes), those
+  //    that need 0.750 0-4 %, or lose up to 4 % (24 tiles of 256x256:
+  //    4096x3072x2048 52.6 -> 54.8, 7680x1536x512 19.0 -> 19.4; five shapes).
+  //  * 320 (two stages): at 0.708 8-13 % (five shapes), at 0.781 and 0.797 3 and
+  //    7 % (one shape each), at 0.850 1 % to -4 % (four shapes).
+  // The kernel has 64-K stages, K blocks of at least one, and 31-bit extents.
   // CCL_GEMM_WIDE=0|192|320 forbids them / takes that one wherever it exists.
   {
     const int64_t lim = ((int64_t)1 << 31) - 4096;
@@ -226,7 +231,7 @@ void choose_gemm_config(Plan* p) {
       if (!exists || pc % n || (e && n != forced_n)) continue;
       const int64_t tiles = (pr / 128) * (pc / n);
       const int64_t waves = ((tiles + g.xcd_per_chiplet - 1) / g.xcd_per_chiplet + 31) / 32;
-      const double tn = (double)waves * 128 * n / 0.75;
+      const double tn = (double)waves * 128 * n / (n == 192 ? 0.725 : 0.75);
       if (e || tn < t) {
         t = tn;
         g.wide_n = n;

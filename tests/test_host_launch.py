@@ -36,6 +36,17 @@ def test_wide_map(wide, G, Gr, tiles_m, tiles_n, monkeypatch):
     assert len(seen) == G * tiles_m * tiles_n
 
 
+@pytest.mark.parametrize("M,N,K,G,Gr,cols", [
+    (4096, 1536, 2048, 8, 2, 192), (256, 16896, 1280, 8, 2, 192), (2048, 4608, 1024, 8, 2, 192),
+    (3840, 3072, 512, 8, 2, 192), (7680, 768, 2048, 8, 4, 192),
+    (4096, 3072, 2048, 8, 2, 256), (7680, 1536, 512, 4, 2, 256), (2048, 6144, 4096, 4, 2, 256),
+    (2048, 12288, 2048, 8, 2, 128),
+    (1920, 5120, 1792, 8, 1, 320), (2560, 7680, 512, 8, 2, 320), (15360, 1280, 1024, 8, 8, 320),
+    (7680, 5120, 4096, 8, 4, 256), (12288, 3200, 1024, 8, 8, 128), (1024, 5120, 4096, 8, 2, 128)])
+def test_wide_tiles_where_they_measured_faster(M, N, K, G, Gr, cols):
+    assert ccl.ccl_debug_launch(ccl.ccl_plan(M, N, K, G, Gr, 4096)).tile_cols == cols
+
+
 @pytest.mark.parametrize("group", [1, 3, 4, 8, 16])
 def test_raster_override_reaches_wide_tiles(group, monkeypatch):
     """CCL_GEMM_GROUP_M sets the raster height of every launch."""
