@@ -15,6 +15,12 @@ from tests.test_gpu_splitk import BF16, FP32, _dev_bytes, _from_dev, _to_dev
 pytestmark = pytest.mark.gpu
 
 
+def _check_tile(wide, plan, operands=0):
+    """The launch runs 128 x wide tiles ("0": others)."""
+    run = ccl.ccl_debug_launch(plan, operands=operands)
+    assert (run.kernel, run.tile_cols) == ("gemm_k64_kernel", int(wide)) if wide != "0" else run.tile_cols in (128, 256)
+
+
 @pytest.mark.parametrize("wide,G,Gr,M,N,K", [("192",) + c for c in [
     (1, 1, 128, 384, 64), (1, 1, 128, 384, 64 * 3), (1, 1, 128, 384, 64 * 4), (1, 1, 128, 384, 64 * 7),
     (1, 1, 128, 384, 64 * 8), (1, 1, 128, 384, 64 * 13), (1, 1, 256, 768, 96), (1, 1, 128, 384, 32 * 15),
@@ -35,6 +41,7 @@ def test_equals_other_tiles(wide, G, Gr, M, N, K, monkeypatch):
     got = {}
     for n in ("0", wide):
         monkeypatch.setenv("CCL_GEMM_WIDE", n)
+        _check_tile(n, ccl.ccl_plan(M, N, K, G, Gr, 4096))
         got[n] = _gemm(A, B, M, N, K, G, Gr)
     assert np.array_equal(got["0"], got[wide])
     assert OG.within_tolerance(OG.errors(OG.decode_bf16(got[wide]), OG.gemm_fp64(A, B)))
@@ -49,6 +56,7 @@ def test_epilogues(wide, c, alpha, beta, monkeypatch):
     A, B = W.draw_array(9200, M, K, "ternary"), W.draw_array(9201, K, N, "ternary")
     C0 = W.draw_array(9202, M, N, "ternary")
     plan = ccl.ccl_plan_typed(M, N, K, G, Gr, 4096, BF16, c)
+    _check_tile(wide, plan)
     gr, gc = ccl.ccl_plan_grid(plan)
     print(f"wide epilogue {wide} c={c} alpha={alpha} beta={beta}", flush=True)
     Ac, Bc = (_dev_bytes(ccl.ccl_plan_layout(plan, op).total_bytes) for op in (ccl.CCL_A, ccl.CCL_B))
@@ -74,6 +82,7 @@ def test_rowmajor(wide, monkeypatch):
     M, N, K = 512, 4 * int(wide) * 2, 320
     A, B = W.draw_array(9300, M, K, "ternary"), W.draw_array(9301, K, N, "ternary")
     plan = ccl.ccl_plan(M, N, K, 4, 2, 4096)
+    _check_tile(wide, plan, operands=2)
     C = _dev_bytes(M * N * 2)
     ccl.ccl_gemm_rowmajor(plan, _to_dev(A), _to_dev(B), C, 1)
     got = OG.decode_bf16(_from_dev(C, np.uint16).reshape(M, N))
