@@ -7,7 +7,8 @@
 //  * gemm_kernel: bf16 operands (described below);
 //  * gemm_a2_kernel: bf16 256x256 with A staged in 64-K pairs of steps
 //    (whole-line A loads), otherwise gemm_kernel's schedule;
-//  * gemm_k64_kernel: bf16 tiles below 256x256 with 64-K stages;
+//  * gemm_k64_kernel: bf16 tiles below 256x256 with 64-K stages (and 128x192,
+//    128x320); gemm_k64_far_kernel: the same for operands of 2 GiB and more;
 //  * gemm_fp8p_kernel: fp8 operands on 256x256 tiles with 8 waves and K
 //    blocks that are multiples of 128 (v_mfma_f32_16x16x128_f8f6f4), the
 //    fragment reads pipelined across steps;
